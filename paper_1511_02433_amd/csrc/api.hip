@@ -489,15 +489,21 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
     // the per-workgroup staging and start-up; very long ones four, whose shorter last
     // round leaves less of the pass's end to the slowest shares (measured on MI355X:
     // 252.8M ratings, user-major passes 2-3% faster; with 100M ratings four rounds were
-    // slower, the staging then weighing more).
+    // slower, the staging then weighing more).  A layout of fewer windows than one
+    // round has waves gives every workgroup at least one window, and leaves waves idle
+    // rather than compute units: a pass is then one window's latency, and four
+    // waves that share a SIMD stretch it (50,000 entries: 4.2 us per pass with 128
+    // workgroups, 5.1 with 16-32, 5.9 with 7, all their waves busy; a million: 6.1 us
+    // with 256, 6.8 with 128).
     int64_t G;
-    if (opt && opt->workgroups > 0) {
+    const bool forced_G = opt && opt->workgroups > 0;
+    if (forced_G) {
         G = opt->workgroups;
     } else {
         const int64_t cus = h->cus;
         const int64_t per_wave = NP / (cus * kWaves * kWin);  // windows per wave, one round
         G = per_wave >= 120 ? 4 * cus : per_wave >= 16 ? 2 * cus : cus;
-        G = std::max<int64_t>(1, std::min<int64_t>(G, (NP + kWaves * kWin - 1) / (kWaves * kWin)));
+        G = std::max<int64_t>(1, std::min<int64_t>(G, (NP + kWin - 1) / kWin));
     }
     const int64_t wseg = !opt || opt->seg_weight == 0 ? kSegWeight
                          : std::max<int64_t>(0, opt->seg_weight);
@@ -533,23 +539,38 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
     index_work();
     auto target = [&](int64_t wt, int64_t g) { return wt / G * g + wt % G * g / G; };
     // With P == 1 (float) every share boundary moves to the start of the nearest row,
-    // when none of them changes its shares by more than an eighth: rows are then
-    // cut only between the waves of one workgroup, which finishes them at the end of
-    // the pass, and no combine kernel runs.  Otherwise the shares stay balanced and
-    // the combine kernel finishes every cut row.
+    // when none of them changes its shares by more than an eighth, or in a small copy
+    // by half a share and kSnapEntries: rows are then cut only between the waves of one
+    // workgroup, which finishes them at the end of the pass, and no combine kernel runs.
+    // Otherwise the shares stay balanced and the combine kernel finishes every cut row.
+    // kSnapEntries from both bounds make one more window per wave, about 1 us; the
+    // combine costs 3-5 us per pass (a million entries: 9.1 us per pass with it, 6.8
+    // without).  Where a bound would have to move further, half as many workgroups may
+    // still do (their shares are longer than more of the rows).
     std::vector<int64_t> snap((size_t)G + 1, -1);
     bool snapped = false;
     if (P == 1 && S_work > 0 && !h->dbl) {  // (one workgroup: nothing to move)
         const int64_t wt = work_at(NP);
-        snapped = true;
-        for (int64_t g = 1; g < G && snapped; ++g) {
-            const int64_t t = target(wt, g);
-            const int64_t sg = std::min<int64_t>(seg_of(0, pos_at(t)), S_work - 1);
-            int64_t best = sg;
-            auto miss = [&](int64_t x) { return std::llabs(work_at(seg_start[x]) - t); };
-            if (sg + 1 < S_work && miss(sg + 1) < miss(sg)) best = sg + 1;
-            snap[g] = best;
-            snapped = miss(best) <= wt / G / 8;
+        auto try_snap = [&]() {
+            const int64_t share = wt / G;
+            const int64_t most = std::max(share / 8, std::min(share / 2, kSnapEntries));
+            for (int64_t g = 1; g < G; ++g) {
+                const int64_t t = target(wt, g);
+                const int64_t sg = std::min<int64_t>(seg_of(0, pos_at(t)), S_work - 1);
+                int64_t best = sg;
+                auto miss = [&](int64_t x) { return std::llabs(work_at(seg_start[x]) - t); };
+                if (sg + 1 < S_work && miss(sg + 1) < miss(sg)) best = sg + 1;
+                snap[g] = best;
+                if (miss(best) > most) return false;
+            }
+            return true;
+        };
+        snapped = try_snap();
+        if (!snapped && !forced_G && G > 1 && NP <= kSmallCopy) {
+            const int64_t full = G;
+            G = (G + 1) / 2;
+            snapped = try_snap();
+            if (!snapped) G = full;
         }
         if (snapped) {
             for (int64_t g = 1; g < G; ++g) align_first[snap[g]] = 1;

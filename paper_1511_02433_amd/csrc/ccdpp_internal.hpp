@@ -99,6 +99,8 @@ constexpr int kLdsVecBytes = kLdsBytes - kCutSlotBytes;  // the rest holds stage
 constexpr int kCutMaxSlots = 12;          // slots of a row a workgroup finishes itself
 constexpr int kMinTiledSeg = 32;          // mean entries per segment for tiling to pay
 constexpr int kSegWeight = 4;             // default work of one segment, in entries
+constexpr int64_t kSnapEntries = 4096;    // how far a small copy's share bound may move to a row start
+constexpr int64_t kSmallCopy = 256 * kWaves * kWin;  // one window per wave of the chip (2.1M entries)
 constexpr int kChunkMid = 1;              // chunk flag: its first segment began in an earlier chunk
 constexpr int kChunkCont = 2;             // chunk flag: its last segment goes on past its end
 constexpr int kEntryPad = 64;             // entries of padding after idx and val (loads past the end)

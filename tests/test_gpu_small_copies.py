@@ -1,0 +1,54 @@
+"""The shares of small copies against the oracle: a workgroup per window, share bounds
+moved to row starts (up to half a share), half as many workgroups where a bound would
+have to move further, and the combine kernel where neither will do.
+
+Tolerance: float sums of up to 512 entries and one rounding per coordinate, over two
+features and two inner iterations: 1e-3 of the largest coordinate of a feature, as for
+every layout (about 1e-6 is seen).
+"""
+import numpy as np
+import pytest
+
+from oracle import Oracle
+from paper_1511_02433_amd import synth
+from paper_1511_02433_amd.ccdpp import CCDPP
+from gpu_util import colscaled_max_rel_err
+
+pytestmark = pytest.mark.gpu
+
+# Row lengths, columns, and whether the user-major copy needs the combine kernel.
+CASES = {
+    "one_window": ([8] * 60, 64, False),            # less than one window: one workgroup
+    "window_edge": ([64] * 16 + [8], 300, False),   # two windows and one lane group
+    "bounds_move": ([700] * 40 + [40] * 100, 900, False),   # rows longer than a window
+    "halved": ([1000] * 60, 1200, False),           # a bound a whole row away from its share
+    "combine": ([9000, 7000, 5000] + [30] * 200, 9500, True),  # rows over many workgroups
+    "many_rows": ([3] * 20_000, 500, False),        # 64 segment starts in every window
+    "one_round": ([600] * 3600, 4000, False),       # past a window per wave of the chip
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_small_copy(name):
+    lens, n, combined = CASES[name]
+    m, k, lam = len(lens), 2, 0.3
+    row, col, val, H0 = synth.lengths_problem(lens, n, k, seed=77)
+    g = CCDPP(m, n, k, lam, row, col, val)
+    info = g.info()
+    print(f"case {name}: nnz {row.size} workgroups {info['u_workgroups']}/{info['v_workgroups']} "
+          f"combined {info['u_rows_combined']}/{info['v_rows_combined']} finished in the pass "
+          f"{info['u_rows_finished_in_pass']}/{info['v_rows_finished_in_pass']}", flush=True)
+    assert (info["u_rows_combined"] > 0) == combined
+    g.set_factors(np.zeros((m, k), np.float32), H0)
+    o = Oracle(m, n, k, lam, row, col, val, H0)
+    for _ in range(2):
+        g.run(1, 2)
+        o.run(1, 2)
+        W, H = g.factors()
+        Wo, Ho = o.factors()
+        ew, eh = colscaled_max_rel_err(W, Wo), colscaled_max_rel_err(H, Ho)
+        print(f"  W err {ew:.2e}  H err {eh:.2e}", flush=True)
+        assert ew <= 1e-3 and eh <= 1e-3
+    assert g.check_consistency() == 0
+    g.close()
+    o.close()
