@@ -642,6 +642,19 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
     std::vector<char> cut_fin(cut_seg.size(), 0);  // finished by its workgroup in the pass
     L.grid = (int32_t)G;
     L.npieces = (int32_t)piece_tile.size();
+    std::vector<WgHead> heads((size_t)G);
+    std::vector<int4> firsts((size_t)G * kWaves, make_int4(0, 0, 0, 0));
+    for (int64_t g = 0; g < G; ++g) {
+        const int32_t pc = wg_piece[g];
+        heads[g] = WgHead{pc, wg_piece[g + 1], 0, 0, 0, {0, 0, 0}};
+        if (pc == wg_piece[g + 1]) continue;
+        heads[g].tile = piece_tile[pc];
+        for (int w = 0; w < kWaves; ++w)
+            firsts[g * kWaves + w] =
+                make_int4((int)piece_chunk[(int64_t)pc * (kWaves + 1) + w],
+                          (int)piece_chunk[(int64_t)pc * (kWaves + 1) + w + 1],
+                          piece_seg[(int64_t)pc * kWaves + w], chunk_flags[(int64_t)pc * kWaves + w]);
+    }
     const int64_t nslots = S + 2 * (int64_t)L.npieces * kWaves;
     if (nslots > INT32_MAX) return fail(h, CCDPP_EINVAL, "too many partial slots");
 
@@ -688,7 +701,10 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
                 wcut.push_back((int32_t)crow.size());
             }
         }
-        RCK(upload(h, &L.wg_cut, wcut));
+        for (int64_t g = 0; g < G; ++g) {
+            heads[g].cut = wcut[g];
+            heads[g].ncut = wcut[g + 1] - wcut[g];
+        }
         if (!crow.empty()) {
             RCK(upload(h, &L.cut_row, crow));
             RCK(upload(h, &L.cut_desc, cdesc_sorted));
@@ -759,7 +775,8 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
     RCK(upload(h, &L.seg_start, seg_start));
     RCK(upload(h, &L.seg_row, seg_row));
     RCK(upload(h, &L.tile_seg, tile_seg));
-    RCK(upload(h, &L.wg_piece, wg_piece));
+    RCK(upload(h, &L.wg_head, heads));
+    RCK(upload(h, &L.wg_first, firsts));
     RCK(upload(h, &L.piece_tile, piece_tile));
     RCK(upload(h, &L.piece_chunk, piece_chunk));
     RCK(upload(h, &L.piece_seg, piece_seg));

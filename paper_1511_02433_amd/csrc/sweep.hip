@@ -383,7 +383,10 @@ __device__ __forceinline__ void load_data(const PassArgs<V>& a, int32_t b, bool 
     const VV* vp = reinterpret_cast<const VV*>(a.val + b) + (int)(lo / kE);
 #pragma unroll
     for (int q = 0; q < kE / Win<V>::E; ++q) w.vv[q] = load_res<CA>(vp + 64 * q);
-    if constexpr (IDX16) {
+    if constexpr (IDX16 && CA == kCacheAll) {  // copies with cached accesses keep plain indices
+        w.c0 = load_res<CA>(
+            reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(a.idx) + b + lo));
+    } else if constexpr (IDX16) {
         bool dz = false;
         if (a.dmask) {
             const int32_t wi = b / kWin;
@@ -520,7 +523,7 @@ __device__ __forceinline__ void window(const PassArgs<V>& a, const Gather<V>& gx
                                        Win<V>& cur, Win<V>& nxt, Win<V>& nn, int lane,
                                        uint32_t le, DMask& dm) {
     using N = Needs<MODE>;
-    if constexpr (IDX16) {
+    if constexpr (IDX16 && CA != kCacheAll) {
         if (cur.dz) {  // back to the plain format: 8 indices packed in pairs
             uint32_t c[8];
             delta_decode(cur.c0.x, cur.c0.y, cur.c0.z, (uint32_t)a.pad, c);
@@ -755,43 +758,40 @@ __device__ __forceinline__ void pass_main(const PassArgs<V>& a) {
     const int lane = (int)(threadIdx.x & 63u);
 
     // P == 1, float: the rows cut between this workgroup's waves (at most 15), one per
-    // lane of wave 0, requested now and finished at the end from the waves' LDS
-    // partials.  (The double kernels are short of registers for it: their layouts
-    // leave every cut row to the combine kernel.)
+    // lane of wave 0, finished at the end from the waves' LDS partials.  (The double
+    // kernels are short of registers for it: their layouts leave every cut row to the
+    // combine kernel.)
     constexpr bool CUT = MODE != kModeFlush && P1 && sizeof(V) == 4;
-    constexpr bool CUT_EARLY = CUT;
-    int cut0 = 0, ncut = 0, crow = 0;
+    const WgHead head = a.wg_head[wg];
+    const int4 first = a.wg_first[wg * kWaves + wave];
+    uint32_t crow = 0;
     uint64_t cdesc = 0;
-    if constexpr (CUT) {
-        cut0 = a.wg_cut[wg];
-        ncut = a.wg_cut[wg + 1] - cut0;
-    }
-    if constexpr (CUT_EARLY) {
-        if (wave == 0 && lane < ncut) {
-            crow = a.cut_row[cut0 + lane];
-            cdesc = a.cut_desc[cut0 + lane];
-        }
-    }
-    if constexpr (MODE != kModeFlush && P1) {
-        // The rows after the last non-empty one have no entries: coordinate 0.
-        for (int i = wg * kWG + (int)threadIdx.x; i < a.rows - a.nseg_ne; i += gridDim.x * kWG)
-            a.y[a.nseg_ne + i] = coordinate<V>(0.0, 0.0, a.lambda);
-    }
 
     double sse = 0.0;
     int staged = -1;
     DMask dm{0, -1};
-    for (int pc = a.wg_piece[wg]; pc < a.wg_piece[wg + 1]; ++pc) {
-        const int32_t c0 = (int32_t)a.piece_chunk[pc * (kWaves + 1) + wave];
-        const int32_t c1 = (int32_t)a.piece_chunk[pc * (kWaves + 1) + wave + 1];
+    for (int pc = head.pc; pc < head.pc_end; ++pc) {
+        int32_t c0 = first.x, c1 = first.y;
+        int s0 = first.z, flags = first.w;
         const int gc = pc * kWaves + wave;
-        const int s0 = a.piece_seg[gc], flags = a.chunk_flags[gc];
+        if (!P1 && pc > head.pc) {
+            c0 = (int32_t)a.piece_chunk[pc * (kWaves + 1) + wave];
+            c1 = (int32_t)a.piece_chunk[pc * (kWaves + 1) + wave + 1];
+            s0 = a.piece_seg[gc];
+            flags = a.chunk_flags[gc];
+        }
         // The chunk's first windows are requested before the staging, which they do
-        // not depend on.
+        // not depend on, and so are the cut rows.
         Win<V> wa, wb;
         if (c0 < c1) begin_chunk<MODE, IDX16, CA, V>(a, c0, c1, s0, flags, lane, wa, wb, dm);
+        if constexpr (CUT) {
+            if (wave == 0 && lane < head.ncut) {
+                crow = (uint32_t)a.cut_row[head.cut + lane];
+                cdesc = a.cut_desc[head.cut + lane];
+            }
+        }
         if constexpr (STAGED) {
-            const int tile = a.piece_tile[pc];
+            const int tile = P1 ? 0 : pc == head.pc ? head.tile : a.piece_tile[pc];
             if (tile != staged) {
                 if (staged >= 0) __syncthreads();  // every wave is done with the old slice
                 stage_tile<MODE, HOT, V>(a, tile, lds, gx);
@@ -802,27 +802,29 @@ __device__ __forceinline__ void pass_main(const PassArgs<V>& a) {
         if (c0 < c1)
             run_chunk<MODE, STAGED, IDX16, P1, CA, XQ, V>(a, gx, c0, c1, s0, flags, gc, lane, wa, wb, sse,
                                                            dm);
+        if constexpr (P1) break;  // one tile: a workgroup has one piece at most
     }
     if constexpr (MODE == kModeFlush) {
         const double t = wave_sum(sse);
         if (lane == 0) a.sse_part[wg * kWaves + wave] = t;
     } else if constexpr (P1) {
+        // The rows after the last non-empty one have no entries: coordinate 0.
+        for (int i = wg * kWG + (int)threadIdx.x; i < a.rows - a.nseg_ne; i += gridDim.x * kWG)
+            a.y[a.nseg_ne + i] = coordinate<V>(0.0, 0.0, a.lambda);
         // Rows cut between this workgroup's waves: their partials, in entry order.
-        if (ncut > 0) {       // the same for every thread of the workgroup
-            __syncthreads();  // every wave's partials are in LDS
-            if (wave == 0 && lane < ncut) {
-                if constexpr (!CUT_EARLY) {
-                    crow = a.cut_row[cut0 + lane];
-                    cdesc = a.cut_desc[cut0 + lane];
+        if constexpr (CUT) {
+            if (head.ncut > 0) {  // the same for every thread of the workgroup
+                __syncthreads();  // every wave's partials are in LDS
+                if (wave == 0 && lane < head.ncut) {
+                    const int n = (int)(cdesc & 15u) + 1;
+                    double num = 0.0, den = 0.0;
+                    for (int i = 0; i < n; ++i) {
+                        const double2 pv = cut_slots(a)[(int)((cdesc >> (4 + 5 * i)) & 31u)];
+                        num += pv.x;
+                        den += pv.y;
+                    }
+                    a.y[crow] = coordinate<V>(num, den, a.lambda);
                 }
-                const int n = (int)(cdesc & 15u) + 1;
-                double num = 0.0, den = 0.0;
-                for (int i = 0; i < n; ++i) {
-                    const double2 pv = cut_slots(a)[(int)((cdesc >> (4 + 5 * i)) & 31u)];
-                    num += pv.x;
-                    den += pv.y;
-                }
-                a.y[crow] = coordinate<V>(num, den, a.lambda);
             }
         }
     }
@@ -1050,21 +1052,21 @@ hipError_t launch_pass(const Layout& L, PassMode mode, const V* x, const V* p, c
     // gathers and hot layouts have P == 1.
     if (staged ? !L.idx16 : L.P != 1) return hipErrorInvalidValue;
     if (hot && L.idx16) return hipErrorInvalidValue;
-    // Write-back cache policies: tiled float copies only.
+    // Write-back cache policies: tiled float copies only.  Cached copies have plain indices.
+    if (L.cache == kCacheAll && L.dmask) return hipErrorInvalidValue;
     if (L.cache != kCacheStream && (!staged || sizeof(V) != 4)) return hipErrorInvalidValue;
     PassArgs<V> a{};
     a.idx = L.idx;
     a.val = static_cast<V*>(L.val);
-    a.wg_piece = L.wg_piece;
+    a.wg_head = L.wg_head;
+    a.wg_first = L.wg_first;
     a.piece_tile = L.piece_tile;
     a.piece_chunk = L.piece_chunk;
     a.piece_seg = L.piece_seg;
     a.chunk_flags = L.chunk_flags;
     a.dmask = L.dmask;
-    a.wg_cut = L.wg_cut;
     a.cut_row = L.cut_row;
     a.cut_desc = L.cut_desc;
-    if (L.P == 1 && !L.wg_cut) return hipErrorInvalidValue;
     a.x = x;
     a.p = p;
     a.pp = pp;
