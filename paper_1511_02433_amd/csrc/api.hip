@@ -118,7 +118,7 @@ struct ccdpp {
     // Value type of the residual, the factors and the sweep arithmetic: float, or
     // double with options.precision = 1.  The arrays below hold that type.
     bool dbl = false;
-    void* A = nullptr;             // A[e], the rating of entry e
+    void* A = nullptr;             // the ratings, in the user-major copy's value slots
     void* fseg[3] = {};            // P > 1: own factor columns spread over segments (k x S)
     void* W = nullptr;             // k x m: W[t*m + i]
     void* H = nullptr;             // k x n
@@ -1152,8 +1152,8 @@ int create_device(ccdpp* h, const int32_t* row, const int32_t* col, const float*
     RCK(with_value_type(h, [&](auto z) -> int {
         using V = decltype(z);
         V *A, *W, *H, *u, *v;
-        HIPCK(h, dalloc(h, &A, N));
-        HIPCK(h, (launch_copy_mapped<V, V>(as<V>(h->L[0].val), h->pos0, A, nullptr, N, s)));
+        HIPCK(h, dalloc(h, &A, h->L[0].npad));
+        HIPCK(h, launch_copy<V>(as<V>(h->L[0].val), A, h->L[0].npad, s));
         // Factors: W = 0 (Algorithm 3), H from the seed; scratch.
         HIPCK(h, dalloc(h, &W, (int64_t)h->k * m));
         HIPCK(h, dalloc(h, &H, (int64_t)h->k * n));
@@ -1429,10 +1429,44 @@ int launch_sq_sum_any(ccdpp* h, void* p, int64_t n) {
         return CCDPP_OK;
     });
 }
+// Row-major copies of the factors for the held-out error, each when the held-out set is
+// large enough against its rows to pay for the turn and for the memory: the error costs
+// about 3 ps per entry, feature and column-major factor, under 1 from a row-major
+// one; the turn 2 ps per value, and fresh memory another 3 (taken for few rows at a time
+// in practice: the items).  m = 480,189, n = 17,770, k = 40, 1.4M entries grouped by
+// user: 333 us from the column-major factors, 180 with HT, 73 + 48 for the turn
+// with both.  Without memory the column-major factors serve as they are.
+struct RowFactors {
+    Tmp tw, th;
+    char *w = nullptr, *h = nullptr;
+    void allocate(const ccdpp* p, int64_t nnz) {
+        const int64_t row = (int64_t)ccdk::row_pitch(p->k) * (p->dbl ? 8 : 4);
+        auto side = [&](Tmp& t, char** c, int64_t rows) {
+            if (nnz >= 8 * rows && talloc(t, c, rows * row) != hipSuccess) (void)hipGetLastError();
+        };
+        side(tw, &w, p->m);
+        side(th, &h, p->n);
+    }
+};
 int launch_test_err_any(ccdpp* h, const int32_t* dr, const int32_t* dc, const float* dv,
-                        int64_t nnz, double* part = nullptr, double* rejected = nullptr) {
+                        int64_t nnz, const RowFactors* rows, double* part = nullptr,
+                        double* rejected = nullptr) {
     return with_value_type(h, [&](auto z) -> int {
         using V = decltype(z);
+        if (rows && (rows->w || rows->h)) {
+            const int32_t pitch = ccdk::row_pitch(h->k);
+            if (rows->w)
+                HIPCK(h, (ccdk::launch_factor_out<V, V>(as<V>(h->W), nullptr, h->m, h->k, pitch,
+                                                        as<V>(rows->w), h->stream)));
+            if (rows->h)
+                HIPCK(h, (ccdk::launch_factor_out<V, V>(as<V>(h->H), nullptr, h->n, h->k, pitch,
+                                                        as<V>(rows->h), h->stream)));
+            HIPCK(h, ccdk::launch_test_err_rows<V>(dr, dc, dv, nnz, h->rold2new, h->cold2new,
+                                                   as<V>(h->W), as<V>(h->H), as<V>(rows->w),
+                                                   as<V>(rows->h), h->m, h->n, h->k, pitch, h->sse_part,
+                                                   kReduceParts, h->stream));
+            return CCDPP_OK;
+        }
         HIPCK(h, ccdk::launch_test_err<V>(dr, dc, dv, nnz, h->rold2new, h->cold2new, as<V>(h->W),
                                           as<V>(h->H), h->m, h->n, h->k,
                                           part ? part : h->sse_part, kReduceParts, rejected,
@@ -1603,8 +1637,8 @@ int get_factors_impl(ccdpp* h, S* W, S* H) {
     if (H) HIPCK(h, talloc(th, &dH, h->n * h->k));
     RCK(with_value_type(h, [&](auto z) -> int {
         using V = decltype(z);
-        if (W) HIPCK(h, (ccdk::launch_gather_factor_out<V, S>(as<V>(h->W), h->rold2new, h->m, h->k, dW, s)));
-        if (H) HIPCK(h, (ccdk::launch_gather_factor_out<V, S>(as<V>(h->H), h->cold2new, h->n, h->k, dH, s)));
+        if (W) HIPCK(h, (ccdk::launch_factor_out<V, S>(as<V>(h->W), h->rnew2old, h->m, h->k, h->k, dW, s)));
+        if (H) HIPCK(h, (ccdk::launch_factor_out<V, S>(as<V>(h->H), h->cnew2old, h->n, h->k, h->k, dH, s)));
         HIPCK(h, hipStreamSynchronize(s));
         return CCDPP_OK;
     }));
@@ -1629,9 +1663,12 @@ int set_factors_impl(ccdpp* h, const S* W, const S* H) {
     // Staging buffers first: a failed allocation leaves the factors and the residual
     // as they were.
     S *dW = nullptr, *dH = nullptr;
-    Tmp tw, th;
+    char* ht = nullptr;  // H row-major, for the rebuild
+    const int32_t pitch = ccdk::row_pitch(h->k);
+    Tmp tw, th, tht;
     if (W) HIPCK(h, talloc(tw, &dW, h->m * h->k));
     if (H) HIPCK(h, talloc(th, &dH, h->n * h->k));
+    HIPCK(h, talloc(tht, &ht, h->n * pitch * (h->dbl ? 8 : 4)));
     if (W) HIPCK(h, hipMemcpyAsync(dW, W, h->m * h->k * sizeof(S), hipMemcpyHostToDevice, s));
     if (H) HIPCK(h, hipMemcpyAsync(dH, H, h->n * h->k * sizeof(S), hipMemcpyHostToDevice, s));
     RCK(with_value_type(h, [&](auto z) -> int {
@@ -1639,8 +1676,9 @@ int set_factors_impl(ccdpp* h, const S* W, const S* H) {
         if (W) HIPCK(h, (ccdk::launch_scatter_factor_in<S, V>(dW, h->rnew2old, h->m, h->k, as<V>(h->W), s)));
         if (H) HIPCK(h, (ccdk::launch_scatter_factor_in<S, V>(dH, h->cnew2old, h->n, h->k, as<V>(h->H), s)));
         RCK(spread_factors(h));
-        HIPCK(h, ccdk::launch_rebuild_residual<V>(h->L[0], h->pos0, as<V>(h->A), as<V>(h->W),
-                                                  as<V>(h->H), h->m, h->n, h->k, s));
+        HIPCK(h, (ccdk::launch_factor_out<V, V>(as<V>(h->H), nullptr, h->n, h->k, pitch, as<V>(ht), s)));
+        HIPCK(h, ccdk::launch_rebuild_residual<V>(h->L[0], as<V>(h->A), as<V>(h->W), as<V>(ht), h->m,
+                                                  h->k, pitch, s));
         HIPCK(h, (ccdk::launch_copy_mapped<V, V>(as<V>(h->L[0].val), h->pos0, as<V>(h->L[1].val),
                                                 h->map01, h->nnz, s)));
         HIPCK(h, hipStreamSynchronize(s));
@@ -1743,6 +1781,7 @@ int ccdpp_run_until(ccdpp_t* h, int32_t max_outer, int32_t inner, double rel_tol
     int32_t *dr = nullptr, *dc = nullptr;
     float* dv = nullptr;
     Tmp tr, tc, tv;
+    RowFactors rows;
     if (test_nnz > 0) {
         HIPCK(h, talloc(tr, &dr, test_nnz));
         HIPCK(h, talloc(tc, &dc, test_nnz));
@@ -1750,6 +1789,7 @@ int ccdpp_run_until(ccdpp_t* h, int32_t max_outer, int32_t inner, double rel_tol
         HIPCK(h, hipMemcpyAsync(dr, test_row, test_nnz * 4, hipMemcpyHostToDevice, s));
         HIPCK(h, hipMemcpyAsync(dc, test_col, test_nnz * 4, hipMemcpyHostToDevice, s));
         HIPCK(h, hipMemcpyAsync(dv, test_val, test_nnz * 4, hipMemcpyHostToDevice, s));
+        if (max_outer > 0) rows.allocate(h, test_nnz);
     }
     // A fixed-order float64 sum on the device, read back.
     auto reduce = [&](double* out) -> int {
@@ -1769,7 +1809,7 @@ int ccdpp_run_until(ccdpp_t* h, int32_t max_outer, int32_t inner, double rel_tol
         RCK(launch_sq_sum_any(h, h->H, h->n * h->k));
         RCK(reduce(&h2));
         if (test_nnz > 0) {
-            RCK(launch_test_err_any(h, dr, dc, dv, test_nnz));
+            RCK(launch_test_err_any(h, dr, dc, dv, test_nnz, &rows));
             double sum = 0.0;
             RCK(reduce(&sum));
             te = std::sqrt(sum / (double)test_nnz);
@@ -1829,7 +1869,9 @@ int ccdpp_rmse(ccdpp_t* h, int64_t nnz, const int32_t* row, const int32_t* col, 
     HIPCK(h, hipMemcpyAsync(dr, row, nnz * 4, hipMemcpyHostToDevice, s));
     HIPCK(h, hipMemcpyAsync(dc, col, nnz * 4, hipMemcpyHostToDevice, s));
     HIPCK(h, hipMemcpyAsync(dv, val, nnz * 4, hipMemcpyHostToDevice, s));
-    RCK(launch_test_err_any(h, dr, dc, dv, nnz));
+    RowFactors rows;
+    rows.allocate(h, nnz);
+    RCK(launch_test_err_any(h, dr, dc, dv, nnz, &rows));
     HIPCK(h, ccdk::launch_reduce_sum(h->sse_part, kReduceParts, h->d_scalar, s));
     double sum = 0.0;
     HIPCK(h, hipMemcpyAsync(&sum, h->d_scalar, 8, hipMemcpyDeviceToHost, s));
@@ -1850,7 +1892,7 @@ int ccdpp_rmse_noalloc(ccdpp_t* h, int64_t nnz, const int32_t* row, const int32_
     double* sc = h->scratch;
     // The same kernel as ccdpp_rmse with the triplets checked on the device (they
     // cannot be checked on the host), partials and counts in the scratch array.
-    RCK(launch_test_err_any(h, row, col, val, nnz, sc + kNaPart, sc + kNaRejected));
+    RCK(launch_test_err_any(h, row, col, val, nnz, nullptr, sc + kNaPart, sc + kNaRejected));
     HIPCK(h, ccdk::launch_reduce_sum(sc + kNaPart, kReduceParts, sc + kNaTotals, s));
     HIPCK(h, ccdk::launch_reduce_sum(sc + kNaRejected, kReduceParts, sc + kNaTotals + 1, s));
     double tot[2] = {0.0, 0.0};

@@ -30,6 +30,26 @@ inline dim3 grid_for(int64_t n, int64_t cap = 1 << 20) {
     return dim3((unsigned)g);
 }
 
+// The elements a thread visits in the copies between the two orders of the entries: each
+// eighth of the range is one XCD's (workgroups go to the XCDs round-robin), walked
+// front to back by its workgroups together.  The stores in flight on an XCD then fall
+// into few lines of the other order (about one per row of its tile), which its own
+// L2 merges.  (Between the copies of 10M ratings: 88 -> 59 us; of 100M: 1230 -> 1190 us.
+// The build's maps, which mostly gather, gained nothing from it.)
+struct Span {
+    int64_t lo, hi, step;
+};
+__device__ __forceinline__ Span xcd_span(int64_t n) {
+    const int64_t per = ((n + 7) / 8 + kT - 1) / kT * kT;
+    const int64_t first = (int64_t)(blockIdx.x & 7u) * per;
+    return Span{first + (int64_t)(blockIdx.x >> 3) * kT + threadIdx.x, min(n, first + per),
+                (int64_t)(gridDim.x >> 3) * kT};
+}
+inline dim3 xcd_grid(int64_t n) {
+    const int64_t per = ((n + 7) / 8 + kT - 1) / kT;
+    return dim3((unsigned)(8 * std::max<int64_t>(1, std::min<int64_t>(per, 1 << 17))));
+}
+
 // Adds one to count[key] for every valid lane of the wave.  A lane whose key equals
 // the previous lane's (a run, as in triplets grouped by row) adds through the run's
 // first lane, so a run costs one atomic.  The valid lanes are a prefix of the wave,
@@ -117,8 +137,7 @@ __global__ void __launch_bounds__(kT) k_seg_histogram(const int32_t* __restrict_
 __global__ void k_seg_keys(const int32_t* __restrict__ lrow, const int32_t* __restrict__ lcol,
                            const int32_t* __restrict__ segid, int64_t nnz, int32_t rows, int32_t T,
                            int cbits, uint64_t* __restrict__ keys, int32_t* __restrict__ ids) {
-    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnz;
-         e += (int64_t)gridDim.x * kT) {
+    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnz; e += (int64_t)gridDim.x * kT) {
         const int64_t c = lcol[e];
         const int64_t p = c / T;
         const uint64_t s = (uint64_t)segid[p * rows + lrow[e]];
@@ -141,8 +160,7 @@ __global__ void k_layout_fill(const uint64_t* __restrict__ keys, const int32_t* 
                               uint64_t mask, const int32_t* __restrict__ seg_off, uint32_t swz_lim,
                               I* __restrict__ idx, V* __restrict__ val,
                               int32_t* __restrict__ pos) {
-    for (int64_t q = (int64_t)blockIdx.x * kT + threadIdx.x; q < nnz;
-         q += (int64_t)gridDim.x * kT) {
+    for (int64_t q = (int64_t)blockIdx.x * kT + threadIdx.x; q < nnz; q += (int64_t)gridDim.x * kT) {
         const uint64_t key = keys[q];
         const int64_t p = q + seg_off[key >> cbits];
         const uint32_t c = (uint32_t)(key & mask);
@@ -183,7 +201,8 @@ __global__ void k_slot_map(const int32_t* __restrict__ from, const int32_t* __re
 template <class V>
 __global__ void k_copy_slots(const V* __restrict__ src, const int32_t* __restrict__ map,
                              V* __restrict__ dst, int64_t n) {
-    for (int64_t f = (int64_t)blockIdx.x * kT + threadIdx.x; f < n; f += (int64_t)gridDim.x * kT) {
+    const Span sp = xcd_span(n);
+    for (int64_t f = sp.lo; f < sp.hi; f += sp.step) {
         const int32_t g = map[f];
         if (g >= 0) dst[g] = src[f];
     }
@@ -195,30 +214,72 @@ __global__ void k_fill(V* __restrict__ dst, V value, int64_t n) {
         dst[i] = value;
 }
 
+// Tiles of kFR rows by kFT columns of a factor matrix, turned in LDS between the
+// column-major order over relabelled ids (rows contiguous) and a row-major one (columns
+// contiguous), so that both sides are read and written in whole lines: bound by
+// the two streams.  (m = 480,189, k = 40, float: in 351 -> 63 us, out 143 -> 59 us.)
+constexpr int kFR = 64, kFT = 32;
+
 // colmajor[t * rows + i'] = rowmajor[new2old[i'] * k + t]
 template <class S, class V>
-__global__ void k_factor_in(const S* __restrict__ rowmajor, const int32_t* __restrict__ new2old,
-                            int64_t rows, int32_t k, V* __restrict__ colmajor) {
-    const int64_t total = rows * k;
-    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * kT) {
-        const int64_t t = e / rows;
-        const int64_t i = e - t * rows;
-        colmajor[e] = (V)rowmajor[(int64_t)new2old[i] * k + t];
+__global__ __launch_bounds__(kT) void k_factor_in(const S* __restrict__ rowmajor,
+                                                  const int32_t* __restrict__ new2old, int64_t rows,
+                                                  int32_t k, V* __restrict__ colmajor) {
+    __shared__ V tile[kFT][kFR + 1];
+    const int64_t r0 = (int64_t)blockIdx.x * kFR;
+    const int nr = (int)min((int64_t)kFR, rows - r0);
+    for (int t0 = 0; t0 < k; t0 += kFT) {
+        const int nt = min(kFT, k - t0);
+        for (int e = threadIdx.x; e < nr * nt; e += kT) {
+            const int r = e / nt, t = e - r * nt;
+            tile[t][r] = (V)rowmajor[(int64_t)new2old[r0 + r] * k + t0 + t];
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < nt * kFR; e += kT) {
+            const int t = e / kFR, r = e % kFR;
+            if (r < nr) colmajor[(int64_t)(t0 + t) * rows + r0 + r] = tile[t][r];
+        }
+        __syncthreads();
     }
 }
 
-// rowmajor[i * k + t] = colmajor[t * rows + old2new[i]]
+// rowmajor[new2old[i'] * pitch + t] = colmajor[t * rows + i'], zero for k <= t < pitch
+// (new2old null: row i')
 template <class V, class S>
-__global__ void k_factor_out(const V* __restrict__ colmajor, const int32_t* __restrict__ old2new,
-                             int64_t rows, int32_t k, S* __restrict__ rowmajor) {
-    const int64_t total = rows * k;
-    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * kT) {
-        const int64_t i = e / k;
-        const int64_t t = e - i * k;
-        rowmajor[e] = (S)colmajor[t * rows + old2new[i]];
+__global__ __launch_bounds__(kT) void k_factor_out(const V* __restrict__ colmajor,
+                                                   const int32_t* __restrict__ new2old, int64_t rows,
+                                                   int32_t k, int32_t pitch, S* __restrict__ rowmajor) {
+    __shared__ V tile[kFT][kFR + 1];
+    const int64_t r0 = (int64_t)blockIdx.x * kFR;
+    const int nr = (int)min((int64_t)kFR, rows - r0);
+    for (int t0 = 0; t0 < pitch; t0 += kFT) {
+        const int nt = min(kFT, pitch - t0);
+        for (int e = threadIdx.x; e < nt * kFR; e += kT) {
+            const int t = e / kFR, r = e % kFR;
+            if (r < nr)
+                tile[t][r] = t0 + t < k ? colmajor[(int64_t)(t0 + t) * rows + r0 + r] : V(0);
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < nr * nt; e += kT) {
+            const int r = e / nt, t = e - r * nt;
+            const int64_t i = new2old ? new2old[r0 + r] : r0 + r;
+            rowmajor[i * pitch + t0 + t] = (S)tile[t][r];
+        }
+        __syncthreads();
     }
+}
+
+// Four values of a row of a row-major factor copy whose pitch is a multiple of 4.
+template <class V> struct Row4 {
+    V v[4];
+};
+template <class V>
+__device__ __forceinline__ Row4<V> load4(const V* p) {
+    struct alignas(16) Q {
+        V v[4];
+    };
+    const Q q = *reinterpret_cast<const Q*>(p);
+    return Row4<V>{{q.v[0], q.v[1], q.v[2], q.v[3]}};
 }
 
 // Rewrites, one wave per window, every window whose lanes' valid entries each climb
@@ -260,54 +321,134 @@ __global__ __launch_bounds__(kT) void k_delta_windows(uint16_t* __restrict__ idx
                             1ull << (w & 63));
 }
 
-// Index of entry q as the plain format holds it, from a delta-coded window when
-// its bit is set.
-template <class I>
-__device__ __forceinline__ uint32_t index_at(const I* idx, const uint64_t* dmask, uint32_t pad,
-                                             int64_t q) {
-    const int64_t w = q / kWin;
-    if (dmask && ((dmask[w >> 6] >> (w & 63)) & 1u)) {
-        const uint32_t* rec = reinterpret_cast<const uint32_t*>(idx + w * kWin) + 3 * ((q % kWin) / kE);
-        uint32_t c[8];
-        delta_decode(rec[0], rec[1], rec[2], pad, c);
-        return c[q % kE];
+// One step of a sum over lanes that also deals the values out: of the 2 * N values, the
+// lanes whose bit is set keep the upper half and the others the lower one, each
+// adding its partner's (the lane CTRL reads, whose bit differs) values of that half.
+template <int CTRL>
+__device__ __forceinline__ double dpp_from(double x) {
+    int2 v = __builtin_bit_cast(int2, x);
+    v.x = __builtin_amdgcn_update_dpp(0, v.x, CTRL, 0xF, 0xF, false);
+    v.y = __builtin_amdgcn_update_dpp(0, v.y, CTRL, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, v);
+}
+template <int CTRL, int N>
+__device__ __forceinline__ void deal(double* v, bool upper) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const double keep = upper ? v[N + i] : v[i], give = upper ? v[i] : v[N + i];
+        v[i] = keep + dpp_from<CTRL>(give);
     }
-    return (uint32_t)idx[q];
 }
 
-// R = A - w_i^T h_j for every entry of the user-major layout (prediction summed
-// in fp64 over ascending features, one rounding to fp32).  Entry e (A[e], in the
-// unpadded layout order) has its value in slot pos[e]; its segment, and from it the
-// row and the tile, are found by binary search.
-template <class I, class V>
-__global__ void k_rebuild(const int64_t* __restrict__ seg_start, int64_t nseg,
-                          const int32_t* __restrict__ seg_row, const int32_t* __restrict__ tile_seg,
-                          int32_t P, int32_t T, uint32_t swz_lim, const I* __restrict__ idx,
-                          const uint64_t* __restrict__ dmask, uint32_t pad,
-                          const int32_t* __restrict__ pos, const V* __restrict__ A,
-                          const V* __restrict__ W, const V* __restrict__ H, int64_t m,
-                          int64_t n, int32_t k, int64_t nnz, V* __restrict__ val) {
-    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnz;
-         e += (int64_t)gridDim.x * kT) {
-        const int64_t f = pos[e];         // value slot
-        const int64_t q = val_entry<V>(f);   // entry position
-        int64_t lo = 0, hi = nseg;  // last s with seg_start[s] <= q
+// R = A - w_i^T h_j for every entry of the user-major layout (prediction summed in fp64,
+// one rounding to the value type).  A wave takes a window: lane l finds the segment of
+// its kE entries (they belong to one) and from it the row and the tile, and puts
+// their columns in LDS.  Then groups of G lanes take the window's lanes' entries in
+// turn, each lane four features of every row h_j at a time, so that a row of HT (H
+// row-major, rows of `pitch` values, a multiple of 4, zero past k) is read in whole
+// lines, and the lanes' sums are added over the group.  A holds the ratings in
+// the slots of val.
+// Bound by L2: one lane per entry fetched a 128-byte line per 16 bytes of a row, at
+// 31 TB/s.  (m = 480,189, n = 17,770, 100.5M ratings, k = 40: 8.3 ms with one
+// 4-byte gather per entry and feature, 4.1 with 16-byte ones, 2.9 now.)
+template <class I, class V, int G>
+__global__ __launch_bounds__(kT) void k_rebuild(
+    const int64_t* __restrict__ seg_start, int64_t nseg, const int32_t* __restrict__ seg_row,
+    const int32_t* __restrict__ tile_seg, int32_t P, int32_t T, uint32_t swz_lim,
+    const I* __restrict__ idx, const uint64_t* __restrict__ dmask, uint32_t pad,
+    const V* __restrict__ A, const V* __restrict__ W, const V* __restrict__ HT, int64_t m, int32_t k,
+    int32_t pitch, int64_t npad, V* __restrict__ val) {
+    constexpr uint32_t kNone = 0xFFFFFFFFu;  // a padding entry
+    __shared__ uint4 cols[kT / 64][64][2];
+    const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63u);
+    const int grp = lane / G, g = lane % G;
+    for (int64_t w = (int64_t)blockIdx.x * (kT / 64) + wave; w < npad / kWin;
+         w += (int64_t)gridDim.x * (kT / 64)) {
+        const int64_t q0 = w * kWin + lane * kE;
+        int64_t lo = 0, hi = nseg;  // last s with seg_start[s] <= q0
         while (hi - lo > 1) {
             const int64_t mid = (lo + hi) >> 1;
-            if (seg_start[mid] <= q) lo = mid; else hi = mid;
+            if (seg_start[mid] <= q0) lo = mid; else hi = mid;
         }
         int32_t plo = 0, phi = P;  // last tile p with tile_seg[p] <= s
         while (phi - plo > 1) {
             const int32_t mid = (plo + phi) >> 1;
             if (tile_seg[mid] <= lo) plo = mid; else phi = mid;
         }
-        const int64_t i = seg_row[lo];
-        const uint32_t c = index_at<I>(idx, dmask, pad, q) & IndexBits<I>::mask;
-        const int64_t j = (int64_t)plo * T + (int64_t)(c < swz_lim ? lds_swizzle(c) : c);
-        double pred = 0.0;
-        for (int32_t t = 0; t < k; ++t)
-            pred = __builtin_fma((double)W[(int64_t)t * m + i], (double)H[(int64_t)t * n + j], pred);
-        val[f] = (V)((double)A[e] - pred);
+        const int32_t row = seg_row[lo];
+        uint32_t c[kE];
+        if constexpr (sizeof(I) == 2) {
+            if (dmask && ((dmask[w >> 6] >> (w & 63)) & 1u)) {
+                const uint32_t* rec = reinterpret_cast<const uint32_t*>(idx + w * kWin) + 3 * lane;
+                delta_decode(rec[0], rec[1], rec[2], pad, c);
+            } else {
+                const uint4 v = *reinterpret_cast<const uint4*>(idx + q0);
+                const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
+                for (int e = 0; e < kE; ++e) c[e] = (wd[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
+            }
+        } else {
+            const uint4 v0 = *reinterpret_cast<const uint4*>(idx + q0);
+            const uint4 v1 = *reinterpret_cast<const uint4*>(idx + q0 + 4);
+            const uint32_t wd[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+            for (int e = 0; e < kE; ++e) c[e] = wd[e];
+        }
+        for (int e = 0; e < kE; ++e) {
+            const uint32_t u = c[e] & IndexBits<I>::mask;
+            c[e] = u == pad ? kNone : (uint32_t)plo * (uint32_t)T + (u < swz_lim ? lds_swizzle(u) : u);
+        }
+        __builtin_amdgcn_wave_barrier();  // the last window's reads come before these writes
+        cols[wave][lane][0] = make_uint4(c[0], c[1], c[2], c[3]);
+        cols[wave][lane][1] = make_uint4(c[4], c[5], c[6], c[7]);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int it = 0; it < G; ++it) {
+            const int b = it * (64 / G) + grp;  // whose entries
+            const int64_t i = __shfl(row, b);
+            const uint4 ca = cols[wave][b][0], cb = cols[wave][b][1];
+            const uint32_t j[kE] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
+            double pred[kE] = {};
+            for (int32_t t = 4 * g; t < pitch; t += 4 * G) {
+                Row4<V> wt;
+                for (int u = 0; u < 4; ++u) wt.v[u] = t + u < k ? W[(int64_t)(t + u) * m + i] : V(0);
+                Row4<V> h[kE];
+#pragma unroll
+                for (int e = 0; e < kE; ++e)
+                    h[e] = load4(HT + (j[e] == kNone ? 0 : (int64_t)j[e]) * pitch + t);
+#pragma unroll
+                for (int e = 0; e < kE; ++e)
+                    for (int u = 0; u < 4; ++u)
+                        pred[e] = __builtin_fma((double)wt.v[u], (double)h[e].v[u], pred[e]);
+            }
+            // Sums over the group; value v0 + i of the lane's kept ones ends in pred[i].
+            int v0;
+            if constexpr (G == 16) {
+                deal<0x140, 4>(pred, g & 8);  // row_mirror: lane 15 - g
+                deal<0x141, 2>(pred, g & 4);  // row_half_mirror: lane 7 - g of its half
+                deal<0x4E, 1>(pred, g & 2);   // quad_perm: lane ^ 2
+                pred[0] += dpp_from<0xB1>(pred[0]);  // quad_perm: lane ^ 1
+                v0 = g >> 1;
+            } else if constexpr (G == 8) {
+                deal<0x141, 4>(pred, g & 4);
+                deal<0x4E, 2>(pred, g & 2);
+                deal<0xB1, 1>(pred, g & 1);
+                v0 = g;
+            } else {
+                deal<0x4E, 4>(pred, g & 2);
+                deal<0xB1, 2>(pred, g & 1);
+                v0 = 2 * g;
+            }
+            constexpr int N = G == 4 ? 2 : 1;
+            if (G < 16 || (g & 1) == 0) {
+#pragma unroll
+                for (int n = 0; n < N; ++n) {
+                    const int e = v0 + n;
+                    const int64_t f = val_slot<V>(w * kWin + b * kE + e);
+                    const bool held = reinterpret_cast<const uint32_t*>(&cols[wave][b][0])[e] != kNone;
+                    val[f] = held ? (V)((double)A[f] - pred[n]) : V(0);  // padding keeps value 0
+                }
+            }
+        }
     }
 }
 
@@ -315,7 +456,8 @@ template <class S, class V>
 __global__ void k_copy_mapped(const S* __restrict__ src, const int32_t* __restrict__ smap,
                               V* __restrict__ dst, const int32_t* __restrict__ dmap,
                               int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kT)
+    const Span sp = xcd_span(n);
+    for (int64_t i = sp.lo; i < sp.hi; i += sp.step)
         dst[dmap ? dmap[i] : i] = (V)src[smap ? smap[i] : i];
 }
 
@@ -423,6 +565,7 @@ __global__ void k_test_err(const int32_t* __restrict__ row, const int32_t* __res
         const int64_t i = rnew[r];
         const int64_t j = cnew[c];
         double pred = 0.0;
+#pragma unroll 8
         for (int32_t t = 0; t < k; ++t)
             pred = __builtin_fma((double)W[(int64_t)t * m + i], (double)H[(int64_t)t * n + j], pred);
         const double err = (double)a - pred;
@@ -433,6 +576,42 @@ __global__ void k_test_err(const int32_t* __restrict__ row, const int32_t* __res
         __syncthreads();  // block_total's LDS is reused
         block_total(bad, &rejected[blockIdx.x]);
     }
+}
+
+// k_test_err with one or both factors as a row-major copy over relabelled ids (rows of
+// `pitch` values, a multiple of 4, zero past k): four features per gather instead of one,
+// and a row's gathers in the same lines.  WR, HR: which are row-major; the other one is
+// column-major.  The same sums in the same order.
+template <class V, bool WR, bool HR>
+__global__ void k_test_err_rows(const int32_t* __restrict__ row, const int32_t* __restrict__ col,
+                                const float* __restrict__ val, int64_t nnz,
+                                const int32_t* __restrict__ rnew, const int32_t* __restrict__ cnew,
+                                const V* __restrict__ W, const V* __restrict__ H, int64_t m, int64_t n,
+                                int32_t k, int32_t pitch, double* __restrict__ part) {
+    double acc = 0.0;
+    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnz;
+         e += (int64_t)gridDim.x * kT) {
+        const int64_t i = rnew[row[e]], j = cnew[col[e]];
+        auto four = [&](auto rows, const V* F, int64_t r, int64_t len, int32_t t) {
+            Row4<V> x;
+            if constexpr (decltype(rows)::value) {
+                x = load4(F + r * pitch + t);
+            } else {
+                for (int u = 0; u < 4; ++u) x.v[u] = t + u < k ? F[(int64_t)(t + u) * len + r] : V(0);
+            }
+            return x;
+        };
+        double pred = 0.0;
+#pragma unroll 4
+        for (int32_t t = 0; t < pitch; t += 4) {
+            const Row4<V> w = four(std::bool_constant<WR>{}, W, i, m, t);
+            const Row4<V> h = four(std::bool_constant<HR>{}, H, j, n, t);
+            for (int u = 0; u < 4; ++u) pred = __builtin_fma((double)w.v[u], (double)h.v[u], pred);
+        }
+        const double err = (double)val[e] - pred;
+        acc = __builtin_fma(err, err, acc);
+    }
+    block_total(acc, &part[blockIdx.x]);
 }
 
 }  // namespace
@@ -536,7 +715,7 @@ hipError_t launch_slot_map(const int32_t* from, const int32_t* to, int64_t n, in
 template <class V>
 hipError_t launch_copy_slots(const V* src, const int32_t* map, V* dst, int64_t n, hipStream_t s) {
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_copy_slots<V>), grid_for(n), dim3(kT), 0, s, src, map, dst, n);
+    hipLaunchKernelGGL((k_copy_slots<V>), xcd_grid(n), dim3(kT), 0, s, src, map, dst, n);
     return hipGetLastError();
 }
 
@@ -550,16 +729,16 @@ hipError_t launch_fill(V* dst, V value, int64_t n, hipStream_t s) {
 template <class S, class V>
 hipError_t launch_scatter_factor_in(const S* rowmajor, const int32_t* new2old, int64_t rows,
                                     int32_t k, V* colmajor, hipStream_t s) {
-    hipLaunchKernelGGL((k_factor_in<S, V>), grid_for(rows * k), dim3(kT), 0, s, rowmajor, new2old,
-                       rows, k, colmajor);
+    hipLaunchKernelGGL((k_factor_in<S, V>), dim3((unsigned)((rows + kFR - 1) / kFR)), dim3(kT), 0, s,
+                       rowmajor, new2old, rows, k, colmajor);
     return hipGetLastError();
 }
 
 template <class V, class S>
-hipError_t launch_gather_factor_out(const V* colmajor, const int32_t* old2new, int64_t rows,
-                                    int32_t k, S* rowmajor, hipStream_t s) {
-    hipLaunchKernelGGL((k_factor_out<V, S>), grid_for(rows * k), dim3(kT), 0, s, colmajor, old2new,
-                       rows, k, rowmajor);
+hipError_t launch_factor_out(const V* colmajor, const int32_t* new2old, int64_t rows, int32_t k,
+                             int32_t pitch, S* rowmajor, hipStream_t s) {
+    hipLaunchKernelGGL((k_factor_out<V, S>), dim3((unsigned)((rows + kFR - 1) / kFR)), dim3(kT), 0, s,
+                       colmajor, new2old, rows, k, pitch, rowmajor);
     return hipGetLastError();
 }
 
@@ -572,20 +751,33 @@ hipError_t launch_delta_windows(void* idx, int64_t npad, int32_t pad, uint64_t* 
     return hipGetLastError();
 }
 
+template <class I, class V>
+static void rebuild_groups(const Layout& L, const V* A, const V* W, const V* HT, int64_t m, int32_t k,
+                           int32_t pitch, hipStream_t s) {
+    // Lanes per row of HT: as many as its values fill, four each.
+    const dim3 grid = grid_for(L.npad / kWin * 64, 1 << 14);
+#define CCDK_REBUILD(G)                                                                            \
+    hipLaunchKernelGGL((k_rebuild<I, V, G>), grid, dim3(kT), 0, s, L.seg_start, L.nseg, L.seg_row,   \
+                       L.tile_seg, L.P, L.T, L.swz_lim, static_cast<const I*>(L.idx),                \
+                       sizeof(I) == 2 ? L.dmask : nullptr, (uint32_t)L.pad, A, W, HT, m, k, pitch,   \
+                       L.npad, static_cast<V*>(L.val))
+    if (pitch <= 16)
+        CCDK_REBUILD(4);
+    else if (pitch <= 32)
+        CCDK_REBUILD(8);
+    else
+        CCDK_REBUILD(16);
+#undef CCDK_REBUILD
+}
+
 template <class V>
-hipError_t launch_rebuild_residual(const Layout& L, const int32_t* pos, const V* A, const V* W,
-                                   const V* H, int64_t m, int64_t n, int32_t k, hipStream_t s) {
+hipError_t launch_rebuild_residual(const Layout& L, const V* A, const V* W, const V* HT, int64_t m,
+                                   int32_t k, int32_t pitch, hipStream_t s) {
     if (L.nnz == 0) return hipSuccess;
     if (L.idx16)
-        hipLaunchKernelGGL((k_rebuild<uint16_t, V>), grid_for(L.nnz), dim3(kT), 0, s, L.seg_start,
-                           L.nseg, L.seg_row, L.tile_seg, L.P, L.T, L.swz_lim,
-                           static_cast<const uint16_t*>(L.idx), L.dmask, (uint32_t)L.pad, pos, A, W,
-                           H, m, n, k, L.nnz, static_cast<V*>(L.val));
+        rebuild_groups<uint16_t, V>(L, A, W, HT, m, k, pitch, s);
     else
-        hipLaunchKernelGGL((k_rebuild<int32_t, V>), grid_for(L.nnz), dim3(kT), 0, s, L.seg_start,
-                           L.nseg, L.seg_row, L.tile_seg, L.P, L.T, L.swz_lim,
-                           static_cast<const int32_t*>(L.idx), nullptr, (uint32_t)L.pad, pos, A, W,
-                           H, m, n, k, L.nnz, static_cast<V*>(L.val));
+        rebuild_groups<int32_t, V>(L, A, W, HT, m, k, pitch, s);
     return hipGetLastError();
 }
 
@@ -593,7 +785,7 @@ template <class S, class V>
 hipError_t launch_copy_mapped(const S* src, const int32_t* smap, V* dst, const int32_t* dmap,
                               int64_t n, hipStream_t s) {
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL((k_copy_mapped<S, V>), grid_for(n), dim3(kT), 0, s, src, smap, dst, dmap, n);
+    hipLaunchKernelGGL((k_copy_mapped<S, V>), xcd_grid(n), dim3(kT), 0, s, src, smap, dst, dmap, n);
     return hipGetLastError();
 }
 
@@ -642,6 +834,24 @@ hipError_t launch_test_err(const int32_t* row, const int32_t* col, const float* 
     return hipGetLastError();
 }
 
+template <class V>
+hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
+                                const int32_t* rold2new, const int32_t* cold2new, const V* W,
+                                const V* H, const V* WT, const V* HT, int64_t m, int64_t n, int32_t k,
+                                int32_t pitch, double* part, int32_t nparts, hipStream_t s) {
+    const dim3 grid((unsigned)nparts);
+    if (WT && HT)
+        hipLaunchKernelGGL((k_test_err_rows<V, true, true>), grid, dim3(kT), 0, s, row, col, val, nnz,
+                           rold2new, cold2new, WT, HT, m, n, k, pitch, part);
+    else if (HT)
+        hipLaunchKernelGGL((k_test_err_rows<V, false, true>), grid, dim3(kT), 0, s, row, col, val, nnz,
+                           rold2new, cold2new, W, HT, m, n, k, pitch, part);
+    else
+        hipLaunchKernelGGL((k_test_err_rows<V, true, false>), grid, dim3(kT), 0, s, row, col, val, nnz,
+                           rold2new, cold2new, WT, H, m, n, k, pitch, part);
+    return hipGetLastError();
+}
+
 #define CCDK_BUILD_INSTANTIATE(V)                                                               \
     template hipError_t launch_layout_fill<V>(const uint64_t*, const int32_t*, const float*,    \
                                               int64_t, int, const int32_t*, uint32_t, bool, void*, \
@@ -652,13 +862,17 @@ hipError_t launch_test_err(const int32_t* row, const int32_t* col, const float* 
                                                            int64_t, int32_t, V*, hipStream_t);  \
     template hipError_t launch_scatter_factor_in<double, V>(const double*, const int32_t*,      \
                                                             int64_t, int32_t, V*, hipStream_t); \
-    template hipError_t launch_gather_factor_out<V, float>(const V*, const int32_t*, int64_t,   \
-                                                           int32_t, float*, hipStream_t);       \
-    template hipError_t launch_gather_factor_out<V, double>(const V*, const int32_t*, int64_t,  \
-                                                            int32_t, double*, hipStream_t);     \
-    template hipError_t launch_rebuild_residual<V>(const Layout&, const int32_t*, const V*,     \
-                                                   const V*, const V*, int64_t, int64_t,        \
-                                                   int32_t, hipStream_t);                       \
+    template hipError_t launch_factor_out<V, float>(const V*, const int32_t*, int64_t, int32_t, \
+                                                    int32_t, float*, hipStream_t);              \
+    template hipError_t launch_factor_out<V, double>(const V*, const int32_t*, int64_t, int32_t, \
+                                                     int32_t, double*, hipStream_t);            \
+    template hipError_t launch_rebuild_residual<V>(const Layout&, const V*, const V*, const V*, \
+                                                   int64_t, int32_t, int32_t, hipStream_t);     \
+    template hipError_t launch_test_err_rows<V>(const int32_t*, const int32_t*, const float*,   \
+                                                int64_t, const int32_t*, const int32_t*,        \
+                                                const V*, const V*, const V*, const V*,         \
+                                                int64_t, int64_t, int32_t, int32_t, double*,    \
+                                                int32_t, hipStream_t);                          \
     template hipError_t launch_copy_mapped<V, V>(const V*, const int32_t*, V*, const int32_t*,  \
                                                  int64_t, hipStream_t);                         \
     template hipError_t launch_consistency<V>(const V*, const int32_t*, const V*,               \

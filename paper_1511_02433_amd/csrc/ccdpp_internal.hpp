@@ -404,12 +404,17 @@ hipError_t launch_fill(V* dst, V value, int64_t n, hipStream_t s);
 template <class S, class V>
 hipError_t launch_scatter_factor_in(const S* rowmajor, const int32_t* new2old, int64_t rows,
                                     int32_t k, V* colmajor, hipStream_t s);
+// rowmajor[new2old[i] * pitch + t] = colmajor[t * rows + i] for t < k, zero for k <= t <
+// pitch (new2old null: row i)
 template <class V, class S>
-hipError_t launch_gather_factor_out(const V* colmajor, const int32_t* old2new, int64_t rows,
-                                    int32_t k, S* rowmajor, hipStream_t s);
+hipError_t launch_factor_out(const V* colmajor, const int32_t* new2old, int64_t rows, int32_t k,
+                             int32_t pitch, S* rowmajor, hipStream_t s);
+// The residual of the user-major copy from the ratings A (in its value slots), W
+// (column-major) and HT (H row-major, rows of `pitch` values, a multiple of 4).
 template <class V>
-hipError_t launch_rebuild_residual(const Layout& L, const int32_t* pos, const V* A, const V* W,
-                                   const V* H, int64_t m, int64_t n, int32_t k, hipStream_t s);
+hipError_t launch_rebuild_residual(const Layout& L, const V* A, const V* W, const V* HT, int64_t m,
+                                   int32_t k, int32_t pitch, hipStream_t s);
+inline int32_t row_pitch(int32_t k) { return (k + 3) / 4 * 4; }
 // dst[dmap ? dmap[i] : i] = src[smap ? smap[i] : i] for i < n (converting between types)
 template <class S, class V>
 hipError_t launch_copy_mapped(const S* src, const int32_t* smap, V* dst, const int32_t* dmap,
@@ -435,6 +440,14 @@ hipError_t launch_test_err(const int32_t* row, const int32_t* col, const float* 
                            const int32_t* rold2new, const int32_t* cold2new, const V* W,
                            const V* H, int64_t m, int64_t n, int32_t k, double* part,
                            int32_t nparts, double* rejected, hipStream_t s);
+// The same with a row-major copy of one or both factors over relabelled ids (WT, HT: rows
+// of `pitch` values, a multiple of 4, zero past k; null: the column-major W or H
+// serves); triplets checked by the caller.
+template <class V>
+hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
+                                const int32_t* rold2new, const int32_t* cold2new, const V* W,
+                                const V* H, const V* WT, const V* HT, int64_t m, int64_t n, int32_t k,
+                                int32_t pitch, double* part, int32_t nparts, hipStream_t s);
 // Device-wide primitives (rocPRIM); tmp is a temporary buffer grown as needed and
 // freed by the caller.  sort_pairs: stable radix sort of (key, value) pairs on the
 // low `bits` bits of the keys.  select_range: out[0 .. *count) = the indices e < n
