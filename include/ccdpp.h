@@ -118,7 +118,9 @@ int ccdpp_create(int64_t m, int64_t n, int32_t k, double lambda, int64_t nnz,
  *                 copy staged in LDS (gather_mode 2) with precision 0, else
  *                 create fails with EINVAL.  Automatic: 3 on both copies
  *                 when their residual streams (values and indices) total at
- *                 most 160 MB, so that they stay in the memory-side cache;
+ *                 most 288 MiB, so that the memory-side cache holds them (hot
+ *                 and precision 1 copies then use cached accesses too, but
+ *                 report 1);
  *                 otherwise 2 on one copy and 1 on the other: the item-major
  *                 copy takes the 2 when it is staged in LDS and not split,
  *                 else a user-major copy staged with one tile does (neither

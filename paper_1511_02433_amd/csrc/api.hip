@@ -45,10 +45,12 @@ bool injected(std::atomic<int64_t>& c) {
 // Gathers address records of up to 16 bytes per column with 32-bit byte offsets.
 constexpr int64_t kMaxDim = int64_t(1) << 28;
 constexpr int64_t kMaxNnz = INT32_MAX;
-// Residual streams (values and indices of both copies) up to this size stay in
-// MI355X's 256 MB memory-side cache from one pass to the next when the passes
-// use cached accesses.
-constexpr int64_t kCachedStreamBytes = int64_t(160) << 20;
+// Residual streams (values and indices of both copies) up to this size gain from cached
+// accesses: MI355X's 256 MB memory-side cache then holds them, or most of them, from one
+// pass to the next.  Per pass, streaming against cached: float 170 MB 28.6 against 25.2 us,
+// 240 MB 32.1 against 29.9, 295 MB 36.5 against 34.9; double 206 MB 35.2 against 30.0,
+// 245 MB 37.2 against 33.2, 330 MB 46.2 against 47.5.
+constexpr int64_t kCachedStreamBytes = int64_t(288) << 20;
 constexpr int32_t kReduceParts = 1024;
 // A row segment of a tiled layout costs about as much as this many gathers from
 // global memory (its emission, partial and combine against one cache line each).
@@ -856,7 +858,8 @@ int code_windows(ccdpp* h, int part, const ccdpp_options_t* opt) {
     using namespace ccdk;
     Layout& L = h->L[part];
     const int forced = opt ? opt->index_coding[part == 0 ? 0 : 1] : 0;
-    if (forced == 1 || L.gather != kGatherLds || !L.idx16 || L.npad == 0 || L.cache == kCacheAll)
+    if (forced == 1 || L.gather != kGatherLds || !L.idx16 || L.npad == 0 || L.cache == kCacheAll ||
+        L.near)
         return CCDPP_OK;
     const hipStream_t s = h->stream;
     const int64_t words = (L.npad / kWin + 63) / 64;
@@ -887,11 +890,11 @@ int spread_factors(ccdpp* h) {
     });
 }
 
-// The cache policy of each copy's residual stream (float, tiled copies; the
-// others always stream).  Measured on MI355X:
+// The cache policy of each copy's residual stream.  Measured on MI355X:
 // - when both streams fit in the memory-side cache (10M ratings: 123 MB), cached
 //   loads and stores keep them there between passes: 7% less time per outer
-//   iteration than streaming;
+//   iteration than streaming (kCachedStreamBytes); so too for hot copies (6M ratings
+//   over 300,007 x 150,001: 33.3 -> 27.8 us per pass) and for double ones;
 // - when they do not (100M ratings: 1.23 GB), cached accesses are 13% slower, but
 //   write-back R-hat stores on one copy make its first pass of each feature about
 //   13% faster for a slower next pass over that copy (1.7% less time per outer
@@ -925,7 +928,8 @@ int choose_cache(ccdpp* h, const ccdpp_options_t* opt) {
         if (forced > 0) {
             L.cache = forced - 1;
         } else if (!eligible(part)) {
-            L.cache = kCacheStream;
+            L.cache = kCacheStream;  // (reported so, also where near)
+            L.near = forced == 0 && stream <= kCachedStreamBytes && L.gather != kGatherGlobal;
         } else if (stream <= kCachedStreamBytes) {
             L.cache = kCacheAll;
         } else {

@@ -288,6 +288,8 @@ struct Layout {
                                      // them (tiled), the hot width (hot), none (global)
     bool idx16 = false;
     int32_t cache = kCacheStream;    // CachePolicy of the passes over this copy
+    bool near = false;               // hot and double copies: cached accesses, as kCacheAll, the
+                                     // copies' streams fitting the memory-side cache
     uint64_t* dmask = nullptr;       // [ceil(npad / kWin / 64)] delta-coded windows, or null
     int64_t ndelta = 0;              // windows coded so
     void* idx = nullptr;             // [npad + kEntryPad]

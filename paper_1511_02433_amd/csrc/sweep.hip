@@ -1008,12 +1008,16 @@ void launch_mode(PassMode mode, dim3 grid, size_t lds, hipStream_t s, const Pass
     }
 }
 
-// Tiled float copies also come with the write-back policies.
+// Tiled float copies also come with the write-back policies, double ones with cached
+// accesses (near).
 template <bool P1, class V>
-void launch_tiled(int cache, PassMode mode, dim3 grid, size_t lds, hipStream_t s, const PassArgs<V>& a) {
+void launch_tiled(int cache, bool near, PassMode mode, dim3 grid, size_t lds, hipStream_t s, const PassArgs<V>& a) {
     if constexpr (sizeof(V) == 4) {
         if (cache == kCacheStores) return launch_mode<true, true, P1, kCacheStores, V>(mode, grid, lds, s, a);
         if (cache == kCacheAll) return launch_mode<true, true, P1, kCacheAll, V>(mode, grid, lds, s, a);
+    }
+    if constexpr (sizeof(V) == 8) {
+        if (near) return launch_mode<true, true, P1, kCacheAll, V>(mode, grid, lds, s, a);
     }
     launch_mode<true, true, P1, kCacheStream, V>(mode, grid, lds, s, a);
 }
@@ -1023,14 +1027,15 @@ hipError_t raise_lds_all() {
     hipError_t e = raise_lds<true, true, true, kCacheStream, V>();
     if (e == hipSuccess) e = raise_lds<true, true, false, kCacheStream, V>();
     if (e == hipSuccess) e = raise_lds<true, false, true, kCacheStream, V>();
+    if (e == hipSuccess) e = raise_lds<true, false, true, kCacheAll, V>();
     if (e == hipSuccess) e = raise_lds<false, true, true, kCacheStream, V>();
     if (e == hipSuccess) e = raise_lds<false, false, true, kCacheStream, V>();
     if constexpr (sizeof(V) == 4) {
         if (e == hipSuccess) e = raise_lds<true, true, true, kCacheStores, V>();
         if (e == hipSuccess) e = raise_lds<true, true, false, kCacheStores, V>();
-        if (e == hipSuccess) e = raise_lds<true, true, true, kCacheAll, V>();
-        if (e == hipSuccess) e = raise_lds<true, true, false, kCacheAll, V>();
     }
+    if (e == hipSuccess) e = raise_lds<true, true, true, kCacheAll, V>();
+    if (e == hipSuccess) e = raise_lds<true, true, false, kCacheAll, V>();
     return e;
 }
 }  // namespace
@@ -1053,7 +1058,7 @@ hipError_t launch_pass(const Layout& L, PassMode mode, const V* x, const V* p, c
     if (staged ? !L.idx16 : L.P != 1) return hipErrorInvalidValue;
     if (hot && L.idx16) return hipErrorInvalidValue;
     // Write-back cache policies: tiled float copies only.  Cached copies have plain indices.
-    if (L.cache == kCacheAll && L.dmask) return hipErrorInvalidValue;
+    if ((L.cache == kCacheAll || L.near) && L.dmask) return hipErrorInvalidValue;
     if (L.cache != kCacheStream && (!staged || sizeof(V) != 4)) return hipErrorInvalidValue;
     PassArgs<V> a{};
     a.idx = L.idx;
@@ -1112,11 +1117,14 @@ hipError_t launch_pass(const Layout& L, PassMode mode, const V* x, const V* p, c
     const dim3 grid(L.grid);
     if (staged) {
         if (L.P == 1)
-            launch_tiled<true, V>(L.cache, mode, grid, lds, s, a);
+            launch_tiled<true, V>(L.cache, L.near, mode, grid, lds, s, a);
         else
-            launch_tiled<false, V>(L.cache, mode, grid, lds, s, a);
+            launch_tiled<false, V>(L.cache, L.near, mode, grid, lds, s, a);
     } else if (hot) {
-        launch_mode<true, false, true, kCacheStream, V>(mode, grid, lds, s, a);
+        if (L.near)
+            launch_mode<true, false, true, kCacheAll, V>(mode, grid, lds, s, a);
+        else
+            launch_mode<true, false, true, kCacheStream, V>(mode, grid, lds, s, a);
     } else if (L.idx16) {
         launch_mode<false, true, true, kCacheStream, V>(mode, grid, lds, s, a);
     } else {

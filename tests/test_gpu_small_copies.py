@@ -11,7 +11,7 @@ import pytest
 
 from oracle import Oracle
 from paper_1511_02433_amd import synth
-from paper_1511_02433_amd.ccdpp import CCDPP
+from paper_1511_02433_amd.ccdpp import CCDPP, make_options
 from gpu_util import colscaled_max_rel_err
 
 pytestmark = pytest.mark.gpu
@@ -52,3 +52,28 @@ def test_small_copy(name):
     assert g.check_consistency() == 0
     g.close()
     o.close()
+
+
+@pytest.mark.parametrize("kind", ["double_one_tile", "double_tiles", "double_hot", "float_hot"])
+def test_cached_accesses_change_nothing(kind):
+    # Hot and double copies whose streams fit the memory-side cache use cached accesses
+    # and plain indices; a forced streaming policy gives the same bits.
+    lens = [850, 700, 300, 40] + list(np.random.default_rng(31).integers(0, 80, 1496))
+    m, n, k = len(lens), 900, 4
+    row, col, val, H0 = synth.lengths_problem(lens, n, k, seed=32)
+    kw = {"double_one_tile": dict(precision=1), "double_tiles": dict(precision=1, gather_mode=(2, 2), tile_width=(192, 128)),
+          "double_hot": dict(precision=1, gather_mode=(3, 3), tile_width=(64, 96)),
+          "float_hot": dict(gather_mode=(3, 3), tile_width=(64, 96))}[kind]
+    print(f"case: cached accesses, {kind}", flush=True)
+    outs = []
+    for cache in ((0, 0), (1, 1)):
+        g = CCDPP(m, n, k, 0.1, row, col, val, opts=make_options(cache=cache, **kw))
+        g.set_factors(None, H0)
+        g.run(2, 2)
+        g.run(1, 1)
+        g.ccd_run(1)
+        outs.append(g.factors_f64() + (g.residual_f64(), g.train_rmse()))
+        assert g.check_consistency() == 0
+        g.close()
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
