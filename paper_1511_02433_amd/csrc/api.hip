@@ -21,7 +21,6 @@
 #include "ccdpp_internal.hpp"
 
 using ccdk::Layout;
-using ccdk::Stager;
 
 namespace {
 
@@ -52,6 +51,10 @@ constexpr int64_t kMaxNnz = INT32_MAX;
 // 245 MB 37.2 against 33.2, 330 MB 46.2 against 47.5.
 constexpr int64_t kCachedStreamBytes = int64_t(288) << 20;
 constexpr int32_t kReduceParts = 1024;
+// Arguments of up to this many elements are checked on the host (about 15 us), longer
+// ones on the device once they are there (30 us with the wait, 1.4M triplets or 20M
+// factors included, which took a host thread 1 and 6 ms).
+constexpr int64_t kHostCheck = 24576;
 // A row segment of a tiled layout costs about as much as this many gathers from
 // global memory (its emission, partial and combine against one cache line each).
 constexpr int64_t kSplitSegCost = 2;
@@ -65,14 +68,8 @@ struct ProfEvent {
 
 }  // namespace
 
-// Every device allocation of the library goes through here.
-hipError_t ccdk::dev_malloc(void** p, size_t bytes) {
-    if (injected(g_inject_alloc)) {
-        *p = nullptr;
-        return hipErrorOutOfMemory;
-    }
-    return hipMalloc(p, bytes);
-}
+// Every device allocation of the library asks here first.
+bool ccdk::alloc_injected() { return injected(g_inject_alloc); }
 
 // ---- scratch of the allocation-free entry point (ccdpp_rmse_noalloc) --------------
 // kReduceParts partial sums of squared errors, as many per-block counts of rejected
@@ -142,8 +139,11 @@ struct ccdpp {
     // scratch; factors; the device set-up before the inputs (device checks, kernel
     // attributes, scratch address).
     int64_t build_phase_us[7] = {};
-    int64_t bytes_held = 0;
-    std::vector<std::pair<void*, int64_t>> allocs;  // device allocations and their sizes
+    // Device memory: what the handle keeps, and temporaries of the running call, of which
+    // at most temp_keep bytes stay for the next one.
+    ccdk::DevicePool kept, temp;
+    size_t temp_keep = 0;
+    ccdk::Stager stage;
     // kernel timing
     bool prof = false;
     int32_t prof_kind = -1, prof_layout = -1;  // restrict timing to one kind / copy (-1: all)
@@ -201,14 +201,10 @@ V* as(void* p) {
 
 template <class T>
 hipError_t dalloc(ccdpp* h, T** p, int64_t count) {
-    size_t bytes = (size_t)std::max<int64_t>(count, 1) * sizeof(T);
     void* q = nullptr;
-    hipError_t e = ccdk::dev_malloc(&q, bytes);
-    if (e != hipSuccess) return e;
-    h->allocs.emplace_back(q, (int64_t)bytes);
-    h->bytes_held += (int64_t)bytes;
-    *p = static_cast<T*>(q);
-    return hipSuccess;
+    hipError_t e = h->kept.take(&q, (size_t)std::max<int64_t>(count, 1) * sizeof(T));
+    if (e == hipSuccess) *p = static_cast<T*>(q);
+    return e;
 }
 
 template <class T>
@@ -219,34 +215,37 @@ int upload(ccdpp* h, T** dst, const std::vector<T>& src) {
     return CCDPP_OK;
 }
 
-// Frees one of the handle's device allocations before the handle goes.
-void dfree(ccdpp* h, void* p) {
-    for (size_t i = 0; i < h->allocs.size(); ++i)
-        if (h->allocs[i].first == p) {
-            h->bytes_held -= h->allocs[i].second;
-            h->allocs.erase(h->allocs.begin() + (std::ptrdiff_t)i);
-            (void)hipFree(p);
-            return;
-        }
-}
-
 // Value slots of the item-major copy: both parts when it is split.
 int64_t item_slots(const ccdpp* h) {
     return h->split > 0 ? h->off2 + h->L[2].npad : h->L[1].npad;
 }
 
-// Temporary device buffer freed when it goes out of scope.
+// Temporary device buffer, back in the handle's pool when it goes out of scope.
 struct Tmp {
+    ccdk::DevicePool* pool = nullptr;
     void* p = nullptr;
+    Tmp() = default;
+    Tmp(const Tmp&) = delete;
+    Tmp& operator=(const Tmp&) = delete;
     ~Tmp() {
-        if (p) (void)hipFree(p);
+        if (p) pool->give(p);
     }
 };
 template <class T>
-hipError_t talloc(Tmp& t, T** p, int64_t count) {
-    hipError_t e = ccdk::dev_malloc(&t.p, (size_t)std::max<int64_t>(count, 1) * sizeof(T));
+hipError_t talloc(ccdpp* h, Tmp& t, T** p, int64_t count) {
+    t.pool = &h->temp;
+    hipError_t e = h->temp.take(&t.p, (size_t)std::max<int64_t>(count, 1) * sizeof(T));
     *p = static_cast<T*>(t.p);
     return e;
+}
+// Temporary memory of a device-wide primitive.
+ccdk::TakeFn take_into(ccdpp* h, Tmp& t) {
+    return [h, &t](void** p, size_t bytes) {
+        char* q = nullptr;
+        hipError_t e = talloc(h, t, &q, (int64_t)bytes);
+        *p = q;
+        return e;
+    };
 }
 
 bool usable(const ccdpp* h) { return h && !h->poisoned; }
@@ -369,7 +368,7 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
         } else {
             int32_t* d_cnt;
             Tmp tc;
-            HIPCK(h, talloc(tc, &d_cnt, P * rows));
+            HIPCK(h, talloc(h, tc, &d_cnt, P * rows));
             HIPCK(h, hipMemsetAsync(d_cnt, 0, (size_t)(P * rows) * 4, s));
             HIPCK(h, launch_seg_histogram(lrow, lcol, N, (int32_t)rows, (int32_t)T, d_cnt, s));
             cnt.assign((size_t)(P * rows), 0);
@@ -813,24 +812,20 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
         uint64_t *k0, *k1;
         int32_t* i0;
         Tmp tsid, toff, tk0, tk1, ti0, ttmp;
-        HIPCK(h, talloc(tsid, &d_segid, P * rows));
+        HIPCK(h, talloc(h, tsid, &d_segid, P * rows));
         HIPCK(h, hipMemcpyAsync(d_segid, segid.data(), segid.size() * 4, hipMemcpyHostToDevice, s));
-        HIPCK(h, talloc(toff, &d_off, S));
+        HIPCK(h, talloc(h, toff, &d_off, S));
         HIPCK(h, hipMemcpyAsync(d_off, seg_off.data(), seg_off.size() * 4, hipMemcpyHostToDevice, s));
-        HIPCK(h, talloc(tk0, &k0, N));
-        HIPCK(h, talloc(tk1, &k1, N));
-        HIPCK(h, talloc(ti0, &i0, N));
+        HIPCK(h, talloc(h, tk0, &k0, N));
+        HIPCK(h, talloc(h, tk1, &k1, N));
+        HIPCK(h, talloc(h, ti0, &i0, N));
         HIPCK(h, launch_seg_keys(lrow, lcol, d_segid, N, (int32_t)rows, (int32_t)T, cbits, k0, i0,
                                  s));
-        void* tmp = nullptr;
-        size_t tmp_bytes = 0;
-        hipError_t e = sort_pairs(k0, k1, i0, perm, N, cbits + sbits, s, &tmp, &tmp_bytes);
-        ttmp.p = tmp;
-        HIPCK(h, e);
+        HIPCK(h, sort_pairs(k0, k1, i0, perm, N, cbits + sbits, s, take_into(h, ttmp)));
         if (side == 0) {
             int32_t* d_flag;
             Tmp tflag;
-            HIPCK(h, talloc(tflag, &d_flag, 1));
+            HIPCK(h, talloc(h, tflag, &d_flag, 1));
             HIPCK(h, hipMemsetAsync(d_flag, 0, 4, s));
             HIPCK(h, launch_dup_check(k1, N, d_flag, s));
             int32_t flag = 0;
@@ -961,13 +956,12 @@ int build_item_major(ccdpp* h, const int32_t* lrow, const int32_t* lcol, const f
     // The entries of the leading H items and of the others, each in input order.
     int32_t *ih, *il;
     int64_t* d_cnt;
-    Tmp tih, til, tcnt, ttmp;
-    size_t tmp_bytes = 0;
-    HIPCK(h, talloc(tih, &ih, N));
-    HIPCK(h, talloc(til, &il, N));
-    HIPCK(h, talloc(tcnt, &d_cnt, 2));
-    HIPCK(h, select_range(lrow, N, 0, (int32_t)H, ih, d_cnt, s, &ttmp.p, &tmp_bytes));
-    HIPCK(h, select_range(lrow, N, (int32_t)H, (int32_t)n, il, d_cnt + 1, s, &ttmp.p, &tmp_bytes));
+    Tmp tih, til, tcnt, ttmp, ttmp2;
+    HIPCK(h, talloc(h, tih, &ih, N));
+    HIPCK(h, talloc(h, til, &il, N));
+    HIPCK(h, talloc(h, tcnt, &d_cnt, 2));
+    HIPCK(h, select_range(lrow, N, 0, (int32_t)H, ih, d_cnt, s, take_into(h, ttmp)));
+    HIPCK(h, select_range(lrow, N, (int32_t)H, (int32_t)n, il, d_cnt + 1, s, take_into(h, ttmp2)));
     int64_t cnt[2] = {0, 0};
     HIPCK(h, hipMemcpyAsync(cnt, d_cnt, sizeof cnt, hipMemcpyDeviceToHost, s));
     HIPCK(h, hipStreamSynchronize(s));
@@ -983,16 +977,16 @@ int build_item_major(ccdpp* h, const int32_t* lrow, const int32_t* lcol, const f
     int32_t *rh, *ch, *rl, *cl, *ph, *qh, *pl, *ql;
     float *vh, *vl;
     Tmp trh, tch, tvh, trl, tcl, tvl, tph, tqh, tpl, tql;
-    HIPCK(h, talloc(trh, &rh, nh));
-    HIPCK(h, talloc(tch, &ch, nh));
-    HIPCK(h, talloc(tvh, &vh, nh));
-    HIPCK(h, talloc(trl, &rl, nl));
-    HIPCK(h, talloc(tcl, &cl, nl));
-    HIPCK(h, talloc(tvl, &vl, nl));
-    HIPCK(h, talloc(tph, &ph, nh));
-    HIPCK(h, talloc(tqh, &qh, nh));
-    HIPCK(h, talloc(tpl, &pl, nl));
-    HIPCK(h, talloc(tql, &ql, nl));
+    HIPCK(h, talloc(h, trh, &rh, nh));
+    HIPCK(h, talloc(h, tch, &ch, nh));
+    HIPCK(h, talloc(h, tvh, &vh, nh));
+    HIPCK(h, talloc(h, trl, &rl, nl));
+    HIPCK(h, talloc(h, tcl, &cl, nl));
+    HIPCK(h, talloc(h, tvl, &vl, nl));
+    HIPCK(h, talloc(h, tph, &ph, nh));
+    HIPCK(h, talloc(h, tqh, &qh, nh));
+    HIPCK(h, talloc(h, tpl, &pl, nl));
+    HIPCK(h, talloc(h, tql, &ql, nl));
     HIPCK(h, launch_map(ih, lrow, nh, rh, s));
     HIPCK(h, launch_map(ih, lcol, nh, ch, s));
     HIPCK(h, (launch_copy_mapped<float, float>(val, ih, vh, nullptr, nh, s)));
@@ -1023,8 +1017,8 @@ int build_item_major(ccdpp* h, const int32_t* lrow, const int32_t* lcol, const f
     HIPCK(h, hipMemcpyAsync(static_cast<char*>(both) + off2 * vb, h->L[2].val,
                             (size_t)(h->L[2].npad + kEntryPad) * vb, hipMemcpyDeviceToDevice, s));
     HIPCK(h, hipStreamSynchronize(s));
-    dfree(h, h->L[1].val);
-    dfree(h, h->L[2].val);
+    h->kept.give(h->L[1].val);
+    h->kept.give(h->L[2].val);
     h->L[1].val = both;
     h->L[2].val = static_cast<char*>(both) + off2 * vb;
     h->split = H;
@@ -1071,19 +1065,27 @@ int create_device(ccdpp* h, const int32_t* row, const int32_t* col, const float*
     hipStream_t s = h->stream;
     phase(6);
 
+    // Device memory: per entry, the handle keeps two copies (values, and indices of 2 or 4
+    // bytes), the ratings and three maps, and the build needs about 60 bytes more; per
+    // row, the factors and the segment lists.  What goes past that comes in smaller pieces.
+    {
+        const size_t vb = h->dbl ? 8 : 4, mn = (size_t)(m + n);
+        h->kept.expect((size_t)N * (17 + 3 * vb) + (size_t)N / 16 * vb + mn * (32 + (h->k + 1) * vb));
+        h->temp.expect((size_t)N * 60 + mn * 16);
+        h->temp_keep = std::max<size_t>(size_t(16) << 20, mn * h->k * (vb + 8));
+    }
     // Inputs and degrees.
     int32_t *d_row, *d_col, *d_cnt_r, *d_cnt_c;
     float* d_val;
     Tmp t_row, t_col, t_val, t_cr, t_cc;
-    HIPCK(h, talloc(t_row, &d_row, N));
-    HIPCK(h, talloc(t_col, &d_col, N));
-    HIPCK(h, talloc(t_val, &d_val, N));
-    HIPCK(h, talloc(t_cr, &d_cnt_r, m));
-    HIPCK(h, talloc(t_cc, &d_cnt_c, n));
-    Stager stage(s);
-    HIPCK(h, stage.copy(d_row, row, (size_t)N * 4));
-    HIPCK(h, stage.copy(d_col, col, (size_t)N * 4));
-    HIPCK(h, stage.copy(d_val, val, (size_t)N * 4));
+    HIPCK(h, talloc(h, t_row, &d_row, N));
+    HIPCK(h, talloc(h, t_col, &d_col, N));
+    HIPCK(h, talloc(h, t_val, &d_val, N));
+    HIPCK(h, talloc(h, t_cr, &d_cnt_r, m));
+    HIPCK(h, talloc(h, t_cc, &d_cnt_c, n));
+    HIPCK(h, h->stage.to_device(d_row, row, (size_t)N * 4, h->device, s));
+    HIPCK(h, h->stage.to_device(d_col, col, (size_t)N * 4, h->device, s));
+    HIPCK(h, h->stage.to_device(d_val, val, (size_t)N * 4, h->device, s));
     HIPCK(h, hipMemsetAsync(d_cnt_r, 0, m * 4, s));
     HIPCK(h, hipMemsetAsync(d_cnt_c, 0, n * 4, s));
     HIPCK(h, launch_histogram(d_row, N, (int32_t)m, d_cnt_r, h->cus, s));
@@ -1108,8 +1110,8 @@ int create_device(ccdpp* h, const int32_t* row, const int32_t* col, const float*
     RCK(upload(h, &h->cold2new, co2n));
     int32_t *d_ru, *d_ci;
     Tmp t_ru, t_ci;
-    HIPCK(h, talloc(t_ru, &d_ru, N));
-    HIPCK(h, talloc(t_ci, &d_ci, N));
+    HIPCK(h, talloc(h, t_ru, &d_ru, N));
+    HIPCK(h, talloc(h, t_ci, &d_ci, N));
     HIPCK(h, launch_map(d_row, h->rold2new, N, d_ru, s));
     HIPCK(h, launch_map(d_col, h->cold2new, N, d_ci, s));
     HIPCK(h, hipStreamSynchronize(s));
@@ -1128,12 +1130,12 @@ int create_device(ccdpp* h, const int32_t* row, const int32_t* col, const float*
     {
         int32_t *perm1, *pos1, *inv1, *e01;
         Tmp tp1, tq1, tinv, te;
-        HIPCK(h, talloc(tp1, &perm1, N));
-        HIPCK(h, talloc(tq1, &pos1, N));
+        HIPCK(h, talloc(h, tp1, &perm1, N));
+        HIPCK(h, talloc(h, tq1, &pos1, N));
         RCK(build_item_major(h, d_ci, d_ru, d_val, opt, perm1, pos1, s, deg_i.data()));
-        HIPCK(h, talloc(tinv, &inv1, N));
+        HIPCK(h, talloc(h, tinv, &inv1, N));
         HIPCK(h, launch_invert(perm1, N, inv1, s));
-        HIPCK(h, talloc(te, &e01, N));
+        HIPCK(h, talloc(h, te, &e01, N));
         HIPCK(h, launch_compose(inv1, h->perm0, N, e01, s));  // item-major entry index
         HIPCK(h, dalloc(h, &h->map01, N));
         HIPCK(h, launch_compose(pos1, e01, N, h->map01, s));
@@ -1184,6 +1186,16 @@ int create_device(ccdpp* h, const int32_t* row, const int32_t* col, const float*
     }));
     h->pending = -1;
     phase(5);
+    return CCDPP_OK;
+}
+
+// Everything a handle holds on its device; the build's temporaries go back at its end.
+int create_timed(ccdpp* h, const int32_t* row, const int32_t* col, const float* val, uint64_t seed,
+                 const ccdpp_options_t* opt) {
+    const auto t0 = std::chrono::steady_clock::now();
+    RCK(create_device(h, row, col, val, seed, opt));
+    HIPCK(h, h->stage.finish());
+    h->temp.trim(0);
     h->build_us = std::chrono::duration_cast<std::chrono::microseconds>(
                       std::chrono::steady_clock::now() - t0)
                       .count();
@@ -1191,8 +1203,9 @@ int create_device(ccdpp* h, const int32_t* row, const int32_t* col, const float*
 }
 
 void destroy_all(ccdpp* h) {
-    for (auto& a : h->allocs) (void)hipFree(a.first);
-    h->allocs.clear();
+    h->stage.release();
+    h->temp.release();
+    h->kept.release();
     for (auto& pe : h->prof_pending) {
         h->event_pool.push_back(pe.a);
         h->event_pool.push_back(pe.b);
@@ -1411,7 +1424,7 @@ int create_impl(int64_t m, int64_t n, int32_t k, double lambda, int64_t nnz, con
     h->lambda = lambda;
     h->nnz = nnz;
     h->dbl = opts && opts->precision == 1;
-    int rc = create_device(h, row, col, val, seed, opts);
+    int rc = create_timed(h, row, col, val, seed, opts);
     if (rc != CCDPP_OK) {
         g_create_error = h->err;
         destroy_all(h);
@@ -1443,18 +1456,60 @@ int launch_sq_sum_any(ccdpp* h, void* p, int64_t n) {
 struct RowFactors {
     Tmp tw, th;
     char *w = nullptr, *h = nullptr;
-    void allocate(const ccdpp* p, int64_t nnz) {
+    void allocate(ccdpp* p, int64_t nnz) {
         const int64_t row = (int64_t)ccdk::row_pitch(p->k) * (p->dbl ? 8 : 4);
         auto side = [&](Tmp& t, char** c, int64_t rows) {
-            if (nnz >= 8 * rows && talloc(t, c, rows * row) != hipSuccess) (void)hipGetLastError();
+            if (nnz >= 8 * rows && talloc(p, t, c, rows * row) != hipSuccess) *c = nullptr;
         };
         side(tw, &w, p->m);
         side(th, &h, p->n);
     }
 };
+// Held-out triplets on the device.  Many of them are checked there, on the way to their
+// use: the number that may not be used goes to h->d_count, and only if there is one
+// does the host look for the first.
+int bad_triplet(ccdpp* h, int64_t nnz, const int32_t* row, const int32_t* col, const float* val) {
+    for (int64_t e = 0; e < nnz; ++e) {
+        if (row[e] < 0 || row[e] >= h->m || col[e] < 0 || col[e] >= h->n)
+            return fail(h, CCDPP_EINVAL, "test entry %lld out of range", (long long)e);
+        if (!std::isfinite(val[e]))
+            return fail(h, CCDPP_EINVAL, "test value %lld is not finite", (long long)e);
+    }
+    return CCDPP_OK;
+}
+struct Held {
+    Tmp tr, tc, tv;
+    int32_t *row = nullptr, *col = nullptr;
+    float* val = nullptr;
+    unsigned long long* bad = nullptr;  // their number, null when the host has checked them
+    int load(ccdpp* h, int64_t nnz, const int32_t* r, const int32_t* c, const float* v) {
+        const hipStream_t s = h->stream;
+        const size_t bytes = (size_t)nnz * 4;
+        if (nnz <= kHostCheck) RCK(bad_triplet(h, nnz, r, c, v));
+        HIPCK(h, talloc(h, tr, &row, nnz));
+        HIPCK(h, talloc(h, tc, &col, nnz));
+        HIPCK(h, talloc(h, tv, &val, nnz));
+        HIPCK(h, h->stage.to_device(row, r, bytes, h->device, s));
+        HIPCK(h, h->stage.to_device(col, c, bytes, h->device, s));
+        HIPCK(h, h->stage.to_device(val, v, bytes, h->device, s));
+        if (nnz <= kHostCheck) return CCDPP_OK;
+        bad = h->d_count;
+        HIPCK(h, ccdk::launch_fill<double>(reinterpret_cast<double*>(bad), 0.0, 1, s));
+        HIPCK(h, ccdk::launch_check_triplets(row, col, val, nnz, h->m, h->n, bad, s));
+        return CCDPP_OK;
+    }
+    // Once the count is known: CCDPP_OK, or EINVAL naming the first of them.
+    static int refuse(ccdpp* h, unsigned long long count, int64_t nnz, const int32_t* r,
+                      const int32_t* c, const float* v) {
+        if (count == 0) return CCDPP_OK;
+        RCK(bad_triplet(h, nnz, r, c, v));
+        return fail(h, CCDPP_EINVAL, "test entries changed during the call");
+    }
+};
+
 int launch_test_err_any(ccdpp* h, const int32_t* dr, const int32_t* dc, const float* dv,
-                        int64_t nnz, const RowFactors* rows, double* part = nullptr,
-                        double* rejected = nullptr) {
+                        int64_t nnz, const RowFactors* rows, const unsigned long long* bad = nullptr,
+                        double* part = nullptr, double* rejected = nullptr) {
     return with_value_type(h, [&](auto z) -> int {
         using V = decltype(z);
         if (rows && (rows->w || rows->h)) {
@@ -1468,12 +1523,12 @@ int launch_test_err_any(ccdpp* h, const int32_t* dr, const int32_t* dc, const fl
             HIPCK(h, ccdk::launch_test_err_rows<V>(dr, dc, dv, nnz, h->rold2new, h->cold2new,
                                                    as<V>(h->W), as<V>(h->H), as<V>(rows->w),
                                                    as<V>(rows->h), h->m, h->n, h->k, pitch, h->sse_part,
-                                                   kReduceParts, h->stream));
+                                                   kReduceParts, bad, h->stream));
             return CCDPP_OK;
         }
         HIPCK(h, ccdk::launch_test_err<V>(dr, dc, dv, nnz, h->rold2new, h->cold2new, as<V>(h->W),
                                           as<V>(h->H), h->m, h->n, h->k,
-                                          part ? part : h->sse_part, kReduceParts, rejected,
+                                          part ? part : h->sse_part, kReduceParts, rejected, bad,
                                           h->stream));
         return CCDPP_OK;
     });
@@ -1497,15 +1552,12 @@ int ccd_impl(ccdpp* h, int32_t outer) {
         // Slot-to-slot maps between the copies, for the residual refresh after each phase.
         // Both maps are allocated before the handle keeps either, so a failed
         // allocation leaves the handle as it was.
-        int32_t *s01, *s10;
-        Tmp t01, t10;
-        HIPCK(h, talloc(t01, &s01, h->L[0].npad));
-        HIPCK(h, talloc(t10, &s10, item_slots(h)));
-        for (Tmp* t : {&t01, &t10}) {
-            h->allocs.emplace_back(t->p, 4 * (t == &t01 ? h->L[0].npad : item_slots(h)));
-            t->p = nullptr;
+        int32_t *s01 = nullptr, *s10 = nullptr;
+        HIPCK(h, dalloc(h, &s01, h->L[0].npad));
+        if (hipError_t e = dalloc(h, &s10, item_slots(h)); e != hipSuccess) {
+            h->kept.give(s01);
+            HIPCK(h, e);
         }
-        h->bytes_held += 4 * (h->L[0].npad + item_slots(h));
         HIPCK(h, hipMemsetAsync(s01, 0xFF, (size_t)h->L[0].npad * 4, h->stream));
         HIPCK(h, hipMemsetAsync(s10, 0xFF, (size_t)item_slots(h) * 4, h->stream));
         HIPCK(h, launch_slot_map(h->pos0, h->map01, h->nnz, s01, h->stream));
@@ -1637,44 +1689,58 @@ int get_factors_impl(ccdpp* h, S* W, S* H) {
     // Both staging buffers first, so that an error leaves W and H untouched.
     S *dW = nullptr, *dH = nullptr;
     Tmp tw, th;
-    if (W) HIPCK(h, talloc(tw, &dW, h->m * h->k));
-    if (H) HIPCK(h, talloc(th, &dH, h->n * h->k));
+    if (W) HIPCK(h, talloc(h, tw, &dW, h->m * h->k));
+    if (H) HIPCK(h, talloc(h, th, &dH, h->n * h->k));
     RCK(with_value_type(h, [&](auto z) -> int {
         using V = decltype(z);
         if (W) HIPCK(h, (ccdk::launch_factor_out<V, S>(as<V>(h->W), h->rnew2old, h->m, h->k, h->k, dW, s)));
         if (H) HIPCK(h, (ccdk::launch_factor_out<V, S>(as<V>(h->H), h->cnew2old, h->n, h->k, h->k, dH, s)));
-        HIPCK(h, hipStreamSynchronize(s));
         return CCDPP_OK;
     }));
-    if (W) HIPCK(h, hipMemcpyAsync(W, dW, h->m * h->k * sizeof(S), hipMemcpyDeviceToHost, s));
-    if (H) HIPCK(h, hipMemcpyAsync(H, dH, h->n * h->k * sizeof(S), hipMemcpyDeviceToHost, s));
-    HIPCK(h, hipStreamSynchronize(s));
+    if (W) HIPCK(h, h->stage.to_host(W, dW, h->m * h->k * sizeof(S), h->device, s));
+    if (H) HIPCK(h, h->stage.to_host(H, dH, h->n * h->k * sizeof(S), h->device, s));
     return CCDPP_OK;
 }
 
 template <class S>
 int set_factors_impl(ccdpp* h, const S* W, const S* H) {
     if (!usable(h)) return CCDPP_ESTATE;
-    if (W)
-        for (int64_t e = 0; e < h->m * h->k; ++e)
+    hipStream_t s = h->stream;
+    const int64_t nw = h->m * h->k, nh = h->n * h->k;
+    auto not_finite = [&]() -> int {  // CCDPP_OK, or EINVAL naming the first such value
+        for (int64_t e = 0; W && e < nw; ++e)
             if (!std::isfinite(W[e]))
                 return fail(h, CCDPP_EINVAL, "W[%lld] is not finite", (long long)e);
-    if (H)
-        for (int64_t e = 0; e < h->n * h->k; ++e)
+        for (int64_t e = 0; H && e < nh; ++e)
             if (!std::isfinite(H[e]))
                 return fail(h, CCDPP_EINVAL, "H[%lld] is not finite", (long long)e);
-    hipStream_t s = h->stream;
+        return CCDPP_OK;
+    };
+    const bool host_check = (W ? nw : 0) + (H ? nh : 0) <= kHostCheck;
+    if (host_check) RCK(not_finite());
     // Staging buffers first: a failed allocation leaves the factors and the residual
     // as they were.
     S *dW = nullptr, *dH = nullptr;
     char* ht = nullptr;  // H row-major, for the rebuild
     const int32_t pitch = ccdk::row_pitch(h->k);
     Tmp tw, th, tht;
-    if (W) HIPCK(h, talloc(tw, &dW, h->m * h->k));
-    if (H) HIPCK(h, talloc(th, &dH, h->n * h->k));
-    HIPCK(h, talloc(tht, &ht, h->n * pitch * (h->dbl ? 8 : 4)));
-    if (W) HIPCK(h, hipMemcpyAsync(dW, W, h->m * h->k * sizeof(S), hipMemcpyHostToDevice, s));
-    if (H) HIPCK(h, hipMemcpyAsync(dH, H, h->n * h->k * sizeof(S), hipMemcpyHostToDevice, s));
+    if (W) HIPCK(h, talloc(h, tw, &dW, h->m * h->k));
+    if (H) HIPCK(h, talloc(h, th, &dH, h->n * h->k));
+    HIPCK(h, talloc(h, tht, &ht, h->n * pitch * (h->dbl ? 8 : 4)));
+    if (W) HIPCK(h, h->stage.to_device(dW, W, nw * sizeof(S), h->device, s));
+    if (H) HIPCK(h, h->stage.to_device(dH, H, nh * sizeof(S), h->device, s));
+    if (!host_check) {  // on the device, before anything changes
+        HIPCK(h, ccdk::launch_fill<double>(reinterpret_cast<double*>(h->d_count), 0.0, 1, s));
+        if (W) HIPCK(h, ccdk::launch_check_finite<S>(dW, nw, h->d_count, s));
+        if (H) HIPCK(h, ccdk::launch_check_finite<S>(dH, nh, h->d_count, s));
+        unsigned long long bad = 0;
+        HIPCK(h, hipMemcpyAsync(&bad, h->d_count, 8, hipMemcpyDeviceToHost, s));
+        HIPCK(h, hipStreamSynchronize(s));
+        if (bad) {
+            RCK(not_finite());
+            return fail(h, CCDPP_EINVAL, "the factors changed during the call");
+        }
+    }
     RCK(with_value_type(h, [&](auto z) -> int {
         using V = decltype(z);
         if (W) HIPCK(h, (ccdk::launch_scatter_factor_in<S, V>(dW, h->rnew2old, h->m, h->k, as<V>(h->W), s)));
@@ -1701,15 +1767,14 @@ int get_residual_impl(ccdpp* h, S* R) {
     hipStream_t s = h->stream;
     S* d;
     Tmp t;
-    HIPCK(h, talloc(t, &d, h->nnz));
+    HIPCK(h, talloc(h, t, &d, h->nnz));
     RCK(flush_pending(h));
     RCK(with_value_type(h, [&](auto z) -> int {
         using V = decltype(z);
         HIPCK(h, (ccdk::launch_copy_mapped<V, S>(as<V>(h->L[0].val), h->pos0, d, h->perm0, h->nnz, s)));
         return CCDPP_OK;
     }));
-    HIPCK(h, hipMemcpyAsync(R, d, h->nnz * sizeof(S), hipMemcpyDeviceToHost, s));
-    HIPCK(h, hipStreamSynchronize(s));
+    HIPCK(h, h->stage.to_host(R, d, h->nnz * sizeof(S), h->device, s));
     return CCDPP_OK;
 }
 }  // namespace
@@ -1728,6 +1793,15 @@ struct DeviceScope {
     }
     DeviceScope(const DeviceScope&) = delete;
     DeviceScope& operator=(const DeviceScope&) = delete;
+};
+// The same for a call with temporaries: those beyond what the handle keeps for the next
+// call go back at its end.
+struct CallScope : DeviceScope {
+    ccdpp* h;
+    explicit CallScope(ccdpp* h_) : DeviceScope(h_), h(h_) {}
+    ~CallScope() {
+        if (h) h->temp.trim(h->temp_keep);
+    }
 };
 
 extern "C" {
@@ -1763,7 +1837,7 @@ int ccdpp_ccd_run(ccdpp_t* h, int32_t outer) {
 int ccdpp_run_until(ccdpp_t* h, int32_t max_outer, int32_t inner, double rel_tol,
                     int64_t test_nnz, const int32_t* test_row, const int32_t* test_col,
                     const float* test_val, double* history, int32_t* outer_done) {
-    DeviceScope dev(h);
+    CallScope dev(h);
     if (!usable(h)) return CCDPP_ESTATE;
     if (!outer_done) return fail(h, CCDPP_EINVAL, "outer_done is NULL");
     if (max_outer < 0 || inner < 1)
@@ -1774,25 +1848,18 @@ int ccdpp_run_until(ccdpp_t* h, int32_t max_outer, int32_t inner, double rel_tol
     if (test_nnz > 0) {
         if (!test_row || !test_col || !test_val)
             return fail(h, CCDPP_EINVAL, "test arrays must be non-NULL when test_nnz > 0");
-        for (int64_t e = 0; e < test_nnz; ++e) {
-            if (test_row[e] < 0 || test_row[e] >= h->m || test_col[e] < 0 || test_col[e] >= h->n)
-                return fail(h, CCDPP_EINVAL, "test entry %lld out of range", (long long)e);
-            if (!std::isfinite(test_val[e]))
-                return fail(h, CCDPP_EINVAL, "test value %lld is not finite", (long long)e);
-        }
     }
     hipStream_t s = h->stream;
-    int32_t *dr = nullptr, *dc = nullptr;
-    float* dv = nullptr;
-    Tmp tr, tc, tv;
+    Held held;
     RowFactors rows;
     if (test_nnz > 0) {
-        HIPCK(h, talloc(tr, &dr, test_nnz));
-        HIPCK(h, talloc(tc, &dc, test_nnz));
-        HIPCK(h, talloc(tv, &dv, test_nnz));
-        HIPCK(h, hipMemcpyAsync(dr, test_row, test_nnz * 4, hipMemcpyHostToDevice, s));
-        HIPCK(h, hipMemcpyAsync(dc, test_col, test_nnz * 4, hipMemcpyHostToDevice, s));
-        HIPCK(h, hipMemcpyAsync(dv, test_val, test_nnz * 4, hipMemcpyHostToDevice, s));
+        RCK(held.load(h, test_nnz, test_row, test_col, test_val));
+        if (held.bad) {  // before any iteration runs
+            unsigned long long bad = 0;
+            HIPCK(h, hipMemcpyAsync(&bad, held.bad, 8, hipMemcpyDeviceToHost, s));
+            HIPCK(h, hipStreamSynchronize(s));
+            RCK(Held::refuse(h, bad, test_nnz, test_row, test_col, test_val));
+        }
         if (max_outer > 0) rows.allocate(h, test_nnz);
     }
     // A fixed-order float64 sum on the device, read back.
@@ -1813,7 +1880,7 @@ int ccdpp_run_until(ccdpp_t* h, int32_t max_outer, int32_t inner, double rel_tol
         RCK(launch_sq_sum_any(h, h->H, h->n * h->k));
         RCK(reduce(&h2));
         if (test_nnz > 0) {
-            RCK(launch_test_err_any(h, dr, dc, dv, test_nnz, &rows));
+            RCK(launch_test_err_any(h, held.row, held.col, held.val, test_nnz, &rows));
             double sum = 0.0;
             RCK(reduce(&sum));
             te = std::sqrt(sum / (double)test_nnz);
@@ -1834,52 +1901,43 @@ int ccdpp_run_until(ccdpp_t* h, int32_t max_outer, int32_t inner, double rel_tol
 
 
 int ccdpp_get_factors(ccdpp_t* h, float* W, float* H) {
-    DeviceScope dev(h);
+    CallScope dev(h);
     return get_factors_impl<float>(h, W, H);
 }
 int ccdpp_get_factors_f64(ccdpp_t* h, double* W, double* H) {
-    DeviceScope dev(h);
+    CallScope dev(h);
     return get_factors_impl<double>(h, W, H);
 }
 int ccdpp_set_factors(ccdpp_t* h, const float* W, const float* H) {
-    DeviceScope dev(h);
+    CallScope dev(h);
     return set_factors_impl<float>(h, W, H);
 }
 int ccdpp_set_factors_f64(ccdpp_t* h, const double* W, const double* H) {
-    DeviceScope dev(h);
+    CallScope dev(h);
     return set_factors_impl<double>(h, W, H);
 }
 
 int ccdpp_rmse(ccdpp_t* h, int64_t nnz, const int32_t* row, const int32_t* col, const float* val,
                double* rmse_out) {
-    DeviceScope dev(h);
+    CallScope dev(h);
     if (!usable(h)) return CCDPP_ESTATE;
     if (!rmse_out) return fail(h, CCDPP_EINVAL, "rmse_out is NULL");
     if (nnz < 1 || nnz > kMaxNnz) return fail(h, CCDPP_EINVAL, "nnz must be in [1, 2^31-1]");
     if (!row || !col || !val) return fail(h, CCDPP_EINVAL, "row, col and val must be non-NULL");
-    for (int64_t e = 0; e < nnz; ++e) {
-        if (row[e] < 0 || row[e] >= h->m || col[e] < 0 || col[e] >= h->n)
-            return fail(h, CCDPP_EINVAL, "test entry %lld out of range", (long long)e);
-        if (!std::isfinite(val[e]))
-            return fail(h, CCDPP_EINVAL, "test value %lld is not finite", (long long)e);
-    }
     hipStream_t s = h->stream;
-    int32_t *dr, *dc;
-    float* dv;
-    Tmp tr, tc, tv;
-    HIPCK(h, talloc(tr, &dr, nnz));
-    HIPCK(h, talloc(tc, &dc, nnz));
-    HIPCK(h, talloc(tv, &dv, nnz));
-    HIPCK(h, hipMemcpyAsync(dr, row, nnz * 4, hipMemcpyHostToDevice, s));
-    HIPCK(h, hipMemcpyAsync(dc, col, nnz * 4, hipMemcpyHostToDevice, s));
-    HIPCK(h, hipMemcpyAsync(dv, val, nnz * 4, hipMemcpyHostToDevice, s));
+    Held held;
     RowFactors rows;
+    RCK(held.load(h, nnz, row, col, val));
     rows.allocate(h, nnz);
-    RCK(launch_test_err_any(h, dr, dc, dv, nnz, &rows));
+    // (a triplet that may not be used stops the kernel)
+    RCK(launch_test_err_any(h, held.row, held.col, held.val, nnz, &rows, held.bad));
     HIPCK(h, ccdk::launch_reduce_sum(h->sse_part, kReduceParts, h->d_scalar, s));
     double sum = 0.0;
+    unsigned long long bad = 0;
     HIPCK(h, hipMemcpyAsync(&sum, h->d_scalar, 8, hipMemcpyDeviceToHost, s));
+    if (held.bad) HIPCK(h, hipMemcpyAsync(&bad, held.bad, 8, hipMemcpyDeviceToHost, s));
     HIPCK(h, hipStreamSynchronize(s));
+    RCK(Held::refuse(h, bad, nnz, row, col, val));
     *rmse_out = std::sqrt(sum / (double)nnz);
     return CCDPP_OK;
 }
@@ -1896,7 +1954,7 @@ int ccdpp_rmse_noalloc(ccdpp_t* h, int64_t nnz, const int32_t* row, const int32_
     double* sc = h->scratch;
     // The same kernel as ccdpp_rmse with the triplets checked on the device (they
     // cannot be checked on the host), partials and counts in the scratch array.
-    RCK(launch_test_err_any(h, row, col, val, nnz, nullptr, sc + kNaPart, sc + kNaRejected));
+    RCK(launch_test_err_any(h, row, col, val, nnz, nullptr, nullptr, sc + kNaPart, sc + kNaRejected));
     HIPCK(h, ccdk::launch_reduce_sum(sc + kNaPart, kReduceParts, sc + kNaTotals, s));
     HIPCK(h, ccdk::launch_reduce_sum(sc + kNaRejected, kReduceParts, sc + kNaTotals + 1, s));
     double tot[2] = {0.0, 0.0};
@@ -1930,11 +1988,11 @@ int ccdpp_train_rmse(ccdpp_t* h, double* rmse_out) {
 
 
 int ccdpp_get_residual(ccdpp_t* h, float* R) {
-    DeviceScope dev(h);
+    CallScope dev(h);
     return get_residual_impl<float>(h, R);
 }
 int ccdpp_get_residual_f64(ccdpp_t* h, double* R) {
-    DeviceScope dev(h);
+    CallScope dev(h);
     return get_residual_impl<double>(h, R);
 }
 
@@ -2032,7 +2090,7 @@ int ccdpp_info(ccdpp_t* h, int64_t* out, int32_t len) {
     const int64_t v[42] = {h->m,         h->n,         h->nnz,       h->k,
                            h->build_us,  h->L[0].gather, h->L[0].P,  width(h->L[0]),
                            h->L[0].grid, h->L[0].nseg, h->L[1].gather, h->L[1].P,
-                           width(h->L[1]), h->L[1].grid, h->L[1].nseg, h->bytes_held,
+                           width(h->L[1]), h->L[1].grid, h->L[1].nseg, (int64_t)(h->kept.held() + h->temp.held()),
                            h->dbl ? 8 : 4, h->L[0].ncut, h->L[0].ncomb, h->L[1].ncut,
                            h->L[1].ncomb, h->L[0].cache + 1, h->L[1].cache + 1,
                            h->L[0].ndelta, h->L[0].npad / ccdk::kWin, h->L[1].ndelta,

@@ -549,9 +549,11 @@ __global__ void k_test_err(const int32_t* __restrict__ row, const int32_t* __res
                            const int32_t* __restrict__ rnew, const int32_t* __restrict__ cnew,
                            const V* __restrict__ W, const V* __restrict__ H, int64_t m,
                            int64_t n, int32_t k, double* __restrict__ part,
-                           double* __restrict__ rejected) {
+                           double* __restrict__ rejected,
+                           const unsigned long long* __restrict__ stop) {
     double acc = 0.0;
     double bad = 0.0;
+    if (stop && *stop != 0) nnz = 0;
     for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnz;
          e += (int64_t)gridDim.x * kT) {
         const int32_t r = row[e], c = col[e];
@@ -587,8 +589,10 @@ __global__ void k_test_err_rows(const int32_t* __restrict__ row, const int32_t* 
                                 const float* __restrict__ val, int64_t nnz,
                                 const int32_t* __restrict__ rnew, const int32_t* __restrict__ cnew,
                                 const V* __restrict__ W, const V* __restrict__ H, int64_t m, int64_t n,
-                                int32_t k, int32_t pitch, double* __restrict__ part) {
+                                int32_t k, int32_t pitch, double* __restrict__ part,
+                                const unsigned long long* __restrict__ stop) {
     double acc = 0.0;
+    if (stop && *stop != 0) nnz = 0;
     for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnz;
          e += (int64_t)gridDim.x * kT) {
         const int64_t i = rnew[row[e]], j = cnew[col[e]];
@@ -614,7 +618,42 @@ __global__ void k_test_err_rows(const int32_t* __restrict__ row, const int32_t* 
     block_total(acc, &part[blockIdx.x]);
 }
 
+// Counts triplets that a kernel must not use (one atomic per wave that has any).
+__global__ void k_check_triplets(const int32_t* __restrict__ row, const int32_t* __restrict__ col,
+                                 const float* __restrict__ val, int64_t nnz, int64_t m, int64_t n,
+                                 unsigned long long* bad) {
+    int count = 0;
+    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnz; e += (int64_t)gridDim.x * kT) {
+        const int32_t r = row[e], c = col[e];
+        count += r < 0 || (int64_t)r >= m || c < 0 || (int64_t)c >= n || !__builtin_isfinite(val[e]);
+    }
+    if (count) atomicAdd(bad, (unsigned long long)count);
+}
+template <class S>
+__global__ void k_check_finite(const S* __restrict__ v, int64_t n, unsigned long long* bad) {
+    int count = 0;
+    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < n; e += (int64_t)gridDim.x * kT)
+        count += !__builtin_isfinite(v[e]);
+    if (count) atomicAdd(bad, (unsigned long long)count);
+}
+
 }  // namespace
+
+hipError_t launch_check_triplets(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
+                                 int64_t m, int64_t n, unsigned long long* bad, hipStream_t s) {
+    if (nnz == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_check_triplets, grid_for(nnz, 4096), dim3(kT), 0, s, row, col, val, nnz, m, n,
+                       bad);
+    return hipGetLastError();
+}
+template <class S>
+hipError_t launch_check_finite(const S* v, int64_t n, unsigned long long* bad, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_check_finite<S>, grid_for(n, 4096), dim3(kT), 0, s, v, n, bad);
+    return hipGetLastError();
+}
+template hipError_t launch_check_finite<float>(const float*, int64_t, unsigned long long*, hipStream_t);
+template hipError_t launch_check_finite<double>(const double*, int64_t, unsigned long long*, hipStream_t);
 
 hipError_t launch_histogram(const int32_t* key, int64_t n, int32_t bins, int32_t* count,
                            int32_t workgroups, hipStream_t s) {
@@ -824,13 +863,14 @@ template <class V>
 hipError_t launch_test_err(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                            const int32_t* rold2new, const int32_t* cold2new, const V* W,
                            const V* H, int64_t m, int64_t n, int32_t k, double* part,
-                           int32_t nparts, double* rejected, hipStream_t s) {
+                           int32_t nparts, double* rejected, const unsigned long long* bad,
+                           hipStream_t s) {
     if (rejected)
         hipLaunchKernelGGL((k_test_err<V, true>), dim3(nparts), dim3(kT), 0, s, row, col, val, nnz,
-                           rold2new, cold2new, W, H, m, n, k, part, rejected);
+                           rold2new, cold2new, W, H, m, n, k, part, rejected, bad);
     else
         hipLaunchKernelGGL((k_test_err<V, false>), dim3(nparts), dim3(kT), 0, s, row, col, val, nnz,
-                           rold2new, cold2new, W, H, m, n, k, part, nullptr);
+                           rold2new, cold2new, W, H, m, n, k, part, nullptr, bad);
     return hipGetLastError();
 }
 
@@ -838,17 +878,18 @@ template <class V>
 hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                                 const int32_t* rold2new, const int32_t* cold2new, const V* W,
                                 const V* H, const V* WT, const V* HT, int64_t m, int64_t n, int32_t k,
-                                int32_t pitch, double* part, int32_t nparts, hipStream_t s) {
+                                int32_t pitch, double* part, int32_t nparts,
+                                const unsigned long long* bad, hipStream_t s) {
     const dim3 grid((unsigned)nparts);
     if (WT && HT)
         hipLaunchKernelGGL((k_test_err_rows<V, true, true>), grid, dim3(kT), 0, s, row, col, val, nnz,
-                           rold2new, cold2new, WT, HT, m, n, k, pitch, part);
+                           rold2new, cold2new, WT, HT, m, n, k, pitch, part, bad);
     else if (HT)
         hipLaunchKernelGGL((k_test_err_rows<V, false, true>), grid, dim3(kT), 0, s, row, col, val, nnz,
-                           rold2new, cold2new, W, HT, m, n, k, pitch, part);
+                           rold2new, cold2new, W, HT, m, n, k, pitch, part, bad);
     else
         hipLaunchKernelGGL((k_test_err_rows<V, true, false>), grid, dim3(kT), 0, s, row, col, val, nnz,
-                           rold2new, cold2new, WT, H, m, n, k, pitch, part);
+                           rold2new, cold2new, WT, H, m, n, k, pitch, part, bad);
     return hipGetLastError();
 }
 
@@ -872,7 +913,7 @@ hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const fl
                                                 int64_t, const int32_t*, const int32_t*,        \
                                                 const V*, const V*, const V*, const V*,         \
                                                 int64_t, int64_t, int32_t, int32_t, double*,    \
-                                                int32_t, hipStream_t);                          \
+                                                int32_t, const unsigned long long*, hipStream_t); \
     template hipError_t launch_copy_mapped<V, V>(const V*, const int32_t*, V*, const int32_t*,  \
                                                  int64_t, hipStream_t);                         \
     template hipError_t launch_consistency<V>(const V*, const int32_t*, const V*,               \
@@ -886,7 +927,8 @@ hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const fl
     template hipError_t launch_test_err<V>(const int32_t*, const int32_t*, const float*,        \
                                            int64_t, const int32_t*, const int32_t*, const V*,   \
                                            const V*, int64_t, int64_t, int32_t, double*,        \
-                                           int32_t, double*, hipStream_t);
+                                           int32_t, double*, const unsigned long long*,         \
+                                           hipStream_t);
 CCDK_BUILD_INSTANTIATE(float)
 CCDK_BUILD_INSTANTIATE(double)
 #undef CCDK_BUILD_INSTANTIATE
@@ -896,37 +938,28 @@ template hipError_t launch_copy_mapped<float, double>(const float*, const int32_
                                                       const int32_t*, int64_t, hipStream_t);
 
 // Radix sort of (key, id) pairs on the low `bits` bits of the key.
-// Grows the shared temporary buffer of the device-wide primitives when needed.
-hipError_t ensure_tmp(void** tmp, size_t* tmp_bytes, size_t need) {
-    if (need <= *tmp_bytes) return hipSuccess;
-    if (*tmp) (void)hipFree(*tmp);
-    *tmp = nullptr;
-    *tmp_bytes = 0;
-    hipError_t e = dev_malloc(tmp, need);
-    if (e == hipSuccess) *tmp_bytes = need;
-    return e;
-}
-
 hipError_t sort_pairs(const uint64_t* kin, uint64_t* kout, const int32_t* vin, int32_t* vout,
-                      int64_t n, int bits, hipStream_t s, void** tmp, size_t* tmp_bytes) {
+                      int64_t n, int bits, hipStream_t s, const TakeFn& take) {
     size_t need = 0;
+    void* tmp = nullptr;
     hipError_t e = rocprim::radix_sort_pairs(nullptr, need, kin, kout, vin, vout, (size_t)n, 0u,
                                              (unsigned)bits, s);
-    if (e == hipSuccess) e = ensure_tmp(tmp, tmp_bytes, need);
+    if (e == hipSuccess) e = take(&tmp, need);
     if (e != hipSuccess) return e;
-    return rocprim::radix_sort_pairs(*tmp, need, kin, kout, vin, vout, (size_t)n, 0u,
+    return rocprim::radix_sort_pairs(tmp, need, kin, kout, vin, vout, (size_t)n, 0u,
                                      (unsigned)bits, s);
 }
 
 hipError_t select_range(const int32_t* key, int64_t n, int32_t lo, int32_t hi, int32_t* out,
-                        int64_t* count, hipStream_t s, void** tmp, size_t* tmp_bytes) {
+                        int64_t* count, hipStream_t s, const TakeFn& take) {
     const rocprim::counting_iterator<int32_t> ids(0);
     const KeyInRange pred{key, lo, hi};
     size_t need = 0;
+    void* tmp = nullptr;
     hipError_t e = rocprim::select(nullptr, need, ids, out, count, (size_t)n, pred, s);
-    if (e == hipSuccess) e = ensure_tmp(tmp, tmp_bytes, need);
+    if (e == hipSuccess) e = take(&tmp, need);
     if (e != hipSuccess) return e;
-    return rocprim::select(*tmp, need, ids, out, count, (size_t)n, pred, s);
+    return rocprim::select(tmp, need, ids, out, count, (size_t)n, pred, s);
 }
 
 hipError_t launch_add(int32_t* a, int64_t n, int32_t delta, hipStream_t s) {

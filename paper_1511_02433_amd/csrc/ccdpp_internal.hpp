@@ -6,7 +6,9 @@
 #include <functional>
 
 #include <cstdint>
+#include <map>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "ccdpp.h"
@@ -330,34 +332,81 @@ struct Layout {
 int host_workers();
 void parallel_ranges(int64_t n, int workers, const std::function<void(int, int64_t, int64_t)>& f);
 
-// Host-to-device copies of caller memory on one stream through two pinned 32 MiB
-// staging buffers (copies under 4 MiB, or without pinned memory, go straight).  The
-// source may be reused once copy() returns; finish() waits until the staging
-// buffers are read, and the destructor does so too before freeing them.
+// Copies between caller (pageable) memory and the device on one stream, through pinned
+// staging slots that a handle keeps: up to kCopyWorkers host threads, each with two
+// slots, fill or empty one while the DMA engine works on the other.  Copies under
+// kStageMin bytes, or without pinned memory, go straight.  to_device: the source may be
+// reused once it returns.  to_host: the data has arrived when it returns.  finish()
+// waits until the slots are idle; release() does so and frees them.
 class Stager {
 public:
-    explicit Stager(hipStream_t s);
-    ~Stager();
+    Stager() = default;
+    ~Stager() { release(); }
     Stager(const Stager&) = delete;
     Stager& operator=(const Stager&) = delete;
-    hipError_t copy(void* dst, const void* src, size_t bytes);
+    hipError_t to_device(void* dst, const void* src, size_t bytes, int device, hipStream_t s);
+    hipError_t to_host(void* dst, const void* src, size_t bytes, int device, hipStream_t s);
     hipError_t finish();
+    void release();
 
 private:
+    // (1.2 GB of triplets to the device: 26.8 ms with six workers of 4 MiB, 30.7 with
+    // eight of 2, 32 with eight of 8; 120 MB: 3.1 ms, 7 with four workers.)
+    static constexpr int kCopyWorkers = 6;
+    static constexpr size_t kChunk = size_t(4) << 20;     // per slot
+    static constexpr size_t kStageMin = size_t(4) << 20;
     bool ready();
-    void release();
-    hipStream_t s_;
-    int workers_;
-    void* slot_[2] = {nullptr, nullptr};
-    hipEvent_t ev_[2] = {nullptr, nullptr};
-    bool busy_[2] = {false, false};
-    int next_ = 0;
+    // f(worker, slot, offset, length) for every chunk of a worker, workers side by side.
+    template <class F>
+    hipError_t run(size_t bytes, int device, F&& f);
+    struct Slot {
+        char* p = nullptr;
+        hipEvent_t ev = nullptr;
+        bool busy = false;
+    };
+    hipError_t idle(Slot& sl);
+    int workers_ = 0;
+    char* pinned_ = nullptr;
+    Slot slot_[kCopyWorkers][2];
     bool tried_ = false;
 };
 
-// Every device allocation of the library (api.hip); a host-forced failure for tests
-// of the error paths returns hipErrorOutOfMemory.
-hipError_t dev_malloc(void** p, size_t bytes);
+// Device memory of one handle in a few large allocations: a hipMalloc or hipFree of some
+// megabytes takes 0.2-0.3 ms on MI355X, and building the copies needs about sixty.
+// take() hands out blocks aligned to 256 bytes, first fit; give() returns one, for
+// use by later work on the handle's stream (which orders it after the work that used it
+// before).  expect() sizes the next allocation.  trim(keep) frees allocations that hold
+// no block until at most `keep` bytes stay; release() frees all.
+class DevicePool {
+public:
+    DevicePool() = default;
+    ~DevicePool() { release(); }
+    DevicePool(const DevicePool&) = delete;
+    DevicePool& operator=(const DevicePool&) = delete;
+    void expect(size_t bytes) { next_ = bytes; }
+    hipError_t take(void** p, size_t bytes);
+    void give(void* p);
+    void trim(size_t keep);
+    void release();
+    size_t held() const { return held_; }
+
+private:
+    struct Slab {
+        char* base = nullptr;
+        size_t size = 0;
+        std::map<size_t, size_t> free;  // offset -> length
+    };
+    struct Block {
+        size_t slab, off, len;
+    };
+    std::vector<Slab> slabs_;  // (freed ones stay as empty entries)
+    std::unordered_map<void*, Block> blocks_;
+    size_t held_ = 0, next_ = 0;
+};
+
+// Whether the device allocation about to be made is to fail (a failure forced from the
+// host for tests of the error paths); counts it otherwise.
+bool alloc_injected();
 
 // Launchers (sweep.hip), instantiated for V = float and V = double.
 hipError_t sweep_init();  // raise the dynamic-LDS limit of the staged kernels
@@ -434,14 +483,16 @@ hipError_t launch_seg_spread(const V* F, int64_t rows, const int32_t* seg_row, i
                              int32_t k, V* out, hipStream_t s);
 template <class V>
 hipError_t launch_sq_sum(const V* v, int64_t n, double* part, int32_t nparts, hipStream_t s);
-// Squared errors of held-out triplets into part[0 .. nparts); with `rejected`, the
+// Squared errors of held-out triplets into part[0 .. nparts); when *bad (if given) is not
+// zero no triplet is looked at and the parts are zero; with `rejected`, the
 // triplets are checked on the device and entries out of range or not finite are
 // skipped and counted per block in rejected[0 .. nparts).
 template <class V>
 hipError_t launch_test_err(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                            const int32_t* rold2new, const int32_t* cold2new, const V* W,
                            const V* H, int64_t m, int64_t n, int32_t k, double* part,
-                           int32_t nparts, double* rejected, hipStream_t s);
+                           int32_t nparts, double* rejected, const unsigned long long* bad,
+                           hipStream_t s);
 // The same with a row-major copy of one or both factors over relabelled ids (WT, HT: rows
 // of `pitch` values, a multiple of 4, zero past k; null: the column-major W or H
 // serves); triplets checked by the caller.
@@ -449,15 +500,22 @@ template <class V>
 hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                                 const int32_t* rold2new, const int32_t* cold2new, const V* W,
                                 const V* H, const V* WT, const V* HT, int64_t m, int64_t n, int32_t k,
-                                int32_t pitch, double* part, int32_t nparts, hipStream_t s);
-// Device-wide primitives (rocPRIM); tmp is a temporary buffer grown as needed and
-// freed by the caller.  sort_pairs: stable radix sort of (key, value) pairs on the
+                                int32_t pitch, double* part, int32_t nparts,
+                                const unsigned long long* bad, hipStream_t s);
+// Adds the number of triplets out of range or not finite, or of values not finite, to *bad.
+hipError_t launch_check_triplets(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
+                                 int64_t m, int64_t n, unsigned long long* bad, hipStream_t s);
+template <class S>
+hipError_t launch_check_finite(const S* v, int64_t n, unsigned long long* bad, hipStream_t s);
+// Device-wide primitives (rocPRIM); take(&p, bytes) gives the temporary memory, which
+// the caller owns.  sort_pairs: stable radix sort of (key, value) pairs on the
 // low `bits` bits of the keys.  select_range: out[0 .. *count) = the indices e < n
 // with lo <= key[e] < hi, in increasing order (count in device memory).
+using TakeFn = std::function<hipError_t(void**, size_t)>;
 hipError_t sort_pairs(const uint64_t* kin, uint64_t* kout, const int32_t* vin, int32_t* vout,
-                      int64_t n, int bits, hipStream_t s, void** tmp, size_t* tmp_bytes);
+                      int64_t n, int bits, hipStream_t s, const TakeFn& take);
 hipError_t select_range(const int32_t* key, int64_t n, int32_t lo, int32_t hi, int32_t* out,
-                        int64_t* count, hipStream_t s, void** tmp, size_t* tmp_bytes);
+                        int64_t* count, hipStream_t s, const TakeFn& take);
 hipError_t launch_add(int32_t* a, int64_t n, int32_t delta, hipStream_t s);
 
 }  // namespace ccdk

@@ -1,8 +1,9 @@
-// Host-side helpers of the library's set-up: a loop split over a few host threads,
-// and the copy of caller (pageable) host memory to the device through two pinned
-// staging buffers, host threads filling one while the DMA engine drains the other.
+// Host-side helpers of the library: a loop split over a few host threads, the copies
+// between caller (pageable) host memory and the device through pinned staging slots,
+// and the pool that a handle's device memory comes from.
 #include <algorithm>
 #include <cstring>
+#include <iterator>
 #include <system_error>
 #include <thread>
 #include <vector>
@@ -34,85 +35,217 @@ void parallel_ranges(int64_t n, int workers, const std::function<void(int, int64
     for (auto& t : pool) t.join();
 }
 
-namespace {
-constexpr size_t kStageBytes = size_t(32) << 20;  // per staging buffer
-constexpr size_t kStageMin = size_t(4) << 20;     // smaller copies go straight through
-}  // namespace
+// ---- staging ------------------------------------------------------------------------
 
-Stager::Stager(hipStream_t s) : s_(s), workers_(host_workers()) {}
-
-Stager::~Stager() { release(); }
-
-void Stager::release() {
-    for (int b = 0; b < 2; ++b) {
-        if (ev_[b]) {
-            if (busy_[b]) (void)hipEventSynchronize(ev_[b]);
-            (void)hipEventDestroy(ev_[b]);
-            ev_[b] = nullptr;
-        }
-        busy_[b] = false;
-        if (slot_[b]) {
-            (void)hipHostFree(slot_[b]);
-            slot_[b] = nullptr;
-        }
-    }
-}
-
-// The pinned buffers, on first use.  Without them (no pinned memory to be had) every
-// copy goes straight from the caller's memory.
+// The pinned slots, on first use (one allocation).
 bool Stager::ready() {
-    if (tried_) return slot_[0] != nullptr;
+    if (tried_) return pinned_ != nullptr;
     tried_ = true;
-    for (int b = 0; b < 2; ++b) {
-        if (hipHostMalloc(&slot_[b], kStageBytes, hipHostMallocDefault) != hipSuccess ||
-            hipEventCreateWithFlags(&ev_[b], hipEventDisableTiming) != hipSuccess) {
-            (void)hipGetLastError();
-            release();
-            return false;
-        }
+    workers_ = std::min(host_workers(), kCopyWorkers);
+    void* p = nullptr;
+    if (hipHostMalloc(&p, (size_t)workers_ * 2 * kChunk, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
     }
+    pinned_ = static_cast<char*>(p);
+    for (int w = 0; w < workers_; ++w)
+        for (int i = 0; i < 2; ++i) {
+            slot_[w][i].p = pinned_ + (size_t)(2 * w + i) * kChunk;
+            if (hipEventCreateWithFlags(&slot_[w][i].ev, hipEventDisableTiming) != hipSuccess) {
+                (void)hipGetLastError();
+                slot_[w][i].ev = nullptr;
+                release();
+                tried_ = true;
+                return false;
+            }
+        }
     return true;
 }
 
-hipError_t Stager::copy(void* dst, const void* src, size_t bytes) {
-    if (bytes == 0) return hipSuccess;
-    if (bytes < kStageMin || !ready())
-        return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s_);
-    const char* from = static_cast<const char*>(src);
-    char* to = static_cast<char*>(dst);
-    for (size_t off = 0; off < bytes; off += kStageBytes) {
-        const size_t len = std::min(kStageBytes, bytes - off);
-        const int b = next_;
-        next_ ^= 1;
-        if (busy_[b]) {
-            hipError_t e = hipEventSynchronize(ev_[b]);  // its last copy has read it
-            if (e != hipSuccess) return e;
-            busy_[b] = false;
-        }
-        char* slot = static_cast<char*>(slot_[b]);
-        const int64_t lines = (int64_t)((len + 63) / 64);
-        parallel_ranges(lines, workers_, [&](int, int64_t lo, int64_t hi) {
-            const size_t a = (size_t)lo * 64, z = std::min(len, (size_t)hi * 64);
-            if (z > a) std::memcpy(slot + a, from + off + a, z - a);
-        });
-        hipError_t e = hipMemcpyAsync(to + off, slot, len, hipMemcpyHostToDevice, s_);
-        if (e != hipSuccess) return e;
-        e = hipEventRecord(ev_[b], s_);
-        if (e != hipSuccess) return e;
-        busy_[b] = true;
-    }
-    return hipSuccess;
+hipError_t Stager::idle(Slot& sl) {
+    if (!sl.busy) return hipSuccess;
+    sl.busy = false;
+    return hipEventSynchronize(sl.ev);
 }
 
 hipError_t Stager::finish() {
-    for (int b = 0; b < 2; ++b) {
-        if (busy_[b]) {
-            hipError_t e = hipEventSynchronize(ev_[b]);
+    hipError_t e = hipSuccess;
+    for (auto& ws : slot_)
+        for (Slot& sl : ws) {
+            const hipError_t r = idle(sl);
+            if (e == hipSuccess) e = r;
+        }
+    return e;
+}
+
+void Stager::release() {
+    (void)finish();
+    for (auto& ws : slot_)
+        for (Slot& sl : ws) {
+            if (sl.ev) (void)hipEventDestroy(sl.ev);
+            sl = Slot{};
+        }
+    if (pinned_) (void)hipHostFree(pinned_);
+    pinned_ = nullptr;
+    tried_ = false;
+}
+
+template <class F>
+hipError_t Stager::run(size_t bytes, int device, F&& f) {
+    const int64_t chunks = (int64_t)((bytes + kChunk - 1) / kChunk);
+    const int used = (int)std::min<int64_t>(workers_, chunks);
+    std::vector<hipError_t> err((size_t)used, hipSuccess);
+    parallel_ranges(used, used, [&](int, int64_t lo, int64_t hi) {
+        int before = 0;  // the current device is a thread's own
+        const bool moved = hipGetDevice(&before) == hipSuccess && before != device &&
+                           hipSetDevice(device) == hipSuccess;
+        for (int64_t w = lo; w < hi; ++w) err[(size_t)w] = f((int)w, used, chunks);
+        if (moved) (void)hipSetDevice(before);
+    });
+    for (hipError_t e : err)
+        if (e != hipSuccess) return e;
+    return hipSuccess;
+}
+
+hipError_t Stager::to_device(void* dst, const void* src, size_t bytes, int device, hipStream_t s) {
+    if (bytes == 0) return hipSuccess;
+    if (bytes < kStageMin || !ready()) return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+    return run(bytes, device, [&](int w, int used, int64_t chunks) -> hipError_t {
+        int i = 0;
+        for (int64_t c = w; c < chunks; c += used, i ^= 1) {
+            Slot& sl = slot_[w][i];
+            hipError_t e = idle(sl);  // its last copy has read it
             if (e != hipSuccess) return e;
-            busy_[b] = false;
+            const size_t off = (size_t)c * kChunk, len = std::min(kChunk, bytes - off);
+            std::memcpy(sl.p, static_cast<const char*>(src) + off, len);
+            e = hipMemcpyAsync(static_cast<char*>(dst) + off, sl.p, len, hipMemcpyHostToDevice, s);
+            if (e == hipSuccess) e = hipEventRecord(sl.ev, s);
+            if (e != hipSuccess) return e;
+            sl.busy = true;
+        }
+        return hipSuccess;
+    });
+}
+
+hipError_t Stager::to_host(void* dst, const void* src, size_t bytes, int device, hipStream_t s) {
+    if (bytes == 0) return hipSuccess;
+    if (bytes < kStageMin || !ready()) {
+        hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+        return e == hipSuccess ? hipStreamSynchronize(s) : e;
+    }
+    return run(bytes, device, [&](int w, int used, int64_t chunks) -> hipError_t {
+        auto request = [&](int64_t c, Slot& sl) -> hipError_t {
+            hipError_t e = idle(sl);
+            if (e != hipSuccess) return e;
+            const size_t off = (size_t)c * kChunk, len = std::min(kChunk, bytes - off);
+            e = hipMemcpyAsync(sl.p, static_cast<const char*>(src) + off, len, hipMemcpyDeviceToHost, s);
+            if (e == hipSuccess) e = hipEventRecord(sl.ev, s);
+            if (e == hipSuccess) sl.busy = true;
+            return e;
+        };
+        hipError_t e = request(w, slot_[w][0]);
+        int i = 0;
+        for (int64_t c = w; e == hipSuccess && c < chunks; c += used, i ^= 1) {
+            if (c + used < chunks) e = request(c + used, slot_[w][i ^ 1]);
+            if (e == hipSuccess) e = idle(slot_[w][i]);  // this chunk has arrived
+            if (e != hipSuccess) break;
+            const size_t off = (size_t)c * kChunk, len = std::min(kChunk, bytes - off);
+            std::memcpy(static_cast<char*>(dst) + off, slot_[w][i].p, len);
+        }
+        return e;
+    });
+}
+
+// ---- device memory --------------------------------------------------------------------
+
+hipError_t DevicePool::take(void** p, size_t bytes) {
+    *p = nullptr;
+    if (alloc_injected()) return hipErrorOutOfMemory;
+    const size_t len = std::max<size_t>((bytes + 255) / 256 * 256, 256);
+    for (int attempt = 0;; ++attempt) {
+        for (size_t i = 0; i < slabs_.size(); ++i) {
+            Slab& sl = slabs_[i];
+            for (auto it = sl.free.begin(); it != sl.free.end(); ++it) {
+                if (it->second < len) continue;
+                const size_t off = it->first, rest = it->second - len;
+                sl.free.erase(it);
+                if (rest) sl.free.emplace(off + len, rest);
+                *p = sl.base + off;
+                blocks_.emplace(*p, Block{i, off, len});
+                return hipSuccess;
+            }
+        }
+        if (attempt) return hipErrorOutOfMemory;  // (not reached: the new one has room)
+        // A new allocation: what is expected, else a quarter of what is held (up to 32 MiB);
+        // 1 MiB at a time for little memory, which takes some microseconds only.
+        const size_t mib = size_t(1) << 20;
+        size_t size = next_ >= 8 * mib ? next_ : held_ >= 8 * mib ? std::min(32 * mib, held_ / 4) : mib;
+        size = std::max(size, len);
+        next_ = 0;
+        void* base = nullptr;
+        hipError_t e = hipMalloc(&base, size);
+        if (e != hipSuccess && size > len) {
+            (void)hipGetLastError();
+            size = len;
+            e = hipMalloc(&base, size);
+        }
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return e;
+        }
+        Slab sl;
+        sl.base = static_cast<char*>(base);
+        sl.size = size;
+        sl.free.emplace(0, size);
+        held_ += size;
+        size_t at = 0;
+        while (at < slabs_.size() && slabs_[at].base) ++at;
+        if (at == slabs_.size())
+            slabs_.push_back(std::move(sl));
+        else
+            slabs_[at] = std::move(sl);
+    }
+}
+
+void DevicePool::give(void* p) {
+    const auto it = blocks_.find(p);
+    if (it == blocks_.end()) return;
+    const Block b = it->second;
+    blocks_.erase(it);
+    std::map<size_t, size_t>& fr = slabs_[b.slab].free;
+    size_t off = b.off, len = b.len;
+    auto next = fr.lower_bound(off);
+    if (next != fr.end() && off + len == next->first) {
+        len += next->second;
+        next = fr.erase(next);
+    }
+    if (next != fr.begin()) {
+        const auto prev = std::prev(next);
+        if (prev->first + prev->second == off) {
+            prev->second += len;
+            return;
         }
     }
-    return hipSuccess;
+    fr.emplace(off, len);
+}
+
+void DevicePool::trim(size_t keep) {
+    for (Slab& sl : slabs_) {
+        if (held_ <= keep) return;
+        if (!sl.base || sl.free.size() != 1 || sl.free.begin()->second != sl.size) continue;
+        (void)hipFree(sl.base);
+        held_ -= sl.size;
+        sl = Slab{};
+    }
+}
+
+void DevicePool::release() {
+    for (Slab& sl : slabs_)
+        if (sl.base) (void)hipFree(sl.base);
+    slabs_.clear();
+    blocks_.clear();
+    held_ = 0;
+    next_ = 0;
 }
 
 }  // namespace ccdk
