@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <memory>
 #include <mutex>
 #include <cmath>
 #include <cstdarg>
@@ -210,8 +211,12 @@ hipError_t dalloc(ccdpp* h, T** p, int64_t count) {
 template <class T>
 int upload(ccdpp* h, T** dst, const std::vector<T>& src) {
     HIPCK(h, dalloc(h, dst, (int64_t)src.size()));
-    if (!src.empty())
-        HIPCK(h, hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice));
+    // The source goes when the caller returns: a staged copy has read it by then.
+    const size_t bytes = src.size() * sizeof(T);
+    if (bytes >= (size_t(8) << 20))
+        HIPCK(h, h->stage.to_device(*dst, src.data(), bytes, h->device, h->stream));
+    else if (bytes > 0)
+        HIPCK(h, hipMemcpy(*dst, src.data(), bytes, hipMemcpyHostToDevice));
     return CCDPP_OK;
 }
 
@@ -234,6 +239,7 @@ struct Tmp {
 template <class T>
 hipError_t talloc(ccdpp* h, Tmp& t, T** p, int64_t count) {
     t.pool = &h->temp;
+    if (t.p) h->temp.give(t.p);
     hipError_t e = h->temp.take(&t.p, (size_t)std::max<int64_t>(count, 1) * sizeof(T));
     *p = static_cast<T*>(t.p);
     return e;
@@ -279,33 +285,28 @@ void relabel(const std::vector<int32_t>& count, std::vector<int32_t>& new2old,
 
 // Rows 0 .. H - 1 of a copy (the longest: rows are relabelled by decreasing length)
 // are worth tiling when their segments cost less than the gathers from global memory
-// a hot layout would give them.  cnt holds the entries per (tile, row) of the tiled
-// layout; a row's segments are its non-empty tiles, and its entries in tiles at or
-// past `hot` columns are those a hot layout staging `hot` columns gathers from global
-// memory.  H maximises the sum of (gathers - seg_cost * segments) over the rows it
-// takes.
-int64_t choose_split(const std::vector<int32_t>& cnt, int64_t P, int64_t rows, int64_t T,
-                     int64_t hot, int64_t seg_cost) {
-    // Segments and cold entries per row, gathered tile by tile (cnt is tile-major).
-    std::vector<int32_t> segs((size_t)rows, 0);
-    std::vector<int64_t> cold((size_t)rows, 0);
-    for (int64_t p = 0; p < P; ++p) {
-        const int32_t* cp = cnt.data() + p * rows;
-        const bool is_cold = p * T >= hot;
-        for (int64_t r = 0; r < rows; ++r) {
-            segs[r] += cp[r] > 0;
-            if (is_cold) cold[r] += cp[r];
-        }
-    }
+// a hot layout would give them.  segs holds each row's segments (its non-empty tiles) in
+// the tiled layout, cold its entries in tiles at or past the columns a hot layout stages,
+// those it gathers from global memory.  H maximises the sum of (gathers - seg_cost * segments) over the rows it
+// takes; *all receives that sum over all rows, positive when tiling the whole copy pays.
+// Measured for whole user-major copies, one first and two plain passes, hot against tiled:
+// 100M ratings over 500,007 x 400,001 (13.6 per segment) 1033 against 773 us, 40M over
+// 300,007 x 150,001 (19.7) 366 against 267, 20M (11.9) 207 against 183, where the sum is
+// positive; 6M (5.7) 75 against 103, 10M over 300,007 x 60,001 (14.2) 86 against
+// 103, where it is negative.
+int64_t choose_split(const std::vector<int32_t>& segs, const std::vector<int32_t>& cold,
+                     int64_t seg_cost, int64_t* all) {
+    const int64_t rows = (int64_t)segs.size();
     int64_t best = 0, H = 0, gain = 0;
     for (int64_t r = 0; r < rows; ++r) {
         if (segs[r] == 0) break;  // the empty rows come last
-        gain += cold[r] - seg_cost * segs[r];
+        gain += (int64_t)cold[r] - seg_cost * segs[r];
         if (gain > best) {
             best = gain;
             H = r + 1;
         }
     }
+    *all = gain;
     return H;
 }
 
@@ -360,41 +361,65 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
         P = 1;
     }
 
-    // Entries per (tile, row).
-    std::vector<int32_t> cnt;
-    for (int attempt = 0; attempt < 2; ++attempt) {
-        if (P == 1 && row_deg) {  // one tile: the entries per row are the row lengths
-            cnt.assign(row_deg, row_deg + rows);
-        } else {
-            int32_t* d_cnt;
-            Tmp tc;
-            HIPCK(h, talloc(h, tc, &d_cnt, P * rows));
-            HIPCK(h, hipMemsetAsync(d_cnt, 0, (size_t)(P * rows) * 4, s));
-            HIPCK(h, launch_seg_histogram(lrow, lcol, N, (int32_t)rows, (int32_t)T, d_cnt, s));
-            cnt.assign((size_t)(P * rows), 0);
-            HIPCK(h, hipMemcpyAsync(cnt.data(), d_cnt, (size_t)(P * rows) * 4,
-                                    hipMemcpyDeviceToHost, s));
-            HIPCK(h, hipStreamSynchronize(s));
-            if (std::accumulate(cnt.begin(), cnt.end(), int64_t(0)) != N)
-                return fail(h, CCDPP_EDEVICE, "segment counts do not add up to nnz");
-        }
-        if (P == 1 || forced == kGatherLds) break;
+    // Entries per (tile, row): on the host the row lengths when there is one tile, else on
+    // the device (d_cnt), from which the host gets each row's segments, entries past the
+    // columns a hot layout's plain passes would stage, and entries.
+    std::vector<int32_t> cnt, segs, cold;
+    int32_t* d_cnt = nullptr;
+    Tmp tc;
+    int64_t S_tiled = 0;
+    if (P > 1) {
+        int32_t* d_stats;
+        Tmp ts;
+        HIPCK(h, talloc(h, tc, &d_cnt, P * rows));
+        HIPCK(h, hipMemsetAsync(d_cnt, 0, (size_t)(P * rows) * 4, s));
+        HIPCK(h, launch_seg_histogram(lrow, lcol, N, (int32_t)rows, (int32_t)T, d_cnt, s));
+        HIPCK(h, talloc(h, ts, &d_stats, 3 * rows));
+        HIPCK(h, launch_row_stats(d_cnt, rows, (int32_t)P, (int32_t)((hmax + T - 1) / T), d_stats, s));
+        std::vector<int32_t> tot((size_t)rows);
+        segs.resize((size_t)rows);
+        cold.resize((size_t)rows);
+        const size_t rb = (size_t)rows * 4;
+        HIPCK(h, h->stage.to_host(segs.data(), d_stats, rb, h->device, s));
+        HIPCK(h, h->stage.to_host(cold.data(), d_stats + rows, rb, h->device, s));
+        HIPCK(h, h->stage.to_host(tot.data(), d_stats + 2 * rows, rb, h->device, s));
+        if (std::accumulate(tot.begin(), tot.end(), int64_t(0)) != N)
+            return fail(h, CCDPP_EDEVICE, "segment counts do not add up to nnz");
+        S_tiled = std::accumulate(segs.begin(), segs.end(), int64_t(0));
         // Tiling pays only when segments are long enough; otherwise stage the leading
         // columns and gather the others through L2.
-        int64_t nonempty = 0;
-        for (int32_t c : cnt) nonempty += c > 0;
-        if (nonempty > 0 && N / nonempty >= kMinTiledSeg) break;
-        if (split_out && forced == 0) {
-            // Stage the hot part's plain passes as wide as one vector allows.
-            const int64_t H = choose_split(cnt, P, rows, T, hmax, kSplitSegCost);
-            if (H > 0 && H < rows) {
+        bool tile = forced == kGatherLds || (S_tiled > 0 && N / S_tiled >= kMinTiledSeg);
+        if (!tile && forced == 0) {
+            // Short segments pay too where a hot layout would gather more from global memory
+            // than they cost, its plain passes staging as much as one vector allows.
+            int64_t all = 0;
+            const int64_t H = choose_split(segs, cold, kSplitSegCost, &all);
+            if (split_out && H > 0 && H < rows) {
                 *split_out = H;
                 return CCDPP_OK;
             }
+            tile = all > 0;
         }
-        mode = kGatherHot;
-        T = cols;
-        P = 1;
+        if (!tile) {
+            mode = kGatherHot;
+            T = cols;
+            P = 1;
+        }
+    }
+    if (P == 1) {
+        if (row_deg) {
+            cnt.assign(row_deg, row_deg + rows);
+        } else {
+            int32_t* d_len;
+            Tmp tl;
+            HIPCK(h, talloc(h, tl, &d_len, rows));
+            HIPCK(h, hipMemsetAsync(d_len, 0, (size_t)rows * 4, s));
+            HIPCK(h, launch_seg_histogram(lrow, lcol, N, (int32_t)rows, (int32_t)T, d_len, s));
+            cnt.assign((size_t)rows, 0);
+            HIPCK(h, h->stage.to_host(cnt.data(), d_len, (size_t)rows * 4, h->device, s));
+        }
+        if (std::accumulate(cnt.begin(), cnt.end(), int64_t(0)) != N)
+            return fail(h, CCDPP_EDEVICE, "segment counts do not add up to nnz");
     }
     // A hot layout stages whole groups of 32 leading columns; with fewer columns than
     // that it gathers everything from global memory.
@@ -421,46 +446,26 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
     // Segments.  P == 1: segment r is row r (rows are relabelled by decreasing
     // length, so the empty ones come last).  P > 1: the non-empty rows of each
     // tile in increasing row order.
-    std::vector<int32_t> segid((size_t)(P * rows), -1), seg_row, tile_seg(P + 1, 0);
-    std::vector<int64_t> seg_start;
-    int64_t pos = 0;
-    for (int64_t p = 0; p < P; ++p) {
-        tile_seg[p] = (int32_t)seg_row.size();
-        const int32_t* cp = cnt.data() + p * rows;
-        for (int64_t r = 0; r < rows; ++r) {
-            if (P > 1 && cp[r] == 0) continue;
-            if (P == 1 && r > 0 && cp[r] > cp[r - 1])
-                return fail(h, CCDPP_EDEVICE, "internal: rows are not in decreasing length");
-            segid[p * rows + r] = (int32_t)seg_row.size();
-            seg_row.push_back((int32_t)r);
-            seg_start.push_back(pos);
-            pos += cp[r];
-        }
-    }
-    tile_seg[P] = (int32_t)seg_row.size();
-    seg_start.push_back(pos);
-    const int64_t S = (int64_t)seg_row.size();
-    if (pos != N) return fail(h, CCDPP_EDEVICE, "internal: segment counts do not cover nnz");
-    L.nseg = S;
-    int64_t S_ne = S;
-    while (S_ne > 0 && seg_start[S_ne] == seg_start[S_ne - 1]) --S_ne;
-    L.nseg_ne = S_ne;
-
     // Alignment padding: every segment starts at a multiple of kE; the first segment
     // of a tile, and a segment that begins a workgroup's share (below), at a multiple
     // of kAlign.  The entries skipped over are padding at the end of the previous
     // segment.
-    const int64_t S_work = P == 1 ? S_ne : S;  // segments that hold entries
-    const std::vector<int64_t> seg_start0 = seg_start;  // unpadded
-    std::vector<int32_t> seg_off((size_t)S, 0);
-    std::vector<char> align_first((size_t)S + 1, 0);
-    for (int64_t p = 0; p < P; ++p) align_first[tile_seg[p]] = 1;
-    int64_t NP = 0;
-    auto pad_layout = [&]() -> int {
+    // seg_start: padded starts, seg_start[S] = NP; d_segid: segment of every (tile, row)
+    // pair, d_off: padding before each segment.
+    std::vector<int32_t> seg_off, tile_seg((size_t)P + 1, 0);
+    std::vector<int64_t> start_p1;            // P == 1
+    std::unique_ptr<int64_t[]> start_tiled;   // P > 1 (not zeroed: the copy fills it)
+    int64_t* seg_start = nullptr;
+    int32_t *d_segid = nullptr, *d_off = nullptr;
+    Tmp tsid, toff;
+    int64_t NP = 0, S = 0, S_ne = 0;
+    std::vector<int64_t> seg_start0;  // P == 1: unpadded
+    std::vector<char> align_first;    // P == 1
+    auto pad_layout = [&]() -> int {  // P == 1
         int64_t off = 0;
-        for (int64_t sg = 0; sg < S_work; ++sg) {
+        for (int64_t sg = 0; sg < S_ne; ++sg) {
             const int64_t al = align_first[sg] ? kAlign : kE;
-            off += (al - (seg_start0[sg] + off) % al) % al;
+            off += -(seg_start0[sg] + off) & (al - 1);  // (al: a power of two)
             if (seg_start0[sg] + off > (int64_t)INT32_MAX - kEntryPad)
                 return fail(h, CCDPP_EINVAL, "too many entries after alignment padding");
             seg_off[sg] = (int32_t)off;
@@ -469,10 +474,79 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
         NP = (N + off + kAlign - 1) / kAlign * kAlign;
         if (NP > (int64_t)INT32_MAX - kEntryPad)
             return fail(h, CCDPP_EINVAL, "too many entries after alignment padding");
-        for (int64_t sg = S_work; sg <= S; ++sg) seg_start[sg] = NP;
+        for (int64_t sg = S_ne; sg <= S; ++sg) seg_start[sg] = NP;
         return CCDPP_OK;
     };
-    RCK(pad_layout());
+    if (P == 1) {
+        S = rows;
+        seg_start0.resize((size_t)S + 1);
+        int64_t pos = 0;
+        for (int64_t r = 0; r < rows; ++r) {
+            if (r > 0 && cnt[r] > cnt[r - 1])
+                return fail(h, CCDPP_EDEVICE, "internal: rows are not in decreasing length");
+            seg_start0[r] = pos;
+            pos += cnt[r];
+        }
+        seg_start0[S] = pos;
+        if (pos != N) return fail(h, CCDPP_EDEVICE, "internal: segment counts do not cover nnz");
+        tile_seg[1] = (int32_t)S;
+        S_ne = S;
+        while (S_ne > 0 && seg_start0[S_ne] == seg_start0[S_ne - 1]) --S_ne;
+        start_p1 = seg_start0;
+        seg_start = start_p1.data();
+        seg_off.assign((size_t)S, 0);
+        align_first.assign((size_t)S + 1, 0);
+        align_first[0] = 1;
+        RCK(pad_layout());
+    } else {
+        // On the device: exclusive scans over the (tile, row) pairs number the non-empty ones
+        // and place them, with lengths rounded up to kE; the tiles' bases follow on the host.
+        S = S_ne = S_tiled;
+        const int64_t pairs = P * rows;
+        int64_t* d_pad;
+        int32_t* d_plain;
+        Tmp tpad, tplain, ttmp;
+        HIPCK(h, talloc(h, tsid, &d_segid, pairs));
+        HIPCK(h, talloc(h, tpad, &d_pad, pairs));
+        HIPCK(h, talloc(h, tplain, &d_plain, pairs));
+        HIPCK(h, scan_segments(d_cnt, pairs, d_segid, d_pad, d_plain, s, take_into(h, ttmp)));
+        std::vector<int64_t> tile_pad((size_t)P + 1, 0), tile_base((size_t)P + 1, 0);
+        int32_t last_len = 0;
+        HIPCK(h, hipMemcpy2DAsync(tile_seg.data(), 4, d_segid, (size_t)rows * 4, 4, (size_t)P,
+                                  hipMemcpyDeviceToHost, s));
+        HIPCK(h, hipMemcpy2DAsync(tile_pad.data(), 8, d_pad, (size_t)rows * 8, 8, (size_t)P,
+                                  hipMemcpyDeviceToHost, s));
+        HIPCK(h, hipMemcpyAsync(&tile_pad[P], d_pad + pairs - 1, 8, hipMemcpyDeviceToHost, s));
+        HIPCK(h, hipMemcpyAsync(&last_len, d_cnt + pairs - 1, 4, hipMemcpyDeviceToHost, s));
+        HIPCK(h, hipStreamSynchronize(s));
+        tile_seg[P] = (int32_t)S;
+        tile_pad[P] += (last_len + kE - 1) / kE * kE;
+        for (int64_t p = 0; p < P; ++p)
+            tile_base[p + 1] = (tile_base[p] + tile_pad[p + 1] - tile_pad[p] + kAlign - 1) / kAlign * kAlign;
+        NP = tile_base[P];
+        if (NP > (int64_t)INT32_MAX - kEntryPad)
+            return fail(h, CCDPP_EINVAL, "too many entries after alignment padding");
+        int64_t *d_tiles, *d_start;
+        int32_t* d_row;
+        Tmp ttl;
+        HIPCK(h, talloc(h, ttl, &d_tiles, 2 * P));
+        HIPCK(h, hipMemcpyAsync(d_tiles, tile_pad.data(), (size_t)P * 8, hipMemcpyHostToDevice, s));
+        HIPCK(h, hipMemcpyAsync(d_tiles + P, tile_base.data(), (size_t)P * 8, hipMemcpyHostToDevice, s));
+        HIPCK(h, dalloc(h, &d_start, S + 1));
+        HIPCK(h, dalloc(h, &d_row, S));
+        L.seg_start = d_start;
+        L.seg_row = d_row;
+        HIPCK(h, talloc(h, toff, &d_off, S));
+        HIPCK(h, launch_seg_emit(d_cnt, d_segid, d_pad, d_plain, rows, (int32_t)P, d_tiles, d_tiles + P,
+                                 d_row, d_start, d_off, s));
+        HIPCK(h, hipMemcpyAsync(d_start + S, &NP, 8, hipMemcpyHostToDevice, s));
+        start_tiled.reset(new int64_t[(size_t)S + 1]);
+        seg_start = start_tiled.get();
+        HIPCK(h, h->stage.to_host(seg_start, d_start, (size_t)(S + 1) * 8, h->device, s));
+    }
+    const int64_t S_work = S_ne;  // segments that hold entries
+    L.nseg = S;
+    L.nseg_ne = S_ne;
 
     // Persistent workgroups own equal shares of the work, cut at multiples of kAlign; a
     // share is processed as one piece per tile it touches, and every piece is cut
@@ -511,33 +585,33 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
     auto upa = [](int64_t v) { return (v + kAlign - 1) / kAlign * kAlign; };
     // Last segment of tile p starting at or before position e.
     auto seg_of = [&](int64_t p, int64_t e) -> int64_t {
-        return std::upper_bound(seg_start.begin() + tile_seg[p], seg_start.begin() + tile_seg[p + 1],
-                                e) - seg_start.begin() - 1;
+        return std::upper_bound(seg_start + tile_seg[p], seg_start + tile_seg[p + 1], e) - seg_start - 1;
     };
     // Work up to position e, and the last position whose work is at most t.
     auto work_at = [&](int64_t e) -> int64_t {
         if (S_work == 0) return e;
-        const int64_t sg = std::upper_bound(seg_start.begin(), seg_start.begin() + S_work, e) -
-                           seg_start.begin();  // segments starting at or before e
+        const int64_t sg = std::upper_bound(seg_start, seg_start + S_work, e) - seg_start;  // segments starting at or before e
         return e + wseg * sg;
     };
     // The largest position e <= NP with work_at(e) <= t (0 if there is none).  Segment
     // starts are strictly increasing, and inside segment s the work grows by one per
-    // position from ws[s], the work at its start, so one search over the segment
+    // position from ws(s), the work at its start, so one search over the segment
     // starts finds it.
-    std::vector<int64_t> ws;
-    auto index_work = [&]() {
-        ws.resize((size_t)S_work);
-        for (int64_t sg = 0; sg < S_work; ++sg) ws[sg] = seg_start[sg] + wseg * (sg + 1);
-    };
+    auto ws = [&](int64_t sg) { return seg_start[sg] + wseg * (sg + 1); };
     auto pos_at = [&](int64_t t) -> int64_t {
         if (S_work == 0) return std::max<int64_t>(0, std::min(t, NP));
-        const int64_t sg = std::upper_bound(ws.begin(), ws.end(), t) - ws.begin() - 1;
+        int64_t sg = -1;  // the last segment with ws <= t
+        for (int64_t lo = 0, hi = S_work; lo < hi;) {
+            const int64_t mid = (lo + hi) / 2;
+            if (ws(mid) <= t)
+                sg = mid, lo = mid + 1;
+            else
+                hi = mid;
+        }
         if (sg < 0) return std::max<int64_t>(0, std::min(t, seg_start[0] - 1));
         const int64_t end = sg + 1 < S_work ? seg_start[sg + 1] - 1 : NP;
-        return std::min(seg_start[sg] + (t - ws[sg]), std::min(end, NP));
+        return std::min(seg_start[sg] + (t - ws(sg)), std::min(end, NP));
     };
-    index_work();
     auto target = [&](int64_t wt, int64_t g) { return wt / G * g + wt % G * g / G; };
     // With P == 1 (float) every share boundary moves to the start of the nearest row,
     // when none of them changes its shares by more than an eighth, or in a small copy
@@ -576,7 +650,6 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
         if (snapped) {
             for (int64_t g = 1; g < G; ++g) align_first[snap[g]] = 1;
             RCK(pad_layout());
-            index_work();
         } else {
             std::fill(snap.begin(), snap.end(), -1);
         }
@@ -713,7 +786,7 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
         L.ncut = (int32_t)crow.size();
     }
     {
-        std::vector<int32_t> ids, sptr(1, 0), srcs, gptr, gsegs;
+        std::vector<int32_t> ids, sptr(1, 0), srcs;  // P == 1
         auto add_cut = [&](size_t c) {
             srcs.insert(srcs.end(), cut_slot.begin() + cut_off[c], cut_slot.begin() + cut_off[c + 1]);
         };
@@ -727,39 +800,52 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
             L.ncomb = (int32_t)ids.size();
             if (!ids.empty()) RCK(upload(h, &L.comb_rows, ids));
         } else {
-            // The segments of each row in tile order: segment ids grow with the tile, so
-            // bucketing them by row in id order lists each row's in tile order.
-            gptr.assign((size_t)rows + 1, 0);
-            for (int64_t sg = 0; sg < S; ++sg) ++gptr[seg_row[sg] + 1];
-            for (int64_t r = 0; r < rows; ++r) gptr[r + 1] += gptr[r];
-            gsegs.resize((size_t)S);
-            {
-                std::vector<int32_t> next(gptr.begin(), gptr.end() - 1);
-                for (int64_t sg = 0; sg < S; ++sg) gsegs[next[seg_row[sg]]++] = (int32_t)sg;
-            }
-            std::vector<int32_t> cut_of((size_t)S, -1);  // index into cut_seg, or -1
-            for (size_t c = 0; c < cut_seg.size(); ++c) cut_of[cut_seg[c]] = (int32_t)c;
-            for (int64_t r = 0; r < rows; ++r) {
-                for (int32_t i = gptr[r]; i < gptr[r + 1]; ++i) {
-                    const int32_t sg = gsegs[i];
-                    if (cut_of[sg] < 0)
-                        srcs.push_back(sg);
-                    else
-                        add_cut((size_t)cut_of[sg]);
-                }
-                sptr.push_back((int32_t)srcs.size());
-            }
+            // Each row's segments in tile order, and its partial slots: a segment's own, or
+            // those of the chunks that cut it.
+            int32_t *d_cut, *d_seg, *d_coff, *d_cslot, *gptr, *sptr, *gsegs, *dsrcs;
+            Tmp tcut, tseg, tcoff, tslot, ttmp;
+            const int64_t nc = (int64_t)cut_seg.size();
+            HIPCK(h, talloc(h, tcut, &d_cut, S));
+            HIPCK(h, talloc(h, tseg, &d_seg, nc));
+            HIPCK(h, talloc(h, tcoff, &d_coff, nc + 1));
+            HIPCK(h, talloc(h, tslot, &d_cslot, (int64_t)cut_slot.size()));
+            HIPCK(h, hipMemcpyAsync(d_seg, cut_seg.data(), cut_seg.size() * 4, hipMemcpyHostToDevice, s));
+            HIPCK(h, hipMemcpyAsync(d_coff, cut_off.data(), cut_off.size() * 4, hipMemcpyHostToDevice, s));
+            HIPCK(h, hipMemcpyAsync(d_cslot, cut_slot.data(), cut_slot.size() * 4, hipMemcpyHostToDevice, s));
+            HIPCK(h, hipMemsetAsync(d_cut, 0xFF, (size_t)S * 4, s));
+            HIPCK(h, launch_mark_cuts(d_seg, nc, d_cut, s));
+            HIPCK(h, dalloc(h, &gptr, rows + 1));
+            HIPCK(h, dalloc(h, &sptr, rows + 1));
+            HIPCK(h, launch_row_counts(d_cnt, d_segid, rows, (int32_t)P, d_cut, d_coff, gptr, sptr, s));
+            HIPCK(h, scan_counts(gptr, rows + 1, s, take_into(h, ttmp)));
+            HIPCK(h, scan_counts(sptr, rows + 1, s, take_into(h, ttmp)));
+            int32_t total[2] = {0, 0};
+            HIPCK(h, hipMemcpyAsync(&total[0], gptr + rows, 4, hipMemcpyDeviceToHost, s));
+            HIPCK(h, hipMemcpyAsync(&total[1], sptr + rows, 4, hipMemcpyDeviceToHost, s));
+            HIPCK(h, hipStreamSynchronize(s));
+            if (total[0] != S) return fail(h, CCDPP_EDEVICE, "internal: the rows' segments do not add up");
+            HIPCK(h, dalloc(h, &gsegs, S));
+            HIPCK(h, dalloc(h, &dsrcs, (int64_t)total[1]));
+            HIPCK(h, launch_row_lists(d_cnt, d_segid, rows, (int32_t)P, d_cut, d_coff, d_cslot, gptr, sptr,
+                                      gsegs, dsrcs, s));
             L.ncomb = (int32_t)rows;
-            RCK(upload(h, &L.row_seg_ptr, gptr));
-            RCK(upload(h, &L.row_segs, gsegs));
+            L.row_seg_ptr = gptr;
+            L.row_segs = gsegs;
+            L.src_ptr = sptr;
+            L.srcs = dsrcs;
+            L.nsrc = total[1];
+            HIPCK(h, hipStreamSynchronize(s));  // the lists' host copies go
         }
-        if (L.ncomb > 0) {
+        if (P == 1 && L.ncomb > 0) {
             RCK(upload(h, &L.src_ptr, sptr));
             RCK(upload(h, &L.srcs, srcs));
         }
-        L.nsrc = (int64_t)srcs.size();
-        // A quad per row when rows have fewer than 12 partials on average.
-        L.comb_lanes = L.ncomb > 0 && L.nsrc < 12 * (int64_t)L.ncomb ? 4 : 16;
+        if (P == 1) L.nsrc = (int64_t)srcs.size();
+        // A quad per row when rows have fewer than 12 partials on average, or when there
+        // are rows enough to fill the chip with quads (us per combine, 16 lanes against 4:
+        // 1.0M rows of 18 partials 129 against 80, 300,007 of 7 25 against 12, 163,000 of
+        // 26 55 against 50; 17,770 of 36 7.5 against 8.4).
+        L.comb_lanes = L.ncomb >= kQuadRows || L.nsrc < 12 * (int64_t)L.ncomb ? 4 : 16;
         RCK(with_value_type(h, [&](auto z) -> int {
             part_t<decltype(z)>* pp;
             HIPCK(h, dalloc(h, &pp, nslots));
@@ -773,8 +859,12 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
         HIPCK(h, dalloc(h, &pk, 4 * cols));
         L.pk = pk;
     }
-    RCK(upload(h, &L.seg_start, seg_start));
-    RCK(upload(h, &L.seg_row, seg_row));
+    if (P == 1) {
+        std::vector<int32_t> seg_row((size_t)S);
+        std::iota(seg_row.begin(), seg_row.end(), 0);
+        RCK(upload(h, &L.seg_start, start_p1));
+        RCK(upload(h, &L.seg_row, seg_row));
+    }
     RCK(upload(h, &L.tile_seg, tile_seg));
     RCK(upload(h, &L.wg_head, heads));
     RCK(upload(h, &L.wg_first, firsts));
@@ -808,14 +898,14 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
     }
     HIPCK(h, launch_fill_idx(L.idx, L.idx16, L.pad, NP + kEntryPad, s));
     if (N > 0) {
-        int32_t *d_segid, *d_off;
         uint64_t *k0, *k1;
         int32_t* i0;
-        Tmp tsid, toff, tk0, tk1, ti0, ttmp;
-        HIPCK(h, talloc(h, tsid, &d_segid, P * rows));
-        HIPCK(h, hipMemcpyAsync(d_segid, segid.data(), segid.size() * 4, hipMemcpyHostToDevice, s));
-        HIPCK(h, talloc(h, toff, &d_off, S));
-        HIPCK(h, hipMemcpyAsync(d_off, seg_off.data(), seg_off.size() * 4, hipMemcpyHostToDevice, s));
+        Tmp tk0, tk1, ti0, ttmp;
+        if (P == 1) {  // segment r is row r
+            d_segid = L.seg_row;
+            HIPCK(h, talloc(h, toff, &d_off, S));
+            HIPCK(h, h->stage.to_device(d_off, seg_off.data(), (size_t)S * 4, h->device, s));
+        }
         HIPCK(h, talloc(h, tk0, &k0, N));
         HIPCK(h, talloc(h, tk1, &k1, N));
         HIPCK(h, talloc(h, ti0, &i0, N));
@@ -1195,7 +1285,7 @@ int create_timed(ccdpp* h, const int32_t* row, const int32_t* col, const float* 
     const auto t0 = std::chrono::steady_clock::now();
     RCK(create_device(h, row, col, val, seed, opt));
     HIPCK(h, h->stage.finish());
-    h->temp.trim(0);
+    h->temp.trim(h->temp_keep);
     h->build_us = std::chrono::duration_cast<std::chrono::microseconds>(
                       std::chrono::steady_clock::now() - t0)
                       .count();

@@ -8,8 +8,10 @@
 // triplet index along so values and the map between the two copies follow.
 // Adjacent equal keys after the user-major sort are repeated positions.
 #include <rocprim/device/device_radix_sort.hpp>
+#include <rocprim/device/device_scan.hpp>
 #include <rocprim/device/device_select.hpp>
 #include <rocprim/iterator/counting_iterator.hpp>
+#include <rocprim/iterator/transform_iterator.hpp>
 
 #include <algorithm>
 #include <type_traits>
@@ -618,6 +620,103 @@ __global__ void k_test_err_rows(const int32_t* __restrict__ row, const int32_t* 
     block_total(acc, &part[blockIdx.x]);
 }
 
+// ---- segments of a tiled copy ----------------------------------------------------------
+// A thread per row walks the row's pairs tile by tile: neighbouring threads read
+// neighbouring words.  (The host's loops over 31M pairs and 18M segments took 0.4 s.)
+__global__ void k_row_stats(const int32_t* __restrict__ cnt, int64_t rows, int32_t P, int32_t cold_tile,
+                            int32_t* __restrict__ stats) {
+    const int64_t r = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (r >= rows) return;
+    int32_t segs = 0, cold = 0, all = 0;
+    for (int32_t p = 0; p < P; ++p) {
+        const int32_t c = cnt[(int64_t)p * rows + r];
+        segs += c > 0;
+        all += c;
+        if (p >= cold_tile) cold += c;
+    }
+    stats[r] = segs;
+    stats[rows + r] = cold;
+    stats[2 * rows + r] = all;
+}
+
+// (blockIdx.y: the tile)
+__global__ void k_seg_emit(const int32_t* __restrict__ cnt, const int32_t* __restrict__ segid,
+                           const int64_t* __restrict__ pad, const int32_t* __restrict__ plain,
+                           int64_t rows, const int64_t* __restrict__ tile_pad,
+                           const int64_t* __restrict__ tile_base, int32_t* __restrict__ seg_row,
+                           int64_t* __restrict__ seg_start, int32_t* __restrict__ seg_off) {
+    const int p = (int)blockIdx.y;
+    for (int64_t r = (int64_t)blockIdx.x * kT + threadIdx.x; r < rows; r += (int64_t)gridDim.x * kT) {
+        const int64_t i = (int64_t)p * rows + r;
+        if (cnt[i] == 0) continue;
+        const int32_t sg = segid[i];
+        const int64_t start = tile_base[p] + pad[i] - tile_pad[p];
+        seg_row[sg] = (int32_t)r;
+        seg_start[sg] = start;
+        seg_off[sg] = (int32_t)(start - plain[i]);
+    }
+}
+
+__global__ void k_mark_cuts(const int32_t* __restrict__ cut_seg, int64_t n, int32_t* __restrict__ cut_of) {
+    const int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (c < n) cut_of[cut_seg[c]] = (int32_t)c;
+}
+
+__global__ void k_row_counts(const int32_t* __restrict__ cnt, const int32_t* __restrict__ segid,
+                             int64_t rows, int32_t P, const int32_t* __restrict__ cut_of,
+                             const int32_t* __restrict__ cut_off, int32_t* __restrict__ nsegs,
+                             int32_t* __restrict__ nslots) {
+    const int64_t r = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (r > rows) return;
+    int32_t segs = 0, slots = 0;
+    for (int32_t p = 0; r < rows && p < P; ++p) {
+        const int64_t i = (int64_t)p * rows + r;
+        if (cnt[i] == 0) continue;
+        const int32_t c = cut_of[segid[i]];
+        ++segs;
+        slots += c < 0 ? 1 : cut_off[c + 1] - cut_off[c];
+    }
+    nsegs[r] = segs;
+    nslots[r] = slots;
+}
+
+__global__ void k_row_lists(const int32_t* __restrict__ cnt, const int32_t* __restrict__ segid,
+                            int64_t rows, int32_t P, const int32_t* __restrict__ cut_of,
+                            const int32_t* __restrict__ cut_off, const int32_t* __restrict__ cut_slot,
+                            const int32_t* __restrict__ seg_ptr, const int32_t* __restrict__ slot_ptr,
+                            int32_t* __restrict__ segs, int32_t* __restrict__ slots) {
+    const int64_t r = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (r >= rows) return;
+    int32_t a = seg_ptr[r], b = slot_ptr[r];
+    for (int32_t p = 0; p < P; ++p) {
+        const int64_t i = (int64_t)p * rows + r;
+        if (cnt[i] == 0) continue;
+        const int32_t sg = segid[i], c = cut_of[sg];
+        segs[a++] = sg;
+        if (c < 0) {
+            slots[b++] = sg;
+        } else {
+            for (int32_t k = cut_off[c]; k < cut_off[c + 1]; ++k) slots[b++] = cut_slot[k];
+        }
+    }
+}
+
+struct NonEmpty {
+    __host__ __device__ int32_t operator()(int32_t c) const { return c > 0; }
+};
+struct Padded {
+    __host__ __device__ int64_t operator()(int32_t c) const { return ((int64_t)c + kE - 1) / kE * kE; }
+};
+template <class In, class T>
+hipError_t scan_to(In in, T* out, int64_t n, hipStream_t s, const TakeFn& take) {
+    size_t need = 0;
+    void* tmp = nullptr;
+    hipError_t e = rocprim::exclusive_scan(nullptr, need, in, out, T(0), (size_t)n, rocprim::plus<T>(), s);
+    if (e == hipSuccess) e = take(&tmp, need);
+    if (e != hipSuccess) return e;
+    return rocprim::exclusive_scan(tmp, need, in, out, T(0), (size_t)n, rocprim::plus<T>(), s);
+}
+
 // Counts triplets that a kernel must not use (one atomic per wave that has any).
 __global__ void k_check_triplets(const int32_t* __restrict__ row, const int32_t* __restrict__ col,
                                  const float* __restrict__ val, int64_t nnz, int64_t m, int64_t n,
@@ -638,6 +737,57 @@ __global__ void k_check_finite(const S* __restrict__ v, int64_t n, unsigned long
 }
 
 }  // namespace
+
+hipError_t launch_row_stats(const int32_t* cnt, int64_t rows, int32_t P, int32_t cold_tile,
+                            int32_t* stats, hipStream_t s) {
+    hipLaunchKernelGGL(k_row_stats, grid_for(rows), dim3(kT), 0, s, cnt, rows, P, cold_tile, stats);
+    return hipGetLastError();
+}
+hipError_t launch_seg_emit(const int32_t* cnt, const int32_t* segid, const int64_t* pad,
+                           const int32_t* plain, int64_t rows, int32_t P, const int64_t* tile_pad,
+                           const int64_t* tile_base, int32_t* seg_row, int64_t* seg_start,
+                           int32_t* seg_off, hipStream_t s) {
+    // (the grid's second dimension is limited to 65,535: more tiles go in turns)
+    for (int32_t p = 0; p < P; p += 65535) {
+        const int32_t np = std::min(P - p, 65535);
+        dim3 grid = grid_for(rows, 4096);
+        grid.y = (unsigned)np;
+        const int64_t at = (int64_t)p * rows;
+        hipLaunchKernelGGL(k_seg_emit, grid, dim3(kT), 0, s, cnt + at, segid + at, pad + at, plain + at,
+                           rows, tile_pad + p, tile_base + p, seg_row, seg_start, seg_off);
+    }
+    return hipGetLastError();
+}
+hipError_t launch_mark_cuts(const int32_t* cut_seg, int64_t n, int32_t* cut_of, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_mark_cuts, grid_for(n), dim3(kT), 0, s, cut_seg, n, cut_of);
+    return hipGetLastError();
+}
+hipError_t launch_row_counts(const int32_t* cnt, const int32_t* segid, int64_t rows, int32_t P,
+                             const int32_t* cut_of, const int32_t* cut_off, int32_t* nsegs,
+                             int32_t* nslots, hipStream_t s) {
+    hipLaunchKernelGGL(k_row_counts, grid_for(rows + 1), dim3(kT), 0, s, cnt, segid, rows, P, cut_of,
+                       cut_off, nsegs, nslots);
+    return hipGetLastError();
+}
+hipError_t launch_row_lists(const int32_t* cnt, const int32_t* segid, int64_t rows, int32_t P,
+                            const int32_t* cut_of, const int32_t* cut_off, const int32_t* cut_slot,
+                            const int32_t* seg_ptr, const int32_t* slot_ptr, int32_t* segs,
+                            int32_t* slots, hipStream_t s) {
+    hipLaunchKernelGGL(k_row_lists, grid_for(rows), dim3(kT), 0, s, cnt, segid, rows, P, cut_of, cut_off,
+                       cut_slot, seg_ptr, slot_ptr, segs, slots);
+    return hipGetLastError();
+}
+hipError_t scan_segments(const int32_t* cnt, int64_t n, int32_t* segid, int64_t* pad, int32_t* plain,
+                         hipStream_t s, const TakeFn& take) {
+    hipError_t e = scan_to(rocprim::make_transform_iterator(cnt, NonEmpty()), segid, n, s, take);
+    if (e == hipSuccess) e = scan_to(rocprim::make_transform_iterator(cnt, Padded()), pad, n, s, take);
+    if (e == hipSuccess) e = scan_to(cnt, plain, n, s, take);
+    return e;
+}
+hipError_t scan_counts(int32_t* a, int64_t n, hipStream_t s, const TakeFn& take) {
+    return scan_to(a, a, n, s, take);
+}
 
 hipError_t launch_check_triplets(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                                  int64_t m, int64_t n, unsigned long long* bad, hipStream_t s) {

@@ -103,6 +103,7 @@ constexpr int kMinTiledSeg = 32;          // mean entries per segment for tiling
 constexpr int kSegWeight = 4;             // default work of one segment, in entries
 constexpr int64_t kSnapEntries = 4096;    // how far a small copy's share bound may move to a row start
 constexpr int64_t kSmallCopy = 256 * kWaves * kWin;  // one window per wave of the chip (2.1M entries)
+constexpr int kQuadRows = 65536;          // rows from which the combine takes four lanes each
 constexpr int kChunkMid = 1;              // chunk flag: its first segment began in an earlier chunk
 constexpr int kChunkCont = 2;             // chunk flag: its last segment goes on past its end
 constexpr int kEntryPad = 64;             // entries of padding after idx and val (loads past the end)
@@ -306,7 +307,8 @@ struct Layout {
     int32_t* piece_seg = nullptr;
     int32_t* chunk_flags = nullptr;
     int32_t npieces = 0;
-    int32_t comb_lanes = 16;         // lanes per row of the combine (4 when rows have few partials)
+    int32_t comb_lanes = 16;         // lanes per row of the combine (4 when rows have few
+                                     // partials or are many)
     int32_t ncomb = 0;               // rows the combine finishes (P == 1: those cut
                                      // between workgroups)
     int32_t* comb_rows = nullptr;    // P == 1: their ids
@@ -335,8 +337,9 @@ void parallel_ranges(int64_t n, int workers, const std::function<void(int, int64
 // Copies between caller (pageable) memory and the device on one stream, through pinned
 // staging slots that a handle keeps: up to kCopyWorkers host threads, each with two
 // slots, fill or empty one while the DMA engine works on the other.  Copies under
-// kStageMin bytes, or without pinned memory, go straight.  to_device: the source may be
-// reused once it returns.  to_host: the data has arrived when it returns.  finish()
+// kStageMin bytes, or without pinned memory, go straight.  to_device: the source of a copy
+// of kStageMin bytes or more may be reused once it returns, that of a shorter one once
+// the stream has passed it.  to_host: the data has arrived when it returns.  finish()
 // waits until the slots are idle; release() does so and frees them.
 class Stager {
 public:
@@ -511,11 +514,35 @@ hipError_t launch_check_finite(const S* v, int64_t n, unsigned long long* bad, h
 // the caller owns.  sort_pairs: stable radix sort of (key, value) pairs on the
 // low `bits` bits of the keys.  select_range: out[0 .. *count) = the indices e < n
 // with lo <= key[e] < hi, in increasing order (count in device memory).
+// Segments of a tiled copy from the entries per (tile, row) pair (cnt, tile-major):
+// each row's non-empty pairs, its entries in tiles from `cold_tile` on, and its entries
+// (stats: three arrays of `rows`); per pair the number of non-empty pairs before it, their
+// lengths rounded up to kE, and their lengths; per non-empty pair its row, its padded
+// start and the padding before it; per row the numbers of segments and partial slots
+// (both with a 0 at [rows], for scan_counts) and the lists of them.
+hipError_t launch_row_stats(const int32_t* cnt, int64_t rows, int32_t P, int32_t cold_tile,
+                            int32_t* stats, hipStream_t s);
+hipError_t launch_seg_emit(const int32_t* cnt, const int32_t* segid, const int64_t* pad,
+                           const int32_t* plain, int64_t rows, int32_t P, const int64_t* tile_pad,
+                           const int64_t* tile_base, int32_t* seg_row, int64_t* seg_start,
+                           int32_t* seg_off, hipStream_t s);
+hipError_t launch_mark_cuts(const int32_t* cut_seg, int64_t n, int32_t* cut_of, hipStream_t s);
+hipError_t launch_row_counts(const int32_t* cnt, const int32_t* segid, int64_t rows, int32_t P,
+                             const int32_t* cut_of, const int32_t* cut_off, int32_t* nsegs,
+                             int32_t* nslots, hipStream_t s);
+hipError_t launch_row_lists(const int32_t* cnt, const int32_t* segid, int64_t rows, int32_t P,
+                            const int32_t* cut_of, const int32_t* cut_off, const int32_t* cut_slot,
+                            const int32_t* seg_ptr, const int32_t* slot_ptr, int32_t* segs,
+                            int32_t* slots, hipStream_t s);
 using TakeFn = std::function<hipError_t(void**, size_t)>;
 hipError_t sort_pairs(const uint64_t* kin, uint64_t* kout, const int32_t* vin, int32_t* vout,
                       int64_t n, int bits, hipStream_t s, const TakeFn& take);
 hipError_t select_range(const int32_t* key, int64_t n, int32_t lo, int32_t hi, int32_t* out,
                         int64_t* count, hipStream_t s, const TakeFn& take);
+hipError_t scan_segments(const int32_t* cnt, int64_t n, int32_t* segid, int64_t* pad, int32_t* plain,
+                         hipStream_t s, const TakeFn& take);
+// a[i] = a[0] + ... + a[i - 1], in place
+hipError_t scan_counts(int32_t* a, int64_t n, hipStream_t s, const TakeFn& take);
 hipError_t launch_add(int32_t* a, int64_t n, int32_t delta, hipStream_t s);
 
 }  // namespace ccdk

@@ -109,7 +109,11 @@ hipError_t Stager::run(size_t bytes, int device, F&& f) {
 
 hipError_t Stager::to_device(void* dst, const void* src, size_t bytes, int device, hipStream_t s) {
     if (bytes == 0) return hipSuccess;
-    if (bytes < kStageMin || !ready()) return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+    if (bytes < kStageMin) return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+    if (!ready()) {  // no pinned memory: the source may go when this returns
+        hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+        return e == hipSuccess ? hipStreamSynchronize(s) : e;
+    }
     return run(bytes, device, [&](int w, int used, int64_t chunks) -> hipError_t {
         int i = 0;
         for (int64_t c = w; c < chunks; c += used, i ^= 1) {

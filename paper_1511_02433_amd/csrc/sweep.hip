@@ -876,7 +876,7 @@ __device__ __forceinline__ double quad_sum(double x) {
 }
 
 // Fixed-order combine of a row's partials: L lanes per row (16, one DPP row, or
-// 4, a quad, for layouts whose rows have few partials); lane l adds the row's
+// 4, a quad, for layouts whose rows have few partials or are many); lane l adds the row's
 // partial slots l, l + L, ... in entry order, then a fixed tree over the L
 // lanes.  With yseg, the coordinate is also written to every segment of the row.
 template <int L, class V>

@@ -77,3 +77,33 @@ def test_cached_accesses_change_nothing(kind):
         g.close()
     for a, b in zip(*outs):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("per_row,tiled", [(60, True), (4, False)])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_short_segments_are_tiled_where_gathers_cost_more(per_row, tiled, precision):
+    # Rows spread evenly over 200,000 columns: of 60 entries, about 48 lie past the columns
+    # that a hot layout stages, against ten segments in tiles; of 4 entries, as many
+    # segments as entries.  The transposed problem takes the item-major copy there.
+    m, n, k, lam = 2_000, 200_000, 2, 0.5
+    row, col, val, H0 = synth.lengths_problem([per_row] * m, n, k, seed=per_row)
+    print(f"case: {per_row} per row, precision {precision}", flush=True)
+    for transposed in (False, True):
+        a = (n, m, k, lam, col, row, val) if transposed else (m, n, k, lam, row, col, val)
+        h0 = np.random.default_rng(3).standard_normal((a[1], k)).astype(np.float32) * 0.1
+        g = CCDPP(*a, opts=make_options(precision=precision))
+        info = g.info()
+        side = "v" if transposed else "u"
+        assert (info[f"{side}_gather"] == 2 and info[f"{side}_tiles"] > 1) == tiled
+        g.set_factors(None, h0)
+        o = Oracle(*a, h0)
+        for step in range(2):
+            g.run(1, 2)
+            o.run(1, 2)
+            W, H = g.factors_f64()
+            Wo, Ho = o.factors()
+            tol = 1e-9 if precision else 1e-3
+            assert colscaled_max_rel_err(W, Wo) <= tol and colscaled_max_rel_err(H, Ho) <= tol
+        assert g.check_consistency() == 0
+        g.close()
+        o.close()
