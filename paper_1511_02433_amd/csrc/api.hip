@@ -317,11 +317,13 @@ int64_t choose_split(const std::vector<int32_t>& segs, const std::vector<int32_t
 // index in lrow/lcol/val_in and epos[e] the slot of its value (val_slot).  With
 // split_out, a copy that automatic mode would make hot may instead ask to be split:
 // *split_out receives the number of leading rows to tile (0: not split), and a
-// nonzero answer returns before anything is built.
+// nonzero answer returns before anything is built.  order (may be null): the entries
+// in an order that keeps those of a tile together.
 int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, const int32_t* lrow,
                  const int32_t* lcol, const float* val_in, const ccdpp_options_t* opt,
                  int32_t* perm, int32_t* epos, hipStream_t s, int64_t nnz,
-                 int64_t* split_out = nullptr, const int32_t* row_deg = nullptr) {
+                 int64_t* split_out = nullptr, const int32_t* row_deg = nullptr,
+                 const int32_t* order = nullptr) {
     using namespace ccdk;
     const int64_t N = nnz;
     L.rows = rows;
@@ -373,7 +375,7 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
         Tmp ts;
         HIPCK(h, talloc(h, tc, &d_cnt, P * rows));
         HIPCK(h, hipMemsetAsync(d_cnt, 0, (size_t)(P * rows) * 4, s));
-        HIPCK(h, launch_seg_histogram(lrow, lcol, N, (int32_t)rows, (int32_t)T, d_cnt, s));
+        HIPCK(h, launch_seg_histogram(lrow, lcol, N, (int32_t)rows, (int32_t)T, order, h->cus, d_cnt, s));
         HIPCK(h, talloc(h, ts, &d_stats, 3 * rows));
         HIPCK(h, launch_row_stats(d_cnt, rows, (int32_t)P, (int32_t)((hmax + T - 1) / T), d_stats, s));
         std::vector<int32_t> tot((size_t)rows);
@@ -414,7 +416,7 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
             Tmp tl;
             HIPCK(h, talloc(h, tl, &d_len, rows));
             HIPCK(h, hipMemsetAsync(d_len, 0, (size_t)rows * 4, s));
-            HIPCK(h, launch_seg_histogram(lrow, lcol, N, (int32_t)rows, (int32_t)T, d_len, s));
+            HIPCK(h, launch_seg_histogram(lrow, lcol, N, (int32_t)rows, (int32_t)T, nullptr, h->cus, d_len, s));
             cnt.assign((size_t)rows, 0);
             HIPCK(h, h->stage.to_host(cnt.data(), d_len, (size_t)rows * 4, h->device, s));
         }
@@ -1037,11 +1039,12 @@ int build_item_major(ccdpp* h, const int32_t* lrow, const int32_t* lcol, const f
     const int32_t forced = opt ? opt->split_rows : 0;
     int64_t H = forced > 0 ? forced : 0;
     if (forced == 0) {
-        RCK(build_layout(h, 1, h->L[1], n, m, lrow, lcol, val, opt, perm1, pos1, s, N, &H, deg));
+        RCK(build_layout(h, 1, h->L[1], n, m, lrow, lcol, val, opt, perm1, pos1, s, N, &H, deg,
+                         h->perm0));
         if (H == 0) return CCDPP_OK;  // built whole
     } else if (forced < 0) {
         return build_layout(h, 1, h->L[1], n, m, lrow, lcol, val, opt, perm1, pos1, s, N, nullptr,
-                            deg);
+                            deg, h->perm0);
     }
     // The entries of the leading H items and of the others, each in input order.
     int32_t *ih, *il;

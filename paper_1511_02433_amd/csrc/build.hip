@@ -135,6 +135,43 @@ __global__ void __launch_bounds__(kT) k_seg_histogram(const int32_t* __restrict_
     }
 }
 
+// The same with the entries taken in an order that keeps most tiles together (the
+// user-major copy's, for the item-major one): a workgroup counts a run of one tile in LDS,
+// one word per row, and adds its counts at the run's end; an entry of another tile
+// inside what the search took for a run is counted in global memory, so the counts
+// are right in any order.  (10M ratings, 6 tiles of 10,681 rows: 0.08 ms; 100M, 36 of
+// 17,770: 0.82 ms; one global atomic per entry took 1.7 and 6.0 ms.)
+__global__ void __launch_bounds__(1024) k_seg_histogram_runs(
+    const int32_t* __restrict__ order, const int32_t* __restrict__ lrow,
+    const int32_t* __restrict__ lcol, int64_t nnz, int32_t rows, int32_t T, int32_t* count) {
+    extern __shared__ int32_t lds_count[];
+    int64_t lo, hi;
+    block_range(nnz, &lo, &hi);
+    while (lo < hi) {
+        const int32_t p = lcol[order[lo]] / T;
+        int64_t a = lo + 1, b = hi;  // the run's end: the first entry of another tile
+        while (a < b) {
+            const int64_t mid = (a + b) >> 1;
+            if (lcol[order[mid]] / T == p) a = mid + 1; else b = mid;
+        }
+        for (int32_t r = threadIdx.x; r < rows; r += blockDim.x) lds_count[r] = 0;
+        __syncthreads();
+        for (int64_t e = lo + threadIdx.x; e < a; e += blockDim.x) {
+            const int32_t t = order[e];
+            const int32_t q = lcol[t] / T, r = lrow[t];
+            if (q == p)
+                atomicAdd(&lds_count[r], 1);
+            else
+                atomicAdd(&count[(int64_t)q * rows + r], 1);
+        }
+        __syncthreads();
+        for (int32_t r = threadIdx.x; r < rows; r += blockDim.x)
+            if (lds_count[r]) atomicAdd(&count[(int64_t)p * rows + r], lds_count[r]);
+        __syncthreads();
+        lo = a;
+    }
+}
+
 // Sort key of an entry: its segment id, then its column inside the tile.
 __global__ void k_seg_keys(const int32_t* __restrict__ lrow, const int32_t* __restrict__ lcol,
                            const int32_t* __restrict__ segid, int64_t nnz, int32_t rows, int32_t T,
@@ -831,8 +868,20 @@ hipError_t launch_map(const int32_t* in, const int32_t* table, int64_t n, int32_
 }
 
 hipError_t launch_seg_histogram(const int32_t* lrow, const int32_t* lcol, int64_t nnz,
-                                int32_t rows, int32_t T, int32_t* count, hipStream_t s) {
+                                int32_t rows, int32_t T, const int32_t* order, int32_t workgroups,
+                                int32_t* count, hipStream_t s) {
     if (nnz == 0) return hipSuccess;
+    if (order && rows <= kHistLdsBins) {
+        const size_t lds = (size_t)rows * 4;
+        hipError_t e = hipFuncSetAttribute((const void*)k_seg_histogram_runs,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        // (runs of at least two entries per word that a workgroup clears and adds)
+        const int64_t g = std::max<int64_t>(1, std::min<int64_t>(workgroups, nnz / (2 * (int64_t)rows + 1)));
+        hipLaunchKernelGGL(k_seg_histogram_runs, dim3((unsigned)g), dim3(1024), lds, s, order, lrow, lcol,
+                           nnz, rows, T, count);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_seg_histogram, grid_for(nnz, 8192), dim3(kT), 0, s, lrow, lcol, nnz, rows,
                        T, count);
     return hipGetLastError();

@@ -431,8 +431,11 @@ hipError_t launch_histogram(const int32_t* key, int64_t n, int32_t bins, int32_t
                            int32_t workgroups, hipStream_t s);
 hipError_t launch_map(const int32_t* in, const int32_t* table, int64_t n, int32_t* out,
                       hipStream_t s);
+// count[(lcol[e] / T) * rows + lrow[e]] += 1 for every e < nnz; order (may be null): the
+// entries in an order whose tiles come in runs.
 hipError_t launch_seg_histogram(const int32_t* lrow, const int32_t* lcol, int64_t nnz,
-                                int32_t rows, int32_t T, int32_t* count, hipStream_t s);
+                                int32_t rows, int32_t T, const int32_t* order, int32_t workgroups,
+                                int32_t* count, hipStream_t s);
 hipError_t launch_seg_keys(const int32_t* lrow, const int32_t* lcol, const int32_t* segid,
                            int64_t nnz, int32_t rows, int32_t T, int cbits, uint64_t* keys,
                            int32_t* ids, hipStream_t s);

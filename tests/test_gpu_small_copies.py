@@ -107,3 +107,31 @@ def test_short_segments_are_tiled_where_gathers_cost_more(per_row, tiled, precis
         assert g.check_consistency() == 0
         g.close()
         o.close()
+
+
+@pytest.mark.parametrize("n", [32_768, 32_769])
+def test_tile_counts_at_the_lds_limit(n):
+    # The item-major copy's (tile, row) counts are taken in LDS for up to 32,768 rows; the
+    # user-major copy's tiles put their order through several resets.
+    m, k, lam = 3_000, 2, 0.5
+    rng = np.random.default_rng(n)
+    key = np.unique(rng.integers(0, m, 80_000) * n + rng.integers(0, n, 80_000))
+    row, col = (key // n).astype(np.int32), (key % n).astype(np.int32)
+    row[:3], col[:3] = [m - 1, m - 1, 0], [n - 1, 0, n - 1]
+    _, first = np.unique(row.astype(np.int64) * n + col, return_index=True)
+    row, col = row[first], col[first]
+    val = rng.standard_normal(row.size).astype(np.float32)
+    H0 = (rng.standard_normal((n, k)) * 0.1).astype(np.float32)
+    for tile in ((0, 0), (9_024, 64)):
+        print(f"case: n {n} tile widths {tile}", flush=True)
+        g = CCDPP(m, n, k, lam, row, col, val, opts=make_options(gather_mode=(2, 2), tile_width=tile))
+        g.set_factors(None, H0)
+        o = Oracle(m, n, k, lam, row, col, val, H0)
+        g.run(1, 2)
+        o.run(1, 2)
+        W, H = g.factors()
+        Wo, Ho = o.factors()
+        assert colscaled_max_rel_err(W, Wo) <= 1e-3 and colscaled_max_rel_err(H, Ho) <= 1e-3
+        assert g.check_consistency() == 0
+        g.close()
+        o.close()
