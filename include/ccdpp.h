@@ -92,7 +92,7 @@ int ccdpp_create(int64_t m, int64_t n, int32_t k, double lambda, int64_t nnz,
  *                 the leading tile_width columns, the most frequent ones,
  *                 and gather the others from global memory (automatic
  *                 mode takes it when tiles would hold too few entries per
- *                 row)
+ *                 row to be worth the gathers they save)
  *   tile_width  : columns per LDS tile (0: as wide as LDS allows); at most
  *                 (163840 - 512) / (b * v) - 64, rounded down to a multiple of 64,
  *                 where b is the bytes per value (4, or 8 with precision 1)
@@ -103,7 +103,8 @@ int ccdpp_create(int64_t m, int64_t n, int32_t k, double lambda, int64_t nnz,
  *                 pass stages as much of it as its vectors leave room for
  *   workgroups  : persistent workgroups per pass (0: two per compute unit,
  *                 one for copies of fewer than about 33.5M entries, four for
- *                 copies of more than about 252M, padding included)
+ *                 copies of more than about 252M, padding included, and at
+ *                 most one per 512 entries)
  *   seg_weight  : work of one row segment, in entries, when the entries are
  *                 shared out among workgroups and waves (0: the default, 4;
  *                 -1: shares by entries alone)

@@ -978,8 +978,8 @@ int spread_factors(ccdpp* h) {
 }
 
 // The cache policy of each copy's residual stream.  Measured on MI355X:
-// - when both streams fit in the memory-side cache (10M ratings: 123 MB), cached
-//   loads and stores keep them there between passes: 7% less time per outer
+// - when both streams fit in the memory-side cache, or nearly (10M ratings: 123 MB),
+//   cached loads and stores keep them there between passes: 7% less time per outer
 //   iteration than streaming (kCachedStreamBytes); so too for hot copies (6M ratings
 //   over 300,007 x 150,001: 33.3 -> 27.8 us per pass) and for double ones;
 // - when they do not (100M ratings: 1.23 GB), cached accesses are 13% slower, but

@@ -32,18 +32,19 @@ namespace ccdk {
 // relabelled by decreasing length, so the empty ones come last) and the pass
 // writes the coordinate directly; with P > 1 every segment yields a partial
 // (numerator, denominator) and a combine kernel adds a row's partials in tile
-// order.  A layout whose tiles would hold too few entries per segment keeps
+// order.  A layout whose segments would cost more than the gathers they save keeps
 // P == 1 and becomes a hot layout (below); a forced "global" layout gathers
 // everything from global memory.  The item-major copy may instead be split in
 // two layouts over its rows: the longest rows tiled, the others hot, their
 // values in one array (api.hip).
 //
 // Persistent workgroups of kWG threads each own an equal, contiguous share of
-// the layout's (tile-major) entries (two shares per CU when every wave still
-// gets several windows, else one).  With P == 1 (float) the share bounds sit on
-// row starts when that keeps the shares within an eighth of equal; rows are then
-// cut only between the waves of one workgroup, which finishes them at the end of
-// the pass from partials its waves leave in LDS, and no combine kernel runs.  A share that crosses tile boundaries is
+// the layout's (tile-major) entries (one to four shares per CU by the windows per
+// wave; the smallest copies one share per window).  With P == 1 (float) the share
+// bounds sit on row starts when none has to move by more than an eighth of a share
+// (small copies: half a share); rows are then cut only between the waves of one
+// workgroup, which finishes them at the end of the pass from partials its waves
+// leave in LDS, and no combine kernel runs.  A share that crosses tile boundaries is
 // processed as one "piece" per tile, restaging LDS between pieces; inside a
 // piece each of the 16 waves owns one of 16 equal contiguous chunks.  Chunk
 // bounds do not follow segment bounds, so every wave streams the same number
@@ -99,7 +100,7 @@ constexpr int kLdsBytes = 160 * 1024;     // LDS per workgroup
 constexpr int kCutSlotBytes = 2 * 16 * 16;  // per-wave head and tail partials (P == 1)
 constexpr int kLdsVecBytes = kLdsBytes - kCutSlotBytes;  // the rest holds staged vectors
 constexpr int kCutMaxSlots = 12;          // slots of a row a workgroup finishes itself
-constexpr int kMinTiledSeg = 32;          // mean entries per segment for tiling to pay
+constexpr int kMinTiledSeg = 32;          // mean entries per segment from which tiling always pays
 constexpr int kSegWeight = 4;             // default work of one segment, in entries
 constexpr int64_t kSnapEntries = 4096;    // how far a small copy's share bound may move to a row start
 constexpr int64_t kSmallCopy = 256 * kWaves * kWin;  // one window per wave of the chip (2.1M entries)
