@@ -362,7 +362,7 @@ private:
     bool ready();
     // f(worker, slot, offset, length) for every chunk of a worker, workers side by side.
     template <class F>
-    hipError_t run(size_t bytes, int device, F&& f);
+    hipError_t run(size_t bytes, int device, hipStream_t s, F&& f);
     struct Slot {
         char* p = nullptr;
         hipEvent_t ev = nullptr;

@@ -91,9 +91,10 @@ void Stager::release() {
 }
 
 template <class F>
-hipError_t Stager::run(size_t bytes, int device, F&& f) {
+hipError_t Stager::run(size_t bytes, int device, hipStream_t s, F&& f) {
     const int64_t chunks = (int64_t)((bytes + kChunk - 1) / kChunk);
-    const int used = (int)std::min<int64_t>(workers_, chunks);
+    // hipStreamPerThread names another stream in each thread: the calling thread does it all.
+    const int used = s == hipStreamPerThread ? 1 : (int)std::min<int64_t>(workers_, chunks);
     std::vector<hipError_t> err((size_t)used, hipSuccess);
     parallel_ranges(used, used, [&](int, int64_t lo, int64_t hi) {
         int before = 0;  // the current device is a thread's own
@@ -114,7 +115,7 @@ hipError_t Stager::to_device(void* dst, const void* src, size_t bytes, int devic
         hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
         return e == hipSuccess ? hipStreamSynchronize(s) : e;
     }
-    return run(bytes, device, [&](int w, int used, int64_t chunks) -> hipError_t {
+    return run(bytes, device, s, [&](int w, int used, int64_t chunks) -> hipError_t {
         int i = 0;
         for (int64_t c = w; c < chunks; c += used, i ^= 1) {
             Slot& sl = slot_[w][i];
@@ -137,7 +138,7 @@ hipError_t Stager::to_host(void* dst, const void* src, size_t bytes, int device,
         hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
         return e == hipSuccess ? hipStreamSynchronize(s) : e;
     }
-    return run(bytes, device, [&](int w, int used, int64_t chunks) -> hipError_t {
+    return run(bytes, device, s, [&](int w, int used, int64_t chunks) -> hipError_t {
         auto request = [&](int64_t c, Slot& sl) -> hipError_t {
             hipError_t e = idle(sl);
             if (e != hipSuccess) return e;

@@ -34,6 +34,22 @@ def test_factors_round_trip(values):
     g.close()
 
 
+def test_factors_round_trip_on_the_per_thread_stream():
+    # hipStreamPerThread (2) is another stream in each thread, and so in a copy's workers.
+    m, n, k = 14 * (4 << 20) // 4 + 17, 40, 1
+    rng = np.random.default_rng(3)
+    row, col = rng.permutation(m)[:500].astype(np.int32), (np.arange(500) % n).astype(np.int32)
+    g = CCDPP(m, n, k, 0.1, row, col, rng.standard_normal(500).astype(np.float32))
+    g.set_stream(2)
+    for _ in range(3):
+        W = rng.standard_normal((m, k)).astype(np.float32)
+        H = rng.standard_normal((n, k)).astype(np.float32)
+        g.set_factors(W, H)
+        W2, H2 = g.factors()
+        assert np.array_equal(W, W2) and np.array_equal(H, H2)
+    g.close()
+
+
 @pytest.mark.parametrize("entries", [50, 24_576, 24_577, 400_000])
 def test_bad_held_out_triplets_are_named(entries):
     m, n, k = 700, 300, 3
