@@ -3,8 +3,9 @@
 // and the pool that a handle's device memory comes from.
 #include <algorithm>
 #include <cstring>
+#include <exception>
 #include <iterator>
-#include <system_error>
+#include <new>
 #include <thread>
 #include <vector>
 
@@ -27,8 +28,8 @@ void parallel_ranges(int64_t n, int workers, const std::function<void(int, int64
         const int64_t lo = std::min(n, w * per), hi = std::min(n, lo + per);
         try {
             pool.emplace_back(f, w, lo, hi);
-        } catch (const std::system_error&) {
-            break;  // no more threads: the calling thread does the rest
+        } catch (const std::exception&) {
+            break;  // no more threads, or no memory for one: the calling thread does the rest
         }
     }
     f(w, std::min(n, w * per), n);
@@ -95,14 +96,19 @@ hipError_t Stager::run(size_t bytes, int device, hipStream_t s, F&& f) {
     const int64_t chunks = (int64_t)((bytes + kChunk - 1) / kChunk);
     // hipStreamPerThread names another stream in each thread: the calling thread does it all.
     const int used = s == hipStreamPerThread ? 1 : (int)std::min<int64_t>(workers_, chunks);
-    std::vector<hipError_t> err((size_t)used, hipSuccess);
-    parallel_ranges(used, used, [&](int, int64_t lo, int64_t hi) {
+    hipError_t err[kCopyWorkers] = {};  // hipSuccess
+    auto work = [&](int, int64_t lo, int64_t hi) {
         int before = 0;  // the current device is a thread's own
         const bool moved = hipGetDevice(&before) == hipSuccess && before != device &&
                            hipSetDevice(device) == hipSuccess;
-        for (int64_t w = lo; w < hi; ++w) err[(size_t)w] = f((int)w, used, chunks);
+        for (int64_t w = lo; w < hi; ++w) err[w] = f((int)w, used, chunks);
         if (moved) (void)hipSetDevice(before);
-    });
+    };
+    try {
+        parallel_ranges(used, used, work);
+    } catch (const std::bad_alloc&) {  // thrown before any worker runs
+        return hipErrorOutOfMemory;
+    }
     for (hipError_t e : err)
         if (e != hipSuccess) return e;
     return hipSuccess;
@@ -173,10 +179,18 @@ hipError_t DevicePool::take(void** p, size_t bytes) {
             for (auto it = sl.free.begin(); it != sl.free.end(); ++it) {
                 if (it->second < len) continue;
                 const size_t off = it->first, rest = it->second - len;
-                sl.free.erase(it);
-                if (rest) sl.free.emplace(off + len, rest);
+                try {
+                    blocks_.emplace(sl.base + off, Block{i, off, len});
+                } catch (const std::bad_alloc&) {  // host memory; nothing has changed
+                    return hipErrorOutOfMemory;
+                }
+                auto node = sl.free.extract(it);  // (its node is used again: no allocation)
+                if (rest) {
+                    node.key() = off + len;
+                    node.mapped() = rest;
+                    sl.free.insert(std::move(node));
+                }
                 *p = sl.base + off;
-                blocks_.emplace(*p, Block{i, off, len});
                 return hipSuccess;
             }
         }
@@ -198,17 +212,18 @@ hipError_t DevicePool::take(void** p, size_t bytes) {
             (void)hipGetLastError();
             return e;
         }
-        Slab sl;
-        sl.base = static_cast<char*>(base);
-        sl.size = size;
-        sl.free.emplace(0, size);
+        try {
+            size_t at = 0;
+            while (at < slabs_.size() && slabs_[at].base) ++at;
+            if (at == slabs_.size()) slabs_.emplace_back();
+            slabs_[at].free.emplace(0, size);
+            slabs_[at].base = static_cast<char*>(base);
+            slabs_[at].size = size;
+        } catch (const std::bad_alloc&) {
+            (void)hipFree(base);
+            return hipErrorOutOfMemory;
+        }
         held_ += size;
-        size_t at = 0;
-        while (at < slabs_.size() && slabs_[at].base) ++at;
-        if (at == slabs_.size())
-            slabs_.push_back(std::move(sl));
-        else
-            slabs_[at] = std::move(sl);
     }
 }
 
@@ -231,7 +246,11 @@ void DevicePool::give(void* p) {
             return;
         }
     }
-    fr.emplace(off, len);
+    try {
+        fr.emplace(off, len);
+    } catch (const std::bad_alloc&) {
+        // Stays taken until release().
+    }
 }
 
 void DevicePool::trim(size_t keep) {
