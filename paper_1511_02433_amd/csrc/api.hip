@@ -622,8 +622,13 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
     // Otherwise the shares stay balanced and the combine kernel finishes every cut row.
     // kSnapEntries from both bounds make one more window per wave, about 1 us; the
     // combine costs 3-5 us per pass (a million entries: 9.1 us per pass with it, 6.8
-    // without).  Where a bound would have to move further, half as many workgroups may
-    // still do (their shares are longer than more of the rows).
+    // without).  Where a bound would have to move further, a small copy's workgroups are
+    // halved until their shares are long enough against the rows around the bounds, down
+    // to shares of a window per wave (fewer leave compute units idle for longer than the
+    // combine takes); only then is the combine kept, with the full number again.  (60,000
+    // entries in 40 rows of 1,500, mean of both copies' passes: 3.6 us with 30 workgroups,
+    // 4.0 with 16, 4.6 with 64 or 128 and the combine; 172,000 in power-law rows of up to
+    // 2,404: 4.8 with 64, 5.9 with 128 and the combine.)
     std::vector<int64_t> snap((size_t)G + 1, -1);
     bool snapped = false;
     if (P == 1 && S_work > 0 && !h->dbl) {  // (one workgroup: nothing to move)
@@ -643,10 +648,12 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
             return true;
         };
         snapped = try_snap();
-        if (!snapped && !forced_G && G > 1 && NP <= kSmallCopy) {
-            const int64_t full = G;
-            G = (G + 1) / 2;
-            snapped = try_snap();
+        if (!snapped && !forced_G && NP <= kSmallCopy) {
+            const int64_t full = G, least = (NP + kWaves * kWin - 1) / (kWaves * kWin);
+            while (!snapped && G > least) {
+                G = std::max(least, (G + 1) / 2);
+                snapped = try_snap();
+            }
             if (!snapped) G = full;
         }
         if (snapped) {

@@ -1,6 +1,6 @@
 """The shares of small copies against the oracle: a workgroup per window, share bounds
-moved to row starts (up to half a share), half as many workgroups where a bound would
-have to move further, and the combine kernel where neither will do.
+moved to row starts (up to half a share), fewer workgroups (down to a window per wave)
+where a bound would have to move further, and the combine kernel where neither will do.
 
 Tolerance: float sums of up to 512 entries and one rounding per coordinate, over two
 features and two inner iterations: 1e-3 of the largest coordinate of a feature, as for
@@ -135,3 +135,55 @@ def test_tile_counts_at_the_lds_limit(n):
         assert g.check_consistency() == 0
         g.close()
         o.close()
+
+
+def _one_share_per_8192_snaps(lens):
+    """Whether shares of 8,192 entries (a window per wave) can start on rows with no bound
+    moved by more than an eighth of a share: the work of a range is its entries plus 4
+    per row, rows start at multiples of 8."""
+    start = np.concatenate([[0], np.cumsum((np.sort(lens)[::-1] + 7) // 8 * 8)])
+    start, npad = start[:-1], -(-int(start[-1]) // 512) * 512
+    work = start + 4 * (np.arange(start.size) + 1)
+    total, shares = npad + 4 * start.size, -(-npad // 8192)
+    for g in range(1, shares):
+        t = total // shares * g + total % shares * g // shares
+        s = int(np.searchsorted(work, t, side="right")) - 1
+        near = [abs(int(work[x]) - t) for x in (s, s + 1) if 0 <= x < start.size]
+        if min(near) > total // shares // 8:
+            return False
+    return True
+
+
+def _long_rows(name):
+    if name == "equal":
+        return [1_500] * 40
+    if name == "one_longer":
+        return [3_200] + [449] * 200
+    seed = int(name.rsplit("_", 1)[1])
+    rng = np.random.default_rng(seed)
+    nnz, rows = int(np.exp(rng.uniform(np.log(5e4), np.log(3e5)))), int(rng.integers(300, 6_000))
+    w = (np.arange(rows) + rows / 200) ** -rng.choice([0.9, 1.001, 1.2])
+    return np.clip(w / w.sum() * nnz, 1, 4_600).astype(int).tolist()
+
+
+@pytest.mark.parametrize("name", ["equal", "one_longer"] + [f"power_law_{s}" for s in range(24)])
+def test_long_rows_keep_the_finish_in_the_pass(name):
+    # Where workgroups of one window each cannot start their shares on rows, fewer can: as
+    # long as shares of a window per wave do, no combine runs.
+    lens = _long_rows(name)
+    m, n, k, lam = len(lens), 4_700, 2, 0.3
+    row, col, val, H0 = synth.lengths_problem(lens, n, k, seed=78)
+    g = CCDPP(m, n, k, lam, row, col, val)
+    info = g.info()
+    snaps = _one_share_per_8192_snaps(lens)
+    print(f"case {name}: nnz {row.size} rows {m} longest {max(lens)} snaps {snaps} workgroups "
+          f"{info['u_workgroups']} combined {info['u_rows_combined']}", flush=True)
+    assert info["u_rows_combined"] == 0 or not snaps
+    g.set_factors(np.zeros((m, k), np.float32), H0)
+    o = Oracle(m, n, k, lam, row, col, val, H0)
+    g.run(1, 2)
+    o.run(1, 2)
+    for x, y in zip(g.factors(), o.factors()):
+        assert colscaled_max_rel_err(x, y) <= 1e-3
+    g.close()
+    o.close()
