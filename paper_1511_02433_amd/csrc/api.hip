@@ -1170,7 +1170,7 @@ int create_device(ccdpp* h, const int32_t* row, const int32_t* col, const float*
     // row, the factors and the segment lists.  What goes past that comes in smaller pieces.
     {
         const size_t vb = h->dbl ? 8 : 4, mn = (size_t)(m + n);
-        h->kept.expect((size_t)N * (17 + 3 * vb) + (size_t)N / 16 * vb + mn * (32 + (h->k + 1) * vb));
+        h->kept.expect((size_t)N * (17 + 3 * vb) + (size_t)N / 16 * vb + mn * (32 + ((size_t)h->k + 1) * vb));
         h->temp.expect((size_t)N * 60 + mn * 16);
         h->temp_keep = std::max<size_t>(size_t(16) << 20, mn * h->k * (vb + 8));
     }
@@ -1615,10 +1615,10 @@ int launch_test_err_any(ccdpp* h, const int32_t* dr, const int32_t* dc, const fl
         if (rows && (rows->w || rows->h)) {
             const int32_t pitch = ccdk::row_pitch(h->k);
             if (rows->w)
-                HIPCK(h, (ccdk::launch_factor_out<V, V>(as<V>(h->W), nullptr, h->m, h->k, pitch,
+                HIPCK(h, (ccdk::launch_factor_out<V, V>(as<V>(h->W), nullptr, nullptr, h->m, h->k, pitch,
                                                         as<V>(rows->w), h->stream)));
             if (rows->h)
-                HIPCK(h, (ccdk::launch_factor_out<V, V>(as<V>(h->H), nullptr, h->n, h->k, pitch,
+                HIPCK(h, (ccdk::launch_factor_out<V, V>(as<V>(h->H), nullptr, nullptr, h->n, h->k, pitch,
                                                         as<V>(rows->h), h->stream)));
             HIPCK(h, ccdk::launch_test_err_rows<V>(dr, dc, dv, nnz, h->rold2new, h->cold2new,
                                                    as<V>(h->W), as<V>(h->H), as<V>(rows->w),
@@ -1793,8 +1793,8 @@ int get_factors_impl(ccdpp* h, S* W, S* H) {
     if (H) HIPCK(h, talloc(h, th, &dH, h->n * h->k));
     RCK(with_value_type(h, [&](auto z) -> int {
         using V = decltype(z);
-        if (W) HIPCK(h, (ccdk::launch_factor_out<V, S>(as<V>(h->W), h->rnew2old, h->m, h->k, h->k, dW, s)));
-        if (H) HIPCK(h, (ccdk::launch_factor_out<V, S>(as<V>(h->H), h->cnew2old, h->n, h->k, h->k, dH, s)));
+        if (W) HIPCK(h, (ccdk::launch_factor_out<V, S>(as<V>(h->W), h->rnew2old, h->rold2new, h->m, h->k, h->k, dW, s)));
+        if (H) HIPCK(h, (ccdk::launch_factor_out<V, S>(as<V>(h->H), h->cnew2old, h->cold2new, h->n, h->k, h->k, dH, s)));
         return CCDPP_OK;
     }));
     if (W) HIPCK(h, h->stage.to_host(W, dW, h->m * h->k * sizeof(S), h->device, s));
@@ -1846,7 +1846,7 @@ int set_factors_impl(ccdpp* h, const S* W, const S* H) {
         if (W) HIPCK(h, (ccdk::launch_scatter_factor_in<S, V>(dW, h->rnew2old, h->m, h->k, as<V>(h->W), s)));
         if (H) HIPCK(h, (ccdk::launch_scatter_factor_in<S, V>(dH, h->cnew2old, h->n, h->k, as<V>(h->H), s)));
         RCK(spread_factors(h));
-        HIPCK(h, (ccdk::launch_factor_out<V, V>(as<V>(h->H), nullptr, h->n, h->k, pitch, as<V>(ht), s)));
+        HIPCK(h, (ccdk::launch_factor_out<V, V>(as<V>(h->H), nullptr, nullptr, h->n, h->k, pitch, as<V>(ht), s)));
         HIPCK(h, ccdk::launch_rebuild_residual<V>(h->L[0], as<V>(h->A), as<V>(h->W), as<V>(ht), h->m,
                                                   h->k, pitch, s));
         HIPCK(h, (ccdk::launch_copy_mapped<V, V>(as<V>(h->L[0].val), h->pos0, as<V>(h->L[1].val),

@@ -253,30 +253,62 @@ __global__ void k_fill(V* __restrict__ dst, V value, int64_t n) {
         dst[i] = value;
 }
 
-// Tiles of kFR rows by kFT columns of a factor matrix, turned in LDS between the
+// Tiles of kFR rows by up to kFT columns of a factor matrix, turned in LDS between the
 // column-major order over relabelled ids (rows contiguous) and a row-major one (columns
 // contiguous), so that both sides are read and written in whole lines: bound by
-// the two streams.  (m = 480,189, k = 40, float: in 351 -> 63 us, out 143 -> 59 us.)
-constexpr int kFR = 64, kFT = 32;
+// the two streams.  `lanes` (a power of two, at least the tile's columns) threads
+// take a row's values together, so that no thread divides.  A workgroup takes the tiles of
+// its rows in steps of gridDim.y: all of them, a row's lines being shared by its tiles, or,
+// where rows alone make too few workgroups (turn_grid), a share.
+constexpr int kFR = 64, kFT = 32, kFE = kFR * kFT / kT;  // kFE values per thread, requested together
+
+// Turns of few values go value by value, in the order of what they write (32-bit
+// positions): one value's latency, where a tile adds LDS and a barrier (kTurnSmall).
+template <class S, class V>
+__global__ void k_factor_in_small(const S* __restrict__ rowmajor, const int32_t* __restrict__ new2old,
+                                  uint32_t rows, uint32_t k, V* __restrict__ colmajor) {
+    const uint32_t e = blockIdx.x * kT + threadIdx.x;
+    if (e >= rows * k) return;
+    const uint32_t t = e / rows;
+    colmajor[e] = (V)rowmajor[(uint32_t)new2old[e - t * rows] * k + t];
+}
+template <class V, class S>
+__global__ void k_factor_out_small(const V* __restrict__ colmajor, const int32_t* __restrict__ old2new,
+                                   uint32_t rows, uint32_t k, uint32_t pitch, S* __restrict__ rowmajor) {
+    const uint32_t e = blockIdx.x * kT + threadIdx.x;
+    if (e >= rows * pitch) return;
+    const uint32_t i = e / pitch, t = e - i * pitch;
+    rowmajor[e] = t < k ? (S)colmajor[t * rows + (old2new ? (uint32_t)old2new[i] : i)] : S(0);
+}
 
 // colmajor[t * rows + i'] = rowmajor[new2old[i'] * k + t]
 template <class S, class V>
 __global__ __launch_bounds__(kT) void k_factor_in(const S* __restrict__ rowmajor,
                                                   const int32_t* __restrict__ new2old, int64_t rows,
-                                                  int32_t k, V* __restrict__ colmajor) {
+                                                  int64_t k, int shift, V* __restrict__ colmajor) {
     __shared__ V tile[kFT][kFR + 1];
     const int64_t r0 = (int64_t)blockIdx.x * kFR;
     const int nr = (int)min((int64_t)kFR, rows - r0);
-    for (int t0 = 0; t0 < k; t0 += kFT) {
-        const int nt = min(kFT, k - t0);
-        for (int e = threadIdx.x; e < nr * nt; e += kT) {
-            const int r = e / nt, t = e - r * nt;
-            tile[t][r] = (V)rowmajor[(int64_t)new2old[r0 + r] * k + t0 + t];
+    const int lanes = 1 << shift, last = nr * lanes - 1;
+    for (int64_t t0 = (int64_t)blockIdx.y * kFT; t0 < k; t0 += (int64_t)gridDim.y * kFT) {
+        const int nt = (int)min((int64_t)kFT, k - t0);
+        V v[kFE];
+#pragma unroll
+        for (int j = 0; j < kFE; ++j) {
+            if (j * kT > last) break;
+            const int e = min(j * kT + (int)threadIdx.x, last);
+            v[j] = (V)rowmajor[(int64_t)new2old[r0 + (e >> shift)] * k + t0 + min(e & (lanes - 1), nt - 1)];
+        }
+#pragma unroll
+        for (int j = 0; j < kFE; ++j) {
+            if (j * kT > last) break;
+            const int e = j * kT + threadIdx.x, t = e & (lanes - 1);
+            if (e <= last && t < nt) tile[t][e >> shift] = v[j];
         }
         __syncthreads();
         for (int e = threadIdx.x; e < nt * kFR; e += kT) {
             const int t = e / kFR, r = e % kFR;
-            if (r < nr) colmajor[(int64_t)(t0 + t) * rows + r0 + r] = tile[t][r];
+            if (r < nr) colmajor[(t0 + t) * rows + r0 + r] = tile[t][r];
         }
         __syncthreads();
     }
@@ -287,25 +319,52 @@ __global__ __launch_bounds__(kT) void k_factor_in(const S* __restrict__ rowmajor
 template <class V, class S>
 __global__ __launch_bounds__(kT) void k_factor_out(const V* __restrict__ colmajor,
                                                    const int32_t* __restrict__ new2old, int64_t rows,
-                                                   int32_t k, int32_t pitch, S* __restrict__ rowmajor) {
+                                                   int64_t k, int64_t pitch, int shift,
+                                                   S* __restrict__ rowmajor) {
     __shared__ V tile[kFT][kFR + 1];
     const int64_t r0 = (int64_t)blockIdx.x * kFR;
     const int nr = (int)min((int64_t)kFR, rows - r0);
-    for (int t0 = 0; t0 < pitch; t0 += kFT) {
-        const int nt = min(kFT, pitch - t0);
-        for (int e = threadIdx.x; e < nt * kFR; e += kT) {
-            const int t = e / kFR, r = e % kFR;
-            if (r < nr)
-                tile[t][r] = t0 + t < k ? colmajor[(int64_t)(t0 + t) * rows + r0 + r] : V(0);
+    const int lanes = 1 << shift, last = nr * lanes - 1;
+    for (int64_t t0 = (int64_t)blockIdx.y * kFT; t0 < pitch; t0 += (int64_t)gridDim.y * kFT) {
+        const int nt = (int)min((int64_t)kFT, pitch - t0);
+        V v[kFE];
+#pragma unroll
+        for (int j = 0; j < kFE; ++j) {
+            if (j * kT >= nt * kFR) break;
+            const int e = j * kT + threadIdx.x, t = min(e / kFR, nt - 1), r = min(e % kFR, nr - 1);
+            v[j] = t0 + t < k ? colmajor[(t0 + t) * rows + r0 + r] : V(0);
+        }
+#pragma unroll
+        for (int j = 0; j < kFE; ++j) {
+            if (j * kT >= nt * kFR) break;
+            const int e = j * kT + threadIdx.x;
+            if (e < nt * kFR) tile[e / kFR][e % kFR] = v[j];
         }
         __syncthreads();
-        for (int e = threadIdx.x; e < nr * nt; e += kT) {
-            const int r = e / nt, t = e - r * nt;
+#pragma unroll 1
+        for (int e = threadIdx.x; e <= last; e += kT) {
+            const int r = e >> shift, t = e & (lanes - 1);
             const int64_t i = new2old ? new2old[r0 + r] : r0 + r;
-            rowmajor[i * pitch + t0 + t] = (S)tile[t][r];
+            if (t < nt) rowmajor[i * pitch + t0 + t] = (S)tile[t][r];
         }
         __syncthreads();
     }
+}
+
+// Workgroups of a turn of `cols` columns, and the shift of `lanes`.  Rows alone fill the
+// chip from kTurnGroups workgroups on.  (64 x 65,536, one workgroup before: out 17.7 ms a call,
+// now 1.1; 20,000 x 64, 313 before: in 13.3 us, now 6.6.)
+constexpr int64_t kTurnGroups = 1024;
+// Up to this many values a turn goes value by value (us, values against tiles: 2,000 x 20
+// in 2.7 against 5.0, out 2.8 against 5.2; 6,041 x 40 in 4.6 against 7.8, out 3.9 against 8.0;
+// 20,000 x 20 equal); rows of up to four values, whole in one sector, into columns always do
+// (480,189 x 4: 9.2 against 10.4).
+constexpr int64_t kTurnSmall = 1 << 18, kTurnNarrow = 1 << 28;
+inline dim3 turn_grid(int64_t rows, int64_t cols, int* shift) {
+    const int64_t gx = (rows + kFR - 1) / kFR, tiles = (cols + kFT - 1) / kFT;
+    const int64_t gy = std::min(std::min<int64_t>(tiles, 65535), (kTurnGroups + gx - 1) / gx);
+    for (*shift = 0; (1 << *shift) < std::min<int64_t>(cols, kFT);) ++*shift;
+    return dim3((unsigned)gx, (unsigned)std::max<int64_t>(1, gy));
 }
 
 // Four values of a row of a row-major factor copy whose pitch is a multiple of 4.
@@ -967,16 +1026,30 @@ hipError_t launch_fill(V* dst, V value, int64_t n, hipStream_t s) {
 template <class S, class V>
 hipError_t launch_scatter_factor_in(const S* rowmajor, const int32_t* new2old, int64_t rows,
                                     int32_t k, V* colmajor, hipStream_t s) {
-    hipLaunchKernelGGL((k_factor_in<S, V>), dim3((unsigned)((rows + kFR - 1) / kFR)), dim3(kT), 0, s,
-                       rowmajor, new2old, rows, k, colmajor);
+    if (rows * k <= (k <= 4 ? kTurnNarrow : kTurnSmall)) {
+        hipLaunchKernelGGL((k_factor_in_small<S, V>), grid_for(rows * k), dim3(kT), 0, s, rowmajor,
+                           new2old, (uint32_t)rows, (uint32_t)k, colmajor);
+        return hipGetLastError();
+    }
+    int shift;
+    const dim3 grid = turn_grid(rows, k, &shift);
+    hipLaunchKernelGGL((k_factor_in<S, V>), grid, dim3(kT), 0, s, rowmajor, new2old, rows, (int64_t)k,
+                       shift, colmajor);
     return hipGetLastError();
 }
 
 template <class V, class S>
-hipError_t launch_factor_out(const V* colmajor, const int32_t* new2old, int64_t rows, int32_t k,
-                             int32_t pitch, S* rowmajor, hipStream_t s) {
-    hipLaunchKernelGGL((k_factor_out<V, S>), dim3((unsigned)((rows + kFR - 1) / kFR)), dim3(kT), 0, s,
-                       colmajor, new2old, rows, k, pitch, rowmajor);
+hipError_t launch_factor_out(const V* colmajor, const int32_t* new2old, const int32_t* old2new,
+                             int64_t rows, int32_t k, int64_t pitch, S* rowmajor, hipStream_t s) {
+    if (rows * pitch <= kTurnSmall) {
+        hipLaunchKernelGGL((k_factor_out_small<V, S>), grid_for(rows * pitch), dim3(kT), 0, s, colmajor,
+                           old2new, (uint32_t)rows, (uint32_t)k, (uint32_t)pitch, rowmajor);
+        return hipGetLastError();
+    }
+    int shift;
+    const dim3 grid = turn_grid(rows, pitch, &shift);
+    hipLaunchKernelGGL((k_factor_out<V, S>), grid, dim3(kT), 0, s, colmajor, new2old, rows, (int64_t)k,
+                       pitch, shift, rowmajor);
     return hipGetLastError();
 }
 
@@ -1102,10 +1175,10 @@ hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const fl
                                                            int64_t, int32_t, V*, hipStream_t);  \
     template hipError_t launch_scatter_factor_in<double, V>(const double*, const int32_t*,      \
                                                             int64_t, int32_t, V*, hipStream_t); \
-    template hipError_t launch_factor_out<V, float>(const V*, const int32_t*, int64_t, int32_t, \
-                                                    int32_t, float*, hipStream_t);              \
-    template hipError_t launch_factor_out<V, double>(const V*, const int32_t*, int64_t, int32_t, \
-                                                     int32_t, double*, hipStream_t);            \
+    template hipError_t launch_factor_out<V, float>(const V*, const int32_t*, const int32_t*,   \
+                                                    int64_t, int32_t, int64_t, float*, hipStream_t); \
+    template hipError_t launch_factor_out<V, double>(const V*, const int32_t*, const int32_t*,  \
+                                                     int64_t, int32_t, int64_t, double*, hipStream_t); \
     template hipError_t launch_rebuild_residual<V>(const Layout&, const V*, const V*, const V*, \
                                                    int64_t, int32_t, int32_t, hipStream_t);     \
     template hipError_t launch_test_err_rows<V>(const int32_t*, const int32_t*, const float*,   \

@@ -463,10 +463,10 @@ template <class S, class V>
 hipError_t launch_scatter_factor_in(const S* rowmajor, const int32_t* new2old, int64_t rows,
                                     int32_t k, V* colmajor, hipStream_t s);
 // rowmajor[new2old[i] * pitch + t] = colmajor[t * rows + i] for t < k, zero for k <= t <
-// pitch (new2old null: row i)
+// pitch (both maps, each the other's inverse, or neither: row i)
 template <class V, class S>
-hipError_t launch_factor_out(const V* colmajor, const int32_t* new2old, int64_t rows, int32_t k,
-                             int32_t pitch, S* rowmajor, hipStream_t s);
+hipError_t launch_factor_out(const V* colmajor, const int32_t* new2old, const int32_t* old2new,
+                             int64_t rows, int32_t k, int64_t pitch, S* rowmajor, hipStream_t s);
 // The residual of the user-major copy from the ratings A (in its value slots), W
 // (column-major) and HT (H row-major, rows of `pitch` values, a multiple of 4).
 template <class V>

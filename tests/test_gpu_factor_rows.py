@@ -10,6 +10,7 @@ numpy's float64 value; the RMSE is a float64 sum of at most 20,000 squares: 1e-1
 import numpy as np
 import pytest
 
+import paper_1511_02433_amd.ccdpp as C
 from paper_1511_02433_amd import synth
 from paper_1511_02433_amd.ccdpp import CCDPP, make_options
 
@@ -55,3 +56,41 @@ def test_factors_residual_and_rmse(k, precision):
         ref = np.sqrt(np.mean((a.astype(np.float64) - (Wd[r] * Hd[c]).sum(1)) ** 2))
         assert abs(g.rmse(r, c, a) - ref) <= 1e-12 * ref
     g.close()
+
+
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (1, 64, 2), (63, 65, 31), (64, 1, 33), (65, 63, 65), (200, 250, 500),
+                                   (64, 65, 4_100), (3, 2, 100_003), (6_000, 70, 60), (70_000, 40, 40),
+                                   (70_000, 129, 3)])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_turns_of_few_rows_or_many_features(m, n, k, precision):
+    # Up to 2^18 values, or four to a row, are turned value by value; few rows of more have
+    # their tiles shared out over several workgroups; 70,000 rows and k = 40 fill the chip
+    # alone and a workgroup takes both tiles of its rows.
+    rng = np.random.default_rng(m + k)
+    row = np.arange(m, dtype=np.int32)
+    col = (row % n).astype(np.int32)
+    g = CCDPP(m, n, k, 0.1, row, col, np.ones(m, np.float32), opts=make_options(precision=precision))
+    print(f"case: {m} x {n}, k {k}, precision {precision}", flush=True)
+    W = rng.standard_normal((m, k)).astype(np.float32)
+    H = rng.standard_normal((n, k)).astype(np.float32)
+    g.set_factors(W, H)
+    for x, y in zip((W, H, W, H), g.factors() + g.factors_f64()):
+        assert np.array_equal(x, y)
+    H = H[::-1].copy()
+    g.set_factors(None, H)
+    for x, y in zip((W, H), g.factors()):
+        assert np.array_equal(x, y)
+    g.close()
+
+
+def test_factors_at_the_largest_k():
+    # The features of a turn are counted past 2^31 - 32 without overflow (8.6 GB per factor).
+    k = 2**31 - 1
+    g = CCDPP(1, 1, k, 0.1, np.zeros(0, np.int32), np.zeros(0, np.int32), np.zeros(0, np.float32), seed=3)
+    H = np.empty((1, k), np.float32)
+    print("case: k 2^31 - 1", flush=True)
+    assert C.lib().ccdpp_get_factors(g._h, None, C._p(H)) == 0
+    g.close()
+    for at in (0, k // 2, k - 64):
+        part = H[0, at:at + 64].astype(np.float64)
+        assert np.isfinite(part).all() and 0.04 < part.std() < 0.2  # N(0, 0.01)
