@@ -625,7 +625,9 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
     // without).  Where a bound would have to move further, a small copy's workgroups are
     // halved until their shares are long enough against the rows around the bounds, down
     // to shares of a window per wave (fewer leave compute units idle for longer than the
-    // combine takes); only then is the combine kept, with the full number again.  (60,000
+    // combine takes), whose bounds move by an eighth at most (a further one costs a pass
+    // of so few workgroups a second window); only then is the combine kept, with the full
+    // number again.  (60,000
     // entries in 40 rows of 1,500, mean of both copies' passes: 3.6 us with 30 workgroups,
     // 4.0 with 16, 4.6 with 64 or 128 and the combine; 172,000 in power-law rows of up to
     // 2,404: 4.8 with 64, 5.9 with 128 and the combine.)
@@ -633,9 +635,9 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
     bool snapped = false;
     if (P == 1 && S_work > 0 && !h->dbl) {  // (one workgroup: nothing to move)
         const int64_t wt = work_at(NP);
-        auto try_snap = [&]() {
+        auto try_snap = [&](bool wide) {
             const int64_t share = wt / G;
-            const int64_t most = std::max(share / 8, std::min(share / 2, kSnapEntries));
+            const int64_t most = std::max(share / 8, wide ? std::min(share / 2, kSnapEntries) : 0);
             for (int64_t g = 1; g < G; ++g) {
                 const int64_t t = target(wt, g);
                 const int64_t sg = std::min<int64_t>(seg_of(0, pos_at(t)), S_work - 1);
@@ -647,12 +649,12 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
             }
             return true;
         };
-        snapped = try_snap();
+        snapped = try_snap(true);
         if (!snapped && !forced_G && NP <= kSmallCopy) {
             const int64_t full = G, least = (NP + kWaves * kWin - 1) / (kWaves * kWin);
             while (!snapped && G > least) {
                 G = std::max(least, (G + 1) / 2);
-                snapped = try_snap();
+                snapped = try_snap(G > least);
             }
             if (!snapped) G = full;
         }
