@@ -56,6 +56,10 @@ constexpr int32_t kReduceParts = 1024;
 // ones on the device once they are there (30 us with the wait, 1.4M triplets or 20M
 // factors included, which took a host thread 1 and 6 ms).
 constexpr int64_t kHostCheck = 24576;
+// Entries times features from which rebuilding the residual pays for a row-major H and its
+// turn (us, an entry per thread against turn and rows: 50,000 x 10 7.1 against 9.1, 300,000 x
+// 10 12.1 against 13.3, 300,000 x 20 18.5 against 17.7, 600,000 x 10 35.6 against 26.5).
+constexpr int64_t kRebuildTurn = 4 << 20;
 // A row segment of a tiled layout costs about as much as this many gathers from
 // global memory (its emission, partial and combine against one cache line each).
 constexpr int64_t kSplitSegCost = 2;
@@ -1559,7 +1563,7 @@ struct RowFactors {
     Tmp tw, th;
     char *w = nullptr, *h = nullptr;
     void allocate(ccdpp* p, int64_t nnz) {
-        const int64_t row = (int64_t)ccdk::row_pitch(p->k) * (p->dbl ? 8 : 4);
+        const int64_t row = ccdk::row_pitch(p->k) * (p->dbl ? 8 : 4);
         auto side = [&](Tmp& t, char** c, int64_t rows) {
             if (nnz >= 8 * rows && talloc(p, t, c, rows * row) != hipSuccess) *c = nullptr;
         };
@@ -1615,7 +1619,7 @@ int launch_test_err_any(ccdpp* h, const int32_t* dr, const int32_t* dc, const fl
     return with_value_type(h, [&](auto z) -> int {
         using V = decltype(z);
         if (rows && (rows->w || rows->h)) {
-            const int32_t pitch = ccdk::row_pitch(h->k);
+            const int64_t pitch = ccdk::row_pitch(h->k);
             if (rows->w)
                 HIPCK(h, (ccdk::launch_factor_out<V, V>(as<V>(h->W), nullptr, nullptr, h->m, h->k, pitch,
                                                         as<V>(rows->w), h->stream)));
@@ -1624,7 +1628,7 @@ int launch_test_err_any(ccdpp* h, const int32_t* dr, const int32_t* dc, const fl
                                                         as<V>(rows->h), h->stream)));
             HIPCK(h, ccdk::launch_test_err_rows<V>(dr, dc, dv, nnz, h->rold2new, h->cold2new,
                                                    as<V>(h->W), as<V>(h->H), as<V>(rows->w),
-                                                   as<V>(rows->h), h->m, h->n, h->k, pitch, h->sse_part,
+                                                   as<V>(rows->h), h->m, h->n, h->k, h->sse_part,
                                                    kReduceParts, bad, h->stream));
             return CCDPP_OK;
         }
@@ -1823,12 +1827,14 @@ int set_factors_impl(ccdpp* h, const S* W, const S* H) {
     // Staging buffers first: a failed allocation leaves the factors and the residual
     // as they were.
     S *dW = nullptr, *dH = nullptr;
-    char* ht = nullptr;  // H row-major, for the rebuild
-    const int32_t pitch = ccdk::row_pitch(h->k);
+    char* ht = nullptr;  // H row-major, for the rebuild (without memory the columns serve)
+    const int64_t pitch = ccdk::row_pitch(h->k);
     Tmp tw, th, tht;
     if (W) HIPCK(h, talloc(h, tw, &dW, h->m * h->k));
     if (H) HIPCK(h, talloc(h, th, &dH, h->n * h->k));
-    HIPCK(h, talloc(h, tht, &ht, h->n * pitch * (h->dbl ? 8 : 4)));
+    if (h->nnz * h->k >= kRebuildTurn &&
+        talloc(h, tht, &ht, h->n * pitch * (h->dbl ? 8 : 4)) != hipSuccess)
+        ht = nullptr;
     if (W) HIPCK(h, h->stage.to_device(dW, W, nw * sizeof(S), h->device, s));
     if (H) HIPCK(h, h->stage.to_device(dH, H, nh * sizeof(S), h->device, s));
     if (!host_check) {  // on the device, before anything changes
@@ -1848,9 +1854,11 @@ int set_factors_impl(ccdpp* h, const S* W, const S* H) {
         if (W) HIPCK(h, (ccdk::launch_scatter_factor_in<S, V>(dW, h->rnew2old, h->m, h->k, as<V>(h->W), s)));
         if (H) HIPCK(h, (ccdk::launch_scatter_factor_in<S, V>(dH, h->cnew2old, h->n, h->k, as<V>(h->H), s)));
         RCK(spread_factors(h));
-        HIPCK(h, (ccdk::launch_factor_out<V, V>(as<V>(h->H), nullptr, nullptr, h->n, h->k, pitch, as<V>(ht), s)));
-        HIPCK(h, ccdk::launch_rebuild_residual<V>(h->L[0], as<V>(h->A), as<V>(h->W), as<V>(ht), h->m,
-                                                  h->k, pitch, s));
+        if (ht)
+            HIPCK(h, (ccdk::launch_factor_out<V, V>(as<V>(h->H), nullptr, nullptr, h->n, h->k, pitch,
+                                                    as<V>(ht), s)));
+        HIPCK(h, ccdk::launch_rebuild_residual<V>(h->L[0], h->pos0, as<V>(h->A), as<V>(h->W),
+                                                  as<V>(h->H), as<V>(ht), h->m, h->k, s));
         HIPCK(h, (ccdk::launch_copy_mapped<V, V>(as<V>(h->L[0].val), h->pos0, as<V>(h->L[1].val),
                                                 h->map01, h->nnz, s)));
         HIPCK(h, hipStreamSynchronize(s));

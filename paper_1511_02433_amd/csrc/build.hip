@@ -438,14 +438,66 @@ __device__ __forceinline__ void deal(double* v, bool upper) {
     }
 }
 
+constexpr int64_t kRebuildWaves = 1536;  // six per compute unit
+
+// Index of entry q as the plain format holds it, from a delta-coded window when
+// its bit is set.
+template <class I>
+__device__ __forceinline__ uint32_t index_at(const I* idx, const uint64_t* dmask, uint32_t pad,
+                                             int64_t q) {
+    const int64_t w = q / kWin;
+    if (dmask && ((dmask[w >> 6] >> (w & 63)) & 1u)) {
+        const uint32_t* rec = reinterpret_cast<const uint32_t*>(idx + w * kWin) + 3 * ((q % kWin) / kE);
+        uint32_t c[8];
+        delta_decode(rec[0], rec[1], rec[2], pad, c);
+        return c[q % kE];
+    }
+    return (uint32_t)idx[q];
+}
+
+// k_rebuild below for few entries and features, or without memory for a row-major H: an
+// entry per thread, both factors read from their columns.  Entry e's value slot is pos[e].
+template <class I, class V>
+__global__ void k_rebuild_each(const int64_t* __restrict__ seg_start, int64_t nseg,
+                               const int32_t* __restrict__ seg_row, const int32_t* __restrict__ tile_seg,
+                               int32_t P, int32_t T, uint32_t swz_lim, const I* __restrict__ idx,
+                               const uint64_t* __restrict__ dmask, uint32_t pad,
+                               const int32_t* __restrict__ pos, const V* __restrict__ A,
+                               const V* __restrict__ W, const V* __restrict__ H, int64_t m,
+                               int64_t n, int32_t k, int64_t nnz, V* __restrict__ val) {
+    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnz;
+         e += (int64_t)gridDim.x * kT) {
+        const int64_t f = pos[e];            // value slot
+        const int64_t q = val_entry<V>(f);   // entry position
+        int64_t lo = 0, hi = nseg;  // last s with seg_start[s] <= q
+        while (hi - lo > 1) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (seg_start[mid] <= q) lo = mid; else hi = mid;
+        }
+        int32_t plo = 0, phi = P;  // last tile p with tile_seg[p] <= s
+        while (phi - plo > 1) {
+            const int32_t mid = (plo + phi) >> 1;
+            if (tile_seg[mid] <= lo) plo = mid; else phi = mid;
+        }
+        const int64_t i = seg_row[lo];
+        const uint32_t c = index_at<I>(idx, dmask, pad, q) & IndexBits<I>::mask;
+        const int64_t j = (int64_t)plo * T + (int64_t)(c < swz_lim ? lds_swizzle(c) : c);
+        double pred = 0.0;
+        for (int32_t t = 0; t < k; ++t)
+            pred = __builtin_fma((double)W[(int64_t)t * m + i], (double)H[(int64_t)t * n + j], pred);
+        val[f] = (V)((double)A[f] - pred);
+    }
+}
+
 // R = A - w_i^T h_j for every entry of the user-major layout (prediction summed in fp64,
 // one rounding to the value type).  A wave takes a window: lane l finds the segment of
 // its kE entries (they belong to one) and from it the row and the tile, and puts
 // their columns in LDS.  Then groups of G lanes take the window's lanes' entries in
 // turn, each lane four features of every row h_j at a time, so that a row of HT (H
 // row-major, rows of `pitch` values, a multiple of 4, zero past k) is read in whole
-// lines, and the lanes' sums are added over the group.  A holds the ratings in
-// the slots of val.
+// lines, and the lanes' sums are added over the group.  `parts` (a power of two, at most
+// G) waves share a window's turns where windows alone are too few (2,000 x 1,000, 50,000
+// ratings, k = 40: 30.9 -> 8.2 us).  A holds the ratings in the slots of val.
 // Bound by L2: one lane per entry fetched a 128-byte line per 16 bytes of a row, at
 // 31 TB/s.  (m = 480,189, n = 17,770, 100.5M ratings, k = 40: 8.3 ms with one
 // 4-byte gather per entry and feature, 4.1 with 16-byte ones, 2.9 now.)
@@ -454,14 +506,16 @@ __global__ __launch_bounds__(kT) void k_rebuild(
     const int64_t* __restrict__ seg_start, int64_t nseg, const int32_t* __restrict__ seg_row,
     const int32_t* __restrict__ tile_seg, int32_t P, int32_t T, uint32_t swz_lim,
     const I* __restrict__ idx, const uint64_t* __restrict__ dmask, uint32_t pad,
-    const V* __restrict__ A, const V* __restrict__ W, const V* __restrict__ HT, int64_t m, int32_t k,
-    int32_t pitch, int64_t npad, V* __restrict__ val) {
+    const V* __restrict__ A, const V* __restrict__ W, const V* __restrict__ HT, int64_t m,
+    uint32_t k, uint32_t pitch, int64_t npad, int parts, V* __restrict__ val) {
     constexpr uint32_t kNone = 0xFFFFFFFFu;  // a padding entry
     __shared__ uint4 cols[kT / 64][64][2];
     const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63u);
     const int grp = lane / G, g = lane % G;
-    for (int64_t w = (int64_t)blockIdx.x * (kT / 64) + wave; w < npad / kWin;
-         w += (int64_t)gridDim.x * (kT / 64)) {
+    for (int64_t wp = (int64_t)blockIdx.x * (kT / 64) + wave; wp < npad / kWin * parts;
+         wp += (int64_t)gridDim.x * (kT / 64)) {
+        const int64_t w = wp / parts;
+        const int turns = G / parts, it0 = (int)(wp % parts) * turns;
         const int64_t q0 = w * kWin + lane * kE;
         int64_t lo = 0, hi = nseg;  // last s with seg_start[s] <= q0
         while (hi - lo > 1) {
@@ -500,13 +554,13 @@ __global__ __launch_bounds__(kT) void k_rebuild(
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        for (int it = 0; it < G; ++it) {
+        for (int it = it0; it < it0 + turns; ++it) {
             const int b = it * (64 / G) + grp;  // whose entries
             const int64_t i = __shfl(row, b);
             const uint4 ca = cols[wave][b][0], cb = cols[wave][b][1];
             const uint32_t j[kE] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
             double pred[kE] = {};
-            for (int32_t t = 4 * g; t < pitch; t += 4 * G) {
+            for (uint32_t t = 4 * g; t < pitch; t += 4 * G) {
                 Row4<V> wt;
                 for (int u = 0; u < 4; ++u) wt.v[u] = t + u < k ? W[(int64_t)(t + u) * m + i] : V(0);
                 Row4<V> h[kE];
@@ -687,14 +741,14 @@ __global__ void k_test_err_rows(const int32_t* __restrict__ row, const int32_t* 
                                 const float* __restrict__ val, int64_t nnz,
                                 const int32_t* __restrict__ rnew, const int32_t* __restrict__ cnew,
                                 const V* __restrict__ W, const V* __restrict__ H, int64_t m, int64_t n,
-                                int32_t k, int32_t pitch, double* __restrict__ part,
+                                uint32_t k, uint32_t pitch, double* __restrict__ part,
                                 const unsigned long long* __restrict__ stop) {
     double acc = 0.0;
     if (stop && *stop != 0) nnz = 0;
     for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnz;
          e += (int64_t)gridDim.x * kT) {
         const int64_t i = rnew[row[e]], j = cnew[col[e]];
-        auto four = [&](auto rows, const V* F, int64_t r, int64_t len, int32_t t) {
+        auto four = [&](auto rows, const V* F, int64_t r, int64_t len, uint32_t t) {
             Row4<V> x;
             if constexpr (decltype(rows)::value) {
                 x = load4(F + r * pitch + t);
@@ -705,7 +759,7 @@ __global__ void k_test_err_rows(const int32_t* __restrict__ row, const int32_t* 
         };
         double pred = 0.0;
 #pragma unroll 4
-        for (int32_t t = 0; t < pitch; t += 4) {
+        for (uint32_t t = 0; t < pitch; t += 4) {
             const Row4<V> w = four(std::bool_constant<WR>{}, W, i, m, t);
             const Row4<V> h = four(std::bool_constant<HR>{}, H, j, n, t);
             for (int u = 0; u < 4; ++u) pred = __builtin_fma((double)w.v[u], (double)h.v[u], pred);
@@ -1064,31 +1118,45 @@ hipError_t launch_delta_windows(void* idx, int64_t npad, int32_t pad, uint64_t* 
 
 template <class I, class V>
 static void rebuild_groups(const Layout& L, const V* A, const V* W, const V* HT, int64_t m, int32_t k,
-                           int32_t pitch, hipStream_t s) {
+                           hipStream_t s) {
     // Lanes per row of HT: as many as its values fill, four each.
-    const dim3 grid = grid_for(L.npad / kWin * 64, 1 << 14);
+    const uint32_t pitch = (uint32_t)row_pitch(k);
+    const int groups = pitch <= 16 ? 4 : pitch <= 32 ? 8 : 16;
+    const int64_t nwin = L.npad / kWin;
+    int parts = 1;
+    while (parts < groups && nwin * parts < kRebuildWaves) parts *= 2;
+    const dim3 grid = grid_for(nwin * parts * 64, 1 << 14);
 #define CCDK_REBUILD(G)                                                                            \
     hipLaunchKernelGGL((k_rebuild<I, V, G>), grid, dim3(kT), 0, s, L.seg_start, L.nseg, L.seg_row,   \
                        L.tile_seg, L.P, L.T, L.swz_lim, static_cast<const I*>(L.idx),                \
-                       sizeof(I) == 2 ? L.dmask : nullptr, (uint32_t)L.pad, A, W, HT, m, k, pitch,   \
-                       L.npad, static_cast<V*>(L.val))
-    if (pitch <= 16)
+                       sizeof(I) == 2 ? L.dmask : nullptr, (uint32_t)L.pad, A, W, HT, m,             \
+                       (uint32_t)k, pitch, L.npad, parts, static_cast<V*>(L.val))
+    if (groups == 4)
         CCDK_REBUILD(4);
-    else if (pitch <= 32)
+    else if (groups == 8)
         CCDK_REBUILD(8);
     else
         CCDK_REBUILD(16);
 #undef CCDK_REBUILD
 }
+template <class I, class V>
+static void rebuild_any(const Layout& L, const int32_t* pos, const V* A, const V* W, const V* H,
+                        const V* HT, int64_t m, int32_t k, hipStream_t s) {
+    if (HT) return rebuild_groups<I, V>(L, A, W, HT, m, k, s);
+    hipLaunchKernelGGL((k_rebuild_each<I, V>), grid_for(L.nnz), dim3(kT), 0, s, L.seg_start, L.nseg,
+                       L.seg_row, L.tile_seg, L.P, L.T, L.swz_lim, static_cast<const I*>(L.idx),
+                       sizeof(I) == 2 ? L.dmask : nullptr, (uint32_t)L.pad, pos, A, W, H, m, L.cols, k,
+                       L.nnz, static_cast<V*>(L.val));
+}
 
 template <class V>
-hipError_t launch_rebuild_residual(const Layout& L, const V* A, const V* W, const V* HT, int64_t m,
-                                   int32_t k, int32_t pitch, hipStream_t s) {
+hipError_t launch_rebuild_residual(const Layout& L, const int32_t* pos, const V* A, const V* W,
+                                   const V* H, const V* HT, int64_t m, int32_t k, hipStream_t s) {
     if (L.nnz == 0) return hipSuccess;
     if (L.idx16)
-        rebuild_groups<uint16_t, V>(L, A, W, HT, m, k, pitch, s);
+        rebuild_any<uint16_t, V>(L, pos, A, W, H, HT, m, k, s);
     else
-        rebuild_groups<int32_t, V>(L, A, W, HT, m, k, pitch, s);
+        rebuild_any<int32_t, V>(L, pos, A, W, H, HT, m, k, s);
     return hipGetLastError();
 }
 
@@ -1150,18 +1218,19 @@ template <class V>
 hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                                 const int32_t* rold2new, const int32_t* cold2new, const V* W,
                                 const V* H, const V* WT, const V* HT, int64_t m, int64_t n, int32_t k,
-                                int32_t pitch, double* part, int32_t nparts,
+                                double* part, int32_t nparts,
                                 const unsigned long long* bad, hipStream_t s) {
     const dim3 grid((unsigned)nparts);
+    const uint32_t pitch = (uint32_t)row_pitch(k);
     if (WT && HT)
         hipLaunchKernelGGL((k_test_err_rows<V, true, true>), grid, dim3(kT), 0, s, row, col, val, nnz,
-                           rold2new, cold2new, WT, HT, m, n, k, pitch, part, bad);
+                           rold2new, cold2new, WT, HT, m, n, (uint32_t)k, pitch, part, bad);
     else if (HT)
         hipLaunchKernelGGL((k_test_err_rows<V, false, true>), grid, dim3(kT), 0, s, row, col, val, nnz,
-                           rold2new, cold2new, W, HT, m, n, k, pitch, part, bad);
+                           rold2new, cold2new, W, HT, m, n, (uint32_t)k, pitch, part, bad);
     else
         hipLaunchKernelGGL((k_test_err_rows<V, true, false>), grid, dim3(kT), 0, s, row, col, val, nnz,
-                           rold2new, cold2new, WT, H, m, n, k, pitch, part, bad);
+                           rold2new, cold2new, WT, H, m, n, (uint32_t)k, pitch, part, bad);
     return hipGetLastError();
 }
 
@@ -1179,13 +1248,14 @@ hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const fl
                                                     int64_t, int32_t, int64_t, float*, hipStream_t); \
     template hipError_t launch_factor_out<V, double>(const V*, const int32_t*, const int32_t*,  \
                                                      int64_t, int32_t, int64_t, double*, hipStream_t); \
-    template hipError_t launch_rebuild_residual<V>(const Layout&, const V*, const V*, const V*, \
-                                                   int64_t, int32_t, int32_t, hipStream_t);     \
+    template hipError_t launch_rebuild_residual<V>(const Layout&, const int32_t*, const V*,     \
+                                                   const V*, const V*, const V*, int64_t,       \
+                                                   int32_t, hipStream_t);                       \
     template hipError_t launch_test_err_rows<V>(const int32_t*, const int32_t*, const float*,   \
                                                 int64_t, const int32_t*, const int32_t*,        \
                                                 const V*, const V*, const V*, const V*,         \
-                                                int64_t, int64_t, int32_t, int32_t, double*,    \
-                                                int32_t, const unsigned long long*, hipStream_t); \
+                                                int64_t, int64_t, int32_t, double*, int32_t,    \
+                                                const unsigned long long*, hipStream_t);        \
     template hipError_t launch_copy_mapped<V, V>(const V*, const int32_t*, V*, const int32_t*,  \
                                                  int64_t, hipStream_t);                         \
     template hipError_t launch_consistency<V>(const V*, const int32_t*, const V*,               \

@@ -467,12 +467,14 @@ hipError_t launch_scatter_factor_in(const S* rowmajor, const int32_t* new2old, i
 template <class V, class S>
 hipError_t launch_factor_out(const V* colmajor, const int32_t* new2old, const int32_t* old2new,
                              int64_t rows, int32_t k, int64_t pitch, S* rowmajor, hipStream_t s);
-// The residual of the user-major copy from the ratings A (in its value slots), W
-// (column-major) and HT (H row-major, rows of `pitch` values, a multiple of 4).
+// Values per row of the row-major copies below: k rounded up to a multiple of 4, zero past k.
+inline int64_t row_pitch(int32_t k) { return ((int64_t)k + 3) / 4 * 4; }
+// The residual of the user-major copy from the ratings A (in its value slots; pos: its
+// entries' slots), W and H (column-major) and, or null, HT (H row-major, rows of
+// row_pitch(k) values).
 template <class V>
-hipError_t launch_rebuild_residual(const Layout& L, const V* A, const V* W, const V* HT, int64_t m,
-                                   int32_t k, int32_t pitch, hipStream_t s);
-inline int32_t row_pitch(int32_t k) { return (k + 3) / 4 * 4; }
+hipError_t launch_rebuild_residual(const Layout& L, const int32_t* pos, const V* A, const V* W,
+                                   const V* H, const V* HT, int64_t m, int32_t k, hipStream_t s);
 // dst[dmap ? dmap[i] : i] = src[smap ? smap[i] : i] for i < n (converting between types)
 template <class S, class V>
 hipError_t launch_copy_mapped(const S* src, const int32_t* smap, V* dst, const int32_t* dmap,
@@ -501,14 +503,14 @@ hipError_t launch_test_err(const int32_t* row, const int32_t* col, const float* 
                            int32_t nparts, double* rejected, const unsigned long long* bad,
                            hipStream_t s);
 // The same with a row-major copy of one or both factors over relabelled ids (WT, HT: rows
-// of `pitch` values, a multiple of 4, zero past k; null: the column-major W or H
-// serves); triplets checked by the caller.
+// of row_pitch(k) values; null: the column-major W or H serves); triplets checked by the
+// caller.
 template <class V>
 hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                                 const int32_t* rold2new, const int32_t* cold2new, const V* W,
                                 const V* H, const V* WT, const V* HT, int64_t m, int64_t n, int32_t k,
-                                int32_t pitch, double* part, int32_t nparts,
-                                const unsigned long long* bad, hipStream_t s);
+                                double* part, int32_t nparts, const unsigned long long* bad,
+                                hipStream_t s);
 // Adds the number of triplets out of range or not finite, or of values not finite, to *bad.
 hipError_t launch_check_triplets(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                                  int64_t m, int64_t n, unsigned long long* bad, hipStream_t s);

@@ -130,6 +130,26 @@ def test_set_factors_out_of_memory_changes_nothing():
     b.close()
 
 
+def test_set_factors_without_memory_for_rows():
+    # 700,000 entries x 6: the rebuild wants H in rows, after the two staging buffers; without
+    # memory for it the columns serve, as they always do for fewer.
+    m, n, k = 3000, 1500, 6
+    a, b, W0, H0 = _pair(m, n, 700_000, k, seed=13)
+    W1 = W0[::-1].copy()
+    for args in ((W1, H0), (None, H0), (W1, None), (None, None)):
+        C.ccdpp_debug_inject(ALLOC, sum(x is not None for x in args))
+        a.set_factors(*args)
+        C.ccdpp_debug_inject(ALLOC, -1)
+        b.set_factors(*args)
+        for x, y in zip(a.factors(), b.factors()):
+            assert np.array_equal(x, y)
+        # (sums of six products in float64, in two orders, each rounded to float once)
+        assert np.abs(a.residual() - b.residual()).max() <= 2.0 ** -23 * np.abs(b.residual()).max()
+        assert a.check_consistency() == 0
+    a.close()
+    b.close()
+
+
 def test_elementwise_ccd_out_of_memory_then_recovers():
     a, b, _, _ = _pair(seed=4)
     C.ccdpp_debug_inject(ALLOC, 1)  # the second slot map of the first ccd_run fails

@@ -94,3 +94,36 @@ def test_factors_at_the_largest_k():
     for at in (0, k // 2, k - 64):
         part = H[0, at:at + 64].astype(np.float64)
         assert np.isfinite(part).all() and 0.04 < part.std() < 0.2  # N(0, 0.01)
+
+
+@pytest.mark.parametrize("k,nnz", [(6, 820_000), (9, 480_000), (16, 300_000), (20, 250_000), (32, 150_000),
+                                   (67, 70_000), (130, 36_000)])
+@pytest.mark.parametrize("layout", sorted(LAYOUTS))
+@pytest.mark.parametrize("precision", [0, 1])
+def test_rebuild_in_rows(k, nnz, layout, precision):
+    # From 2^22 entries times features the rebuild reads rows of H, 4, 8 or 16 lanes to a
+    # row; 820,000 entries give every wave a window, fewer share a window out.
+    m, n = 2_900, 701
+    rng = np.random.default_rng(k)
+    key = rng.choice(m * n, nnz, replace=False)
+    row, col = (key // n).astype(np.int32), (key % n).astype(np.int32)
+    val = rng.standard_normal(nnz).astype(np.float32)
+    dt = np.float64 if precision else np.float32
+    W, H = rng.standard_normal((m, k)).astype(dt), rng.standard_normal((n, k)).astype(dt)
+    kw = dict(LAYOUTS[layout], precision=precision)
+    if layout != "global":
+        kw["tile_width"] = (192, 320)
+    print(f"case: k {k} nnz {nnz} {layout} precision {precision}", flush=True)
+    g = CCDPP(m, n, k, 0.1, row, col, val, opts=make_options(**kw))
+    (g.set_factors_f64 if precision else g.set_factors)(W, H)
+    Wd, Hd = W.astype(np.float64), H.astype(np.float64)
+    dot, mag = np.zeros(nnz), np.abs(val).astype(np.float64)
+    for t in range(k):
+        x = Wd[:, t][row] * Hd[:, t][col]
+        dot, mag = dot + x, mag + np.abs(x)
+    want = val.astype(np.float64) - dot
+    got = g.residual_f64()
+    bound = np.abs(want) * (2.0 ** -24 if precision == 0 else 0.0) * 1.001 + mag * 4e-16 * (k + 2)
+    assert (np.abs(got - want) <= bound).all()
+    assert g.check_consistency() == 0
+    g.close()
