@@ -52,10 +52,12 @@ constexpr int64_t kMaxNnz = INT32_MAX;
 // 245 MB 37.2 against 33.2, 330 MB 46.2 against 47.5.
 constexpr int64_t kCachedStreamBytes = int64_t(288) << 20;
 constexpr int32_t kReduceParts = 1024;
-// Arguments of up to this many elements are checked on the host (about 15 us), longer
-// ones on the device once they are there (30 us with the wait, 1.4M triplets or 20M
-// factors included, which took a host thread 1 and 6 ms).
-constexpr int64_t kHostCheck = 24576;
+// Arguments of up to this many elements are checked on the host, longer ones on the device
+// once they are there: for factors a wait of its own, some 20 us, against 0.2 ns per value on
+// the host (2,000 x 1,000, k = 40: 91 us a call either way; k = 20: 65 against 78; 6,041 x 3,707, k =
+// 40: 184 against 129).
+constexpr int64_t kHostCheckTriplets = 24576;
+constexpr int64_t kHostCheckValues = 1 << 17;
 // Entries times features from which rebuilding the residual pays for a row-major H and its
 // turn (us, an entry per thread against turn and rows: 50,000 x 10 7.1 against 9.1, 300,000 x
 // 10 12.1 against 13.3, 300,000 x 20 18.5 against 17.7, 600,000 x 10 35.6 against 26.5).
@@ -1591,14 +1593,14 @@ struct Held {
     int load(ccdpp* h, int64_t nnz, const int32_t* r, const int32_t* c, const float* v) {
         const hipStream_t s = h->stream;
         const size_t bytes = (size_t)nnz * 4;
-        if (nnz <= kHostCheck) RCK(bad_triplet(h, nnz, r, c, v));
+        if (nnz <= kHostCheckTriplets) RCK(bad_triplet(h, nnz, r, c, v));
         HIPCK(h, talloc(h, tr, &row, nnz));
         HIPCK(h, talloc(h, tc, &col, nnz));
         HIPCK(h, talloc(h, tv, &val, nnz));
         HIPCK(h, h->stage.to_device(row, r, bytes, h->device, s));
         HIPCK(h, h->stage.to_device(col, c, bytes, h->device, s));
         HIPCK(h, h->stage.to_device(val, v, bytes, h->device, s));
-        if (nnz <= kHostCheck) return CCDPP_OK;
+        if (nnz <= kHostCheckTriplets) return CCDPP_OK;
         bad = h->d_count;
         HIPCK(h, ccdk::launch_fill<double>(reinterpret_cast<double*>(bad), 0.0, 1, s));
         HIPCK(h, ccdk::launch_check_triplets(row, col, val, nnz, h->m, h->n, bad, s));
@@ -1822,7 +1824,7 @@ int set_factors_impl(ccdpp* h, const S* W, const S* H) {
                 return fail(h, CCDPP_EINVAL, "H[%lld] is not finite", (long long)e);
         return CCDPP_OK;
     };
-    const bool host_check = (W ? nw : 0) + (H ? nh : 0) <= kHostCheck;
+    const bool host_check = (W ? nw : 0) + (H ? nh : 0) <= kHostCheckValues;
     if (host_check) RCK(not_finite());
     // Staging buffers first: a failed allocation leaves the factors and the residual
     // as they were.

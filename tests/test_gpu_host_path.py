@@ -80,7 +80,7 @@ def test_bad_held_out_triplets_are_named(entries):
     g.close()
 
 
-@pytest.mark.parametrize("m", [200, 40_000])
+@pytest.mark.parametrize("m", [200, 32_618, 32_619, 40_000])  # (2^17 values are checked on the host)
 def test_factors_that_are_not_finite_change_nothing(m):
     n, k = 150, 4
     row, col, val, H0 = synth.small_random(m, n, 3_000, k, seed=9)
