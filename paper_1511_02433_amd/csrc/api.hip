@@ -53,9 +53,11 @@ constexpr int64_t kMaxNnz = INT32_MAX;
 constexpr int64_t kCachedStreamBytes = int64_t(288) << 20;
 constexpr int32_t kReduceParts = 1024;
 // Arguments of up to this many elements are checked on the host, longer ones on the device
-// once they are there: for factors a wait of its own, some 20 us, against 0.2 ns per value on
-// the host (2,000 x 1,000, k = 40: 91 us a call either way; k = 20: 65 against 78; 6,041 x 3,707, k =
-// 40: 184 against 129).
+// once they are there, with a wait of their own (some 20 us), against 0.7 ns per triplet and
+// 0.2 per factor on the host (factors of 2,000 x 1,000, k = 40: 91 us a call either way; k = 20: 65
+// against 78; 6,041 x 3,707, k = 40: 184 against 129).  The held-out RMSE checks its triplets in
+// the kernel that uses them, at any number (24,577 of them: 63 us a call, 73 with the host's
+// check; 200,000: 112 against 199).
 constexpr int64_t kHostCheckTriplets = 24576;
 constexpr int64_t kHostCheckValues = 1 << 17;
 // Entries times features from which rebuilding the residual pays for a row-major H and its
@@ -132,7 +134,8 @@ struct ccdpp {
     void* v = nullptr;
     double* sse_part = nullptr;
     int32_t sse_nparts = 0;
-    double* d_scalar = nullptr;
+    double* d_scalar = nullptr;    // a sum, and next to it
+    unsigned long long* d_bad = nullptr;    // arguments refused by the running call; 0 between calls
     unsigned long long* d_count = nullptr;
     double* scratch = nullptr;     // device address of this device's `scratch` array
     int32_t pending = -1;          // feature whose eq. 18 subtract is still folded into R-hat
@@ -1255,7 +1258,9 @@ int create_device(ccdpp* h, const int32_t* row, const int32_t* col, const float*
     h->sse_nparts = std::max<int32_t>((h->L[0].grid + h->L[1].grid + h->L[2].grid) * kWaves,
                                       kReduceParts);
     HIPCK(h, dalloc(h, &h->sse_part, h->sse_nparts));
-    HIPCK(h, dalloc(h, &h->d_scalar, 1));
+    HIPCK(h, dalloc(h, &h->d_scalar, 2));
+    h->d_bad = reinterpret_cast<unsigned long long*>(h->d_scalar + 1);
+    HIPCK(h, launch_fill<double>(h->d_scalar, 0.0, 2, s));
     HIPCK(h, dalloc(h, &h->d_count, 1));
     HIPCK(h, hipStreamSynchronize(s));
     phase(4);
@@ -1573,9 +1578,15 @@ struct RowFactors {
         side(th, &h, p->n);
     }
 };
-// Held-out triplets on the device.  Many of them are checked there, on the way to their
-// use: the number that may not be used goes to h->d_count, and only if there is one
-// does the host look for the first.
+// The arguments that kernels found unusable, once the stream is idle: clears their number
+// for the next call.
+int clear_bad(ccdpp* h, unsigned long long count) {
+    if (count) HIPCK(h, ccdk::launch_fill<double>(reinterpret_cast<double*>(h->d_bad), 0.0, 1, h->stream));
+    return CCDPP_OK;
+}
+// Held-out triplets on the device.  They are checked there, by the kernel that uses them
+// (in_use) or by check() where they are many: the number that may not be used goes to
+// h->d_bad, and only if there is one does the host look for the first.
 int bad_triplet(ccdpp* h, int64_t nnz, const int32_t* row, const int32_t* col, const float* val) {
     for (int64_t e = 0; e < nnz; ++e) {
         if (row[e] < 0 || row[e] >= h->m || col[e] < 0 || col[e] >= h->n)
@@ -1589,34 +1600,44 @@ struct Held {
     Tmp tr, tc, tv;
     int32_t *row = nullptr, *col = nullptr;
     float* val = nullptr;
-    unsigned long long* bad = nullptr;  // their number, null when the host has checked them
-    int load(ccdpp* h, int64_t nnz, const int32_t* r, const int32_t* c, const float* v) {
+    unsigned long long* bad = nullptr;  // h->d_bad, null when the host has checked them
+    int load(ccdpp* h, int64_t nnz, const int32_t* r, const int32_t* c, const float* v, bool in_use) {
         const hipStream_t s = h->stream;
         const size_t bytes = (size_t)nnz * 4;
-        if (nnz <= kHostCheckTriplets) RCK(bad_triplet(h, nnz, r, c, v));
+        if (in_use || nnz > kHostCheckTriplets)
+            bad = h->d_bad;
+        else
+            RCK(bad_triplet(h, nnz, r, c, v));
         HIPCK(h, talloc(h, tr, &row, nnz));
         HIPCK(h, talloc(h, tc, &col, nnz));
         HIPCK(h, talloc(h, tv, &val, nnz));
         HIPCK(h, h->stage.to_device(row, r, bytes, h->device, s));
         HIPCK(h, h->stage.to_device(col, c, bytes, h->device, s));
         HIPCK(h, h->stage.to_device(val, v, bytes, h->device, s));
-        if (nnz <= kHostCheckTriplets) return CCDPP_OK;
-        bad = h->d_count;
-        HIPCK(h, ccdk::launch_fill<double>(reinterpret_cast<double*>(bad), 0.0, 1, s));
-        HIPCK(h, ccdk::launch_check_triplets(row, col, val, nnz, h->m, h->n, bad, s));
         return CCDPP_OK;
+    }
+    // Their check ahead of any use.
+    int check(ccdpp* h, int64_t nnz, const int32_t* r, const int32_t* c, const float* v) {
+        if (!bad) return CCDPP_OK;
+        unsigned long long count = 0;
+        HIPCK(h, ccdk::launch_check_triplets(row, col, val, nnz, h->m, h->n, bad, h->stream));
+        HIPCK(h, hipMemcpyAsync(&count, bad, 8, hipMemcpyDeviceToHost, h->stream));
+        HIPCK(h, hipStreamSynchronize(h->stream));
+        bad = nullptr;
+        return refuse(h, count, nnz, r, c, v);
     }
     // Once the count is known: CCDPP_OK, or EINVAL naming the first of them.
     static int refuse(ccdpp* h, unsigned long long count, int64_t nnz, const int32_t* r,
                       const int32_t* c, const float* v) {
         if (count == 0) return CCDPP_OK;
+        RCK(clear_bad(h, count));
         RCK(bad_triplet(h, nnz, r, c, v));
         return fail(h, CCDPP_EINVAL, "test entries changed during the call");
     }
 };
 
 int launch_test_err_any(ccdpp* h, const int32_t* dr, const int32_t* dc, const float* dv,
-                        int64_t nnz, const RowFactors* rows, const unsigned long long* bad = nullptr,
+                        int64_t nnz, const RowFactors* rows, unsigned long long* bad = nullptr,
                         double* part = nullptr, double* rejected = nullptr) {
     return with_value_type(h, [&](auto z) -> int {
         using V = decltype(z);
@@ -1840,13 +1861,13 @@ int set_factors_impl(ccdpp* h, const S* W, const S* H) {
     if (W) HIPCK(h, h->stage.to_device(dW, W, nw * sizeof(S), h->device, s));
     if (H) HIPCK(h, h->stage.to_device(dH, H, nh * sizeof(S), h->device, s));
     if (!host_check) {  // on the device, before anything changes
-        HIPCK(h, ccdk::launch_fill<double>(reinterpret_cast<double*>(h->d_count), 0.0, 1, s));
-        if (W) HIPCK(h, ccdk::launch_check_finite<S>(dW, nw, h->d_count, s));
-        if (H) HIPCK(h, ccdk::launch_check_finite<S>(dH, nh, h->d_count, s));
+        if (W) HIPCK(h, ccdk::launch_check_finite<S>(dW, nw, h->d_bad, s));
+        if (H) HIPCK(h, ccdk::launch_check_finite<S>(dH, nh, h->d_bad, s));
         unsigned long long bad = 0;
-        HIPCK(h, hipMemcpyAsync(&bad, h->d_count, 8, hipMemcpyDeviceToHost, s));
+        HIPCK(h, hipMemcpyAsync(&bad, h->d_bad, 8, hipMemcpyDeviceToHost, s));
         HIPCK(h, hipStreamSynchronize(s));
         if (bad) {
+            RCK(clear_bad(h, bad));
             RCK(not_finite());
             return fail(h, CCDPP_EINVAL, "the factors changed during the call");
         }
@@ -1965,13 +1986,8 @@ int ccdpp_run_until(ccdpp_t* h, int32_t max_outer, int32_t inner, double rel_tol
     Held held;
     RowFactors rows;
     if (test_nnz > 0) {
-        RCK(held.load(h, test_nnz, test_row, test_col, test_val));
-        if (held.bad) {  // before any iteration runs
-            unsigned long long bad = 0;
-            HIPCK(h, hipMemcpyAsync(&bad, held.bad, 8, hipMemcpyDeviceToHost, s));
-            HIPCK(h, hipStreamSynchronize(s));
-            RCK(Held::refuse(h, bad, test_nnz, test_row, test_col, test_val));
-        }
+        RCK(held.load(h, test_nnz, test_row, test_col, test_val, false));
+        RCK(held.check(h, test_nnz, test_row, test_col, test_val));  // before any iteration runs
         if (max_outer > 0) rows.allocate(h, test_nnz);
     }
     // A fixed-order float64 sum on the device, read back.
@@ -2039,18 +2055,19 @@ int ccdpp_rmse(ccdpp_t* h, int64_t nnz, const int32_t* row, const int32_t* col, 
     hipStream_t s = h->stream;
     Held held;
     RowFactors rows;
-    RCK(held.load(h, nnz, row, col, val));
+    RCK(held.load(h, nnz, row, col, val, true));
     rows.allocate(h, nnz);
-    // (a triplet that may not be used stops the kernel)
     RCK(launch_test_err_any(h, held.row, held.col, held.val, nnz, &rows, held.bad));
     HIPCK(h, ccdk::launch_reduce_sum(h->sse_part, kReduceParts, h->d_scalar, s));
-    double sum = 0.0;
-    unsigned long long bad = 0;
-    HIPCK(h, hipMemcpyAsync(&sum, h->d_scalar, 8, hipMemcpyDeviceToHost, s));
-    if (held.bad) HIPCK(h, hipMemcpyAsync(&bad, held.bad, 8, hipMemcpyDeviceToHost, s));
+    struct {
+        double sum;
+        unsigned long long bad;
+    } got{};
+    static_assert(sizeof got == 16, "as in d_scalar and d_bad");
+    HIPCK(h, hipMemcpyAsync(&got, h->d_scalar, sizeof got, hipMemcpyDeviceToHost, s));
     HIPCK(h, hipStreamSynchronize(s));
-    RCK(Held::refuse(h, bad, nnz, row, col, val));
-    *rmse_out = std::sqrt(sum / (double)nnz);
+    RCK(Held::refuse(h, got.bad, nnz, row, col, val));
+    *rmse_out = std::sqrt(got.sum / (double)nnz);
     return CCDPP_OK;
 }
 

@@ -690,29 +690,32 @@ __global__ void k_sq_sum(const V* __restrict__ v, int64_t n, double* __restrict_
     block_total(acc, &part[blockIdx.x]);
 }
 
+// A held-out triplet that no kernel may use.
+__device__ __forceinline__ bool unusable(int32_t r, int32_t c, float a, int64_t m, int64_t n) {
+    return r < 0 || (int64_t)r >= m || c < 0 || (int64_t)c >= n || !__builtin_isfinite(a);
+}
+
 // Squared prediction errors of held-out triplets, one fixed-order partial per block.
 // CHECK: the triplets were not validated on the host; an entry whose indices are out
 // of range or whose value is not finite is skipped (never used as an index) and
-// counted in rejected[blockIdx.x].  Valid entries take the same arithmetic in the
-// same order either way.
+// counted in rejected[blockIdx.x] and *bad (either may be null).  Valid entries take the
+// same arithmetic in the same order either way.
 template <class V, bool CHECK>
 __global__ void k_test_err(const int32_t* __restrict__ row, const int32_t* __restrict__ col,
                            const float* __restrict__ val, int64_t nnz,
                            const int32_t* __restrict__ rnew, const int32_t* __restrict__ cnew,
                            const V* __restrict__ W, const V* __restrict__ H, int64_t m,
                            int64_t n, int32_t k, double* __restrict__ part,
-                           double* __restrict__ rejected,
-                           const unsigned long long* __restrict__ stop) {
+                           double* __restrict__ rejected, unsigned long long* bad) {
     double acc = 0.0;
-    double bad = 0.0;
-    if (stop && *stop != 0) nnz = 0;
+    int refused = 0;
     for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnz;
          e += (int64_t)gridDim.x * kT) {
         const int32_t r = row[e], c = col[e];
         const float a = val[e];
         if constexpr (CHECK) {
-            if (r < 0 || (int64_t)r >= m || c < 0 || (int64_t)c >= n || !__builtin_isfinite(a)) {
-                bad += 1.0;
+            if (unusable(r, c, a, m, n)) {
+                ++refused;
                 continue;
             }
         }
@@ -727,27 +730,38 @@ __global__ void k_test_err(const int32_t* __restrict__ row, const int32_t* __res
     }
     block_total(acc, &part[blockIdx.x]);
     if constexpr (CHECK) {
-        __syncthreads();  // block_total's LDS is reused
-        block_total(bad, &rejected[blockIdx.x]);
+        if (bad && refused) atomicAdd(bad, (unsigned long long)refused);
+        if (rejected) {
+            __syncthreads();  // block_total's LDS is reused
+            block_total((double)refused, &rejected[blockIdx.x]);
+        }
     }
 }
 
 // k_test_err with one or both factors as a row-major copy over relabelled ids (rows of
 // `pitch` values, a multiple of 4, zero past k): four features per gather instead of one,
 // and a row's gathers in the same lines.  WR, HR: which are row-major; the other one is
-// column-major.  The same sums in the same order.
-template <class V, bool WR, bool HR>
+// column-major.  CHECK: as there.  The same sums in the same order.
+template <class V, bool WR, bool HR, bool CHECK>
 __global__ void k_test_err_rows(const int32_t* __restrict__ row, const int32_t* __restrict__ col,
                                 const float* __restrict__ val, int64_t nnz,
                                 const int32_t* __restrict__ rnew, const int32_t* __restrict__ cnew,
                                 const V* __restrict__ W, const V* __restrict__ H, int64_t m, int64_t n,
                                 uint32_t k, uint32_t pitch, double* __restrict__ part,
-                                const unsigned long long* __restrict__ stop) {
+                                unsigned long long* bad) {
     double acc = 0.0;
-    if (stop && *stop != 0) nnz = 0;
+    int refused = 0;
     for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnz;
          e += (int64_t)gridDim.x * kT) {
-        const int64_t i = rnew[row[e]], j = cnew[col[e]];
+        const int32_t r = row[e], c = col[e];
+        const float a = val[e];
+        if constexpr (CHECK) {
+            if (unusable(r, c, a, m, n)) {
+                ++refused;
+                continue;
+            }
+        }
+        const int64_t i = rnew[r], j = cnew[c];
         auto four = [&](auto rows, const V* F, int64_t r, int64_t len, uint32_t t) {
             Row4<V> x;
             if constexpr (decltype(rows)::value) {
@@ -764,10 +778,13 @@ __global__ void k_test_err_rows(const int32_t* __restrict__ row, const int32_t* 
             const Row4<V> h = four(std::bool_constant<HR>{}, H, j, n, t);
             for (int u = 0; u < 4; ++u) pred = __builtin_fma((double)w.v[u], (double)h.v[u], pred);
         }
-        const double err = (double)val[e] - pred;
+        const double err = (double)a - pred;
         acc = __builtin_fma(err, err, acc);
     }
     block_total(acc, &part[blockIdx.x]);
+    if constexpr (CHECK) {
+        if (refused) atomicAdd(bad, (unsigned long long)refused);
+    }
 }
 
 // ---- segments of a tiled copy ----------------------------------------------------------
@@ -873,8 +890,7 @@ __global__ void k_check_triplets(const int32_t* __restrict__ row, const int32_t*
                                  unsigned long long* bad) {
     int count = 0;
     for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnz; e += (int64_t)gridDim.x * kT) {
-        const int32_t r = row[e], c = col[e];
-        count += r < 0 || (int64_t)r >= m || c < 0 || (int64_t)c >= n || !__builtin_isfinite(val[e]);
+        count += unusable(row[e], col[e], val[e], m, n);
     }
     if (count) atomicAdd(bad, (unsigned long long)count);
 }
@@ -1203,14 +1219,14 @@ template <class V>
 hipError_t launch_test_err(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                            const int32_t* rold2new, const int32_t* cold2new, const V* W,
                            const V* H, int64_t m, int64_t n, int32_t k, double* part,
-                           int32_t nparts, double* rejected, const unsigned long long* bad,
+                           int32_t nparts, double* rejected, unsigned long long* bad,
                            hipStream_t s) {
-    if (rejected)
+    if (rejected || bad)
         hipLaunchKernelGGL((k_test_err<V, true>), dim3(nparts), dim3(kT), 0, s, row, col, val, nnz,
                            rold2new, cold2new, W, H, m, n, k, part, rejected, bad);
     else
         hipLaunchKernelGGL((k_test_err<V, false>), dim3(nparts), dim3(kT), 0, s, row, col, val, nnz,
-                           rold2new, cold2new, W, H, m, n, k, part, nullptr, bad);
+                           rold2new, cold2new, W, H, m, n, k, part, nullptr, nullptr);
     return hipGetLastError();
 }
 
@@ -1218,19 +1234,12 @@ template <class V>
 hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                                 const int32_t* rold2new, const int32_t* cold2new, const V* W,
                                 const V* H, const V* WT, const V* HT, int64_t m, int64_t n, int32_t k,
-                                double* part, int32_t nparts,
-                                const unsigned long long* bad, hipStream_t s) {
-    const dim3 grid((unsigned)nparts);
-    const uint32_t pitch = (uint32_t)row_pitch(k);
-    if (WT && HT)
-        hipLaunchKernelGGL((k_test_err_rows<V, true, true>), grid, dim3(kT), 0, s, row, col, val, nnz,
-                           rold2new, cold2new, WT, HT, m, n, (uint32_t)k, pitch, part, bad);
-    else if (HT)
-        hipLaunchKernelGGL((k_test_err_rows<V, false, true>), grid, dim3(kT), 0, s, row, col, val, nnz,
-                           rold2new, cold2new, W, HT, m, n, (uint32_t)k, pitch, part, bad);
-    else
-        hipLaunchKernelGGL((k_test_err_rows<V, true, false>), grid, dim3(kT), 0, s, row, col, val, nnz,
-                           rold2new, cold2new, WT, H, m, n, (uint32_t)k, pitch, part, bad);
+                                double* part, int32_t nparts, unsigned long long* bad, hipStream_t s) {
+    const auto kernel = WT && HT ? (bad ? k_test_err_rows<V, true, true, true> : k_test_err_rows<V, true, true, false>)
+                        : HT ? (bad ? k_test_err_rows<V, false, true, true> : k_test_err_rows<V, false, true, false>)
+                             : (bad ? k_test_err_rows<V, true, false, true> : k_test_err_rows<V, true, false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nparts), dim3(kT), 0, s, row, col, val, nnz, rold2new, cold2new,
+                       WT ? WT : W, HT ? HT : H, m, n, (uint32_t)k, (uint32_t)row_pitch(k), part, bad);
     return hipGetLastError();
 }
 
@@ -1255,7 +1264,7 @@ hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const fl
                                                 int64_t, const int32_t*, const int32_t*,        \
                                                 const V*, const V*, const V*, const V*,         \
                                                 int64_t, int64_t, int32_t, double*, int32_t,    \
-                                                const unsigned long long*, hipStream_t);        \
+                                                unsigned long long*, hipStream_t);              \
     template hipError_t launch_copy_mapped<V, V>(const V*, const int32_t*, V*, const int32_t*,  \
                                                  int64_t, hipStream_t);                         \
     template hipError_t launch_consistency<V>(const V*, const int32_t*, const V*,               \
@@ -1269,8 +1278,7 @@ hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const fl
     template hipError_t launch_test_err<V>(const int32_t*, const int32_t*, const float*,        \
                                            int64_t, const int32_t*, const int32_t*, const V*,   \
                                            const V*, int64_t, int64_t, int32_t, double*,        \
-                                           int32_t, double*, const unsigned long long*,         \
-                                           hipStream_t);
+                                           int32_t, double*, unsigned long long*, hipStream_t);
 CCDK_BUILD_INSTANTIATE(float)
 CCDK_BUILD_INSTANTIATE(double)
 #undef CCDK_BUILD_INSTANTIATE

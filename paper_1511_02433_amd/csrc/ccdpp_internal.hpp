@@ -492,25 +492,21 @@ hipError_t launch_seg_spread(const V* F, int64_t rows, const int32_t* seg_row, i
                              int32_t k, V* out, hipStream_t s);
 template <class V>
 hipError_t launch_sq_sum(const V* v, int64_t n, double* part, int32_t nparts, hipStream_t s);
-// Squared errors of held-out triplets into part[0 .. nparts); when *bad (if given) is not
-// zero no triplet is looked at and the parts are zero; with `rejected`, the
-// triplets are checked on the device and entries out of range or not finite are
-// skipped and counted per block in rejected[0 .. nparts).
+// Squared errors of held-out triplets into part[0 .. nparts).  With `rejected` or `bad` the
+// triplets are checked on the device: entries out of range or not finite are skipped, counted
+// per block in rejected[0 .. nparts) and added to *bad (either may be null).
 template <class V>
 hipError_t launch_test_err(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                            const int32_t* rold2new, const int32_t* cold2new, const V* W,
                            const V* H, int64_t m, int64_t n, int32_t k, double* part,
-                           int32_t nparts, double* rejected, const unsigned long long* bad,
-                           hipStream_t s);
+                           int32_t nparts, double* rejected, unsigned long long* bad, hipStream_t s);
 // The same with a row-major copy of one or both factors over relabelled ids (WT, HT: rows
-// of row_pitch(k) values; null: the column-major W or H serves); triplets checked by the
-// caller.
+// of row_pitch(k) values; null: the column-major W or H serves); checked where `bad` is given.
 template <class V>
 hipError_t launch_test_err_rows(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                                 const int32_t* rold2new, const int32_t* cold2new, const V* W,
                                 const V* H, const V* WT, const V* HT, int64_t m, int64_t n, int32_t k,
-                                double* part, int32_t nparts, const unsigned long long* bad,
-                                hipStream_t s);
+                                double* part, int32_t nparts, unsigned long long* bad, hipStream_t s);
 // Adds the number of triplets out of range or not finite, or of values not finite, to *bad.
 hipError_t launch_check_triplets(const int32_t* row, const int32_t* col, const float* val, int64_t nnz,
                                  int64_t m, int64_t n, unsigned long long* bad, hipStream_t s);
