@@ -1565,14 +1565,23 @@ int launch_sq_sum_any(ccdpp* h, void* p, int64_t n) {
 // one; the turn 2 ps per value, and fresh memory another 3 (taken for few rows at a time
 // in practice: the items).  m = 480,189, n = 17,770, k = 40, 1.4M entries grouped by
 // user: 333 us from the column-major factors, 180 with HT, 73 + 48 for the turn
-// with both.  Without memory the column-major factors serve as they are.
+// with both.  The launches cost some 10 us a turn whatever its size, and columns that the
+// caches hold cost little to gather from, so that few entries times features (kTurnWork) and
+// small factors (kTurnValues) stay as they are (us a call, turned against not: 6,041 x
+// 3,707, k = 64, 64,000 entries 103 against 88, 200,000 151 either way, 400,000 255 against
+// 264; 2,000 x 1,000, k = 64, 400,000 entries 247 against 226; 71,567 x 10,681, k = 20, 400,000
+// entries 218 against 232).  Without memory the column-major factors serve too.
+constexpr int64_t kTurnWork = 8 << 20;
+constexpr int64_t kTurnValues = 1 << 17;
 struct RowFactors {
     Tmp tw, th;
     char *w = nullptr, *h = nullptr;
     void allocate(ccdpp* p, int64_t nnz) {
         const int64_t row = ccdk::row_pitch(p->k) * (p->dbl ? 8 : 4);
         auto side = [&](Tmp& t, char** c, int64_t rows) {
-            if (nnz >= 8 * rows && talloc(p, t, c, rows * row) != hipSuccess) *c = nullptr;
+            if (nnz >= 8 * rows && nnz * p->k >= kTurnWork && rows * p->k >= kTurnValues &&
+                talloc(p, t, c, rows * row) != hipSuccess)
+                *c = nullptr;
         };
         side(tw, &w, p->m);
         side(th, &h, p->n);

@@ -1,7 +1,7 @@
 """The kernels that turn factors between column-major and row-major order, rebuild the
 residual from them and sum held-out errors, at the edges of their tiles: features
 around multiples of 4, 16, 32 and 64, rows around 64, held-out sets that turn neither,
-one or both factors.
+one or both factors, few and many values, entries and windows.
 
 Tolerances: the rebuilt residual is a float64 sum (k terms, below 1e-15 k of the
 summed magnitudes) rounded once to the value type, so it lies within one rounding of
@@ -48,13 +48,48 @@ def test_factors_residual_and_rmse(k, precision):
     bound = np.abs(want) * (2.0 ** -24 if precision == 0 else 0.0) * 1.001 + mag * 4e-16 * (k + 2)
     assert (np.abs(got - want) <= bound).all()
     assert g.check_consistency() == 0
-    # Held-out sets that turn neither factor, H only (8 n <= entries < 8 m), or both.
     for entries in (1, 100, 8 * n, 8 * m, 20_000):
         r = rng.integers(0, m, entries).astype(np.int32)
         c = rng.integers(0, n, entries).astype(np.int32)
         a = rng.standard_normal(entries).astype(np.float32)
         ref = np.sqrt(np.mean((a.astype(np.float64) - (Wd[r] * Hd[c]).sum(1)) ** 2))
         assert abs(g.rmse(r, c, a) - ref) <= 1e-12 * ref
+    g.close()
+
+
+@pytest.mark.parametrize("m,n,turned", [(3_000, 2_000, "both"), (40_000, 2_000, "H"), (2_000, 40_000, "W"),
+                                        (1_800, 1_800, "neither")])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_rmse_from_turned_factors(m, n, turned, precision):
+    # 120,000 entries times 70 features turn a factor of at least 2^17 values and at most
+    # 15,000 rows; with triplets that may not be used, each variant names the first.
+    k, entries = 70, 120_000
+    row, col, val, _ = synth.small_random(m, n, 9_000, k, seed=m)
+    rng = np.random.default_rng(n)
+    W = rng.standard_normal((m, k)).astype(np.float32)
+    H = rng.standard_normal((n, k)).astype(np.float32)
+    print(f"case: {m} x {n}, turned {turned}, precision {precision}", flush=True)
+    g = CCDPP(m, n, k, 0.1, row, col, val, opts=make_options(precision=precision))
+    g.set_factors(W, H)
+    r = rng.integers(0, m, entries).astype(np.int32)
+    c = rng.integers(0, n, entries).astype(np.int32)
+    a = rng.standard_normal(entries).astype(np.float32)
+    err = a.astype(np.float64)
+    for t in range(k):
+        err -= W[:, t].astype(np.float64)[r] * H[:, t].astype(np.float64)[c]
+    ref = np.sqrt(np.mean(err ** 2))
+    got = g.rmse(r, c, a)
+    assert abs(got - ref) <= 1e-12 * ref
+    for arr, x in ((r, m), (c, -1), (a, np.nan)):
+        keep = arr[777], arr[-1]
+        arr[777] = arr[-1] = x
+        with pytest.raises(C.CCDPPError) as ei:
+            g.rmse(r, c, a)
+        assert ei.value.code == C.CCDPP_EINVAL and "777" in str(ei.value)
+        arr[777], arr[-1] = keep
+        assert g.rmse(r, c, a) == got
+    _, hist = g.run_until(1, 1, -1.0, (r, c, a))
+    assert hist[0, 2] == g.rmse(r, c, a)
     g.close()
 
 
