@@ -153,6 +153,10 @@ struct ccdpp {
     // at most temp_keep bytes stay for the next one.
     ccdk::DevicePool kept, temp;
     size_t temp_keep = 0;
+    ccdpp() {
+        kept.set_peer(&temp);
+        temp.set_peer(&kept);
+    }
     ccdk::Stager stage;
     // kernel timing
     bool prof = false;

@@ -380,7 +380,8 @@ private:
 // take() hands out blocks aligned to 256 bytes, first fit; give() returns one, for
 // use by later work on the handle's stream (which orders it after the work that used it
 // before).  expect() sizes the next allocation.  trim(keep) frees allocations that hold
-// no block until at most `keep` bytes stay; release() frees all.
+// no block until at most `keep` bytes stay (hipFree waits for the device); release() frees
+// all.  Before take() fails, it trims both its own pool and its peer's.
 class DevicePool {
 public:
     DevicePool() = default;
@@ -388,6 +389,7 @@ public:
     DevicePool(const DevicePool&) = delete;
     DevicePool& operator=(const DevicePool&) = delete;
     void expect(size_t bytes) { next_ = bytes; }
+    void set_peer(DevicePool* p) { peer_ = p; }
     hipError_t take(void** p, size_t bytes);
     void give(void* p);
     void trim(size_t keep);
@@ -406,6 +408,7 @@ private:
     std::vector<Slab> slabs_;  // (freed ones stay as empty entries)
     std::unordered_map<void*, Block> blocks_;
     size_t held_ = 0, next_ = 0;
+    DevicePool* peer_ = nullptr;
 };
 
 // Whether the device allocation about to be made is to fail (a failure forced from the

@@ -209,6 +209,13 @@ hipError_t DevicePool::take(void** p, size_t bytes) {
             e = hipMalloc(&base, size);
         }
         if (e != hipSuccess) {
+            // What this pool and its peer hold without use goes back to the device first.
+            (void)hipGetLastError();
+            trim(0);
+            if (peer_) peer_->trim(0);
+            e = hipMalloc(&base, size);
+        }
+        if (e != hipSuccess) {
             (void)hipGetLastError();
             return e;
         }
