@@ -1163,6 +1163,7 @@ int create_device(ccdpp* h, const int32_t* row, const int32_t* col, const float*
                     prop.sharedMemPerBlock, kLdsBytes);
     h->cus = prop.multiProcessorCount;
     HIPCK(h, sweep_init());
+    HIPCK(h, build_init());
     // The device address of the allocation-free entry point's scratch, looked up once
     // per device with that device current (host code never uses the array's name).
     if (h->device < 0 || h->device >= kMaxDevices)

@@ -904,6 +904,16 @@ __global__ void k_check_finite(const S* __restrict__ v, int64_t n, unsigned long
 
 }  // namespace
 
+// The limits are the process's, so they are always set to the most any call asks for: a create
+// on another thread cannot lower them between a set and a launch.
+hipError_t build_init() {
+    for (const void* k : {(const void*)k_histogram<true>, (const void*)k_seg_histogram_runs}) {
+        hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kHistLdsBins * 4);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_row_stats(const int32_t* cnt, int64_t rows, int32_t P, int32_t cold_tile,
                             int32_t* stats, hipStream_t s) {
     hipLaunchKernelGGL(k_row_stats, grid_for(rows), dim3(kT), 0, s, cnt, rows, P, cold_tile, stats);
@@ -976,9 +986,6 @@ hipError_t launch_histogram(const int32_t* key, int64_t n, int32_t bins, int32_t
     if (n == 0) return hipSuccess;
     if (bins <= kHistLdsBins) {
         const size_t lds = (size_t)bins * 4;
-        hipError_t e = hipFuncSetAttribute((const void*)k_histogram<true>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
         const int64_t g = std::min<int64_t>(workgroups, (n + 1023) / 1024);
         hipLaunchKernelGGL(k_histogram<true>, dim3((unsigned)g), dim3(1024), lds, s, key, n, bins,
                            count);
@@ -1002,9 +1009,6 @@ hipError_t launch_seg_histogram(const int32_t* lrow, const int32_t* lcol, int64_
     if (nnz == 0) return hipSuccess;
     if (order && rows <= kHistLdsBins) {
         const size_t lds = (size_t)rows * 4;
-        hipError_t e = hipFuncSetAttribute((const void*)k_seg_histogram_runs,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
         // (runs of at least two entries per word that a workgroup clears and adds)
         const int64_t g = std::max<int64_t>(1, std::min<int64_t>(workgroups, nnz / (2 * (int64_t)rows + 1)));
         hipLaunchKernelGGL(k_seg_histogram_runs, dim3((unsigned)g), dim3(1024), lds, s, order, lrow, lcol,

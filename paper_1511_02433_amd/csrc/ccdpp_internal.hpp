@@ -429,6 +429,7 @@ hipError_t launch_reduce_sum(const double* part, int32_t n, double* out, hipStre
 int staged_vectors(PassMode mode, bool x_is_q);
 
 // Device build and utilities (build.hip); V as above, S a host-side element type.
+hipError_t build_init();  // raise the dynamic-LDS limit of the histograms
 // count[key[e]] += 1 over e < n, key[e] < bins (count zeroed by the caller); at most
 // `workgroups` workgroups when the bins fit LDS.
 hipError_t launch_histogram(const int32_t* key, int64_t n, int32_t bins, int32_t* count,

@@ -102,3 +102,40 @@ def test_two_handles_in_two_threads():
         assert np.array_equal(alone[i][0], together[i][0])
         assert np.array_equal(alone[i][1], together[i][1])
         assert alone[i][2] == together[i][2]
+
+
+def test_creates_of_different_sizes_in_two_threads():
+    """Creates on two threads at once whose histograms ask for different amounts of LDS (a
+    kernel's limit is the process's): none fails, and each builds what it builds alone."""
+    import threading
+
+    probs = {300: synth.small_random(300, 200, 4_000, 2, seed=79),
+             32_000: synth.small_random(32_000, 31_000, 90_000, 2, seed=80)}
+    shapes = {300: (300, 200), 32_000: (32_000, 31_000)}
+
+    def fit(size):
+        row, col, val, H0 = probs[size]
+        g = CCDPP(*shapes[size], 2, LAM, row, col, val)
+        g.set_factors(None, H0)
+        g.run(1, 1)
+        f = g.factors()
+        g.close()
+        return f
+
+    alone = {size: fit(size) for size in probs}
+    errors = []
+
+    def job(size):
+        try:
+            for _ in range(30):
+                if not all(np.array_equal(x, y) for x, y in zip(fit(size), alone[size])):
+                    errors.append(f"{size}: other factors")
+        except Exception as e:  # noqa: BLE001
+            errors.append(f"{size}: {e}")
+
+    threads = [threading.Thread(target=job, args=(size,)) for size in probs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(timeout=100)
+    assert not errors, errors[:3]
