@@ -1615,6 +1615,14 @@ struct Held {
     int32_t *row = nullptr, *col = nullptr;
     float* val = nullptr;
     unsigned long long* bad = nullptr;  // h->d_bad, null when the host has checked them
+    // The caller's arrays may be read until the stream has passed their copies: whichever way
+    // the call ends, it waits for that, unless it already has (arrived).
+    hipStream_t stream = nullptr;
+    bool in_flight = false;
+    ~Held() {
+        if (in_flight) (void)hipStreamSynchronize(stream);
+    }
+    void arrived() { in_flight = false; }
     int load(ccdpp* h, int64_t nnz, const int32_t* r, const int32_t* c, const float* v, bool in_use) {
         const hipStream_t s = h->stream;
         const size_t bytes = (size_t)nnz * 4;
@@ -1625,6 +1633,8 @@ struct Held {
         HIPCK(h, talloc(h, tr, &row, nnz));
         HIPCK(h, talloc(h, tc, &col, nnz));
         HIPCK(h, talloc(h, tv, &val, nnz));
+        stream = s;
+        in_flight = true;
         HIPCK(h, h->stage.to_device(row, r, bytes, h->device, s));
         HIPCK(h, h->stage.to_device(col, c, bytes, h->device, s));
         HIPCK(h, h->stage.to_device(val, v, bytes, h->device, s));
@@ -1637,6 +1647,7 @@ struct Held {
         HIPCK(h, ccdk::launch_check_triplets(row, col, val, nnz, h->m, h->n, bad, h->stream));
         HIPCK(h, hipMemcpyAsync(&count, bad, 8, hipMemcpyDeviceToHost, h->stream));
         HIPCK(h, hipStreamSynchronize(h->stream));
+        arrived();
         bad = nullptr;
         return refuse(h, count, nnz, r, c, v);
     }
@@ -2025,6 +2036,7 @@ int ccdpp_run_until(ccdpp_t* h, int32_t max_outer, int32_t inner, double rel_tol
             RCK(launch_test_err_any(h, held.row, held.col, held.val, test_nnz, &rows));
             double sum = 0.0;
             RCK(reduce(&sum));
+            held.arrived();
             te = std::sqrt(sum / (double)test_nnz);
         }
         const double f = h->train_sse + h->lambda * (w2 + h2);
@@ -2080,6 +2092,7 @@ int ccdpp_rmse(ccdpp_t* h, int64_t nnz, const int32_t* row, const int32_t* col, 
     static_assert(sizeof got == 16, "as in d_scalar and d_bad");
     HIPCK(h, hipMemcpyAsync(&got, h->d_scalar, sizeof got, hipMemcpyDeviceToHost, s));
     HIPCK(h, hipStreamSynchronize(s));
+    held.arrived();
     RCK(Held::refuse(h, got.bad, nnz, row, col, val));
     *rmse_out = std::sqrt(got.sum / (double)nnz);
     return CCDPP_OK;

@@ -5,6 +5,7 @@ bad element and change nothing.
 import numpy as np
 import pytest
 
+import paper_1511_02433_amd.ccdpp as C
 from paper_1511_02433_amd import synth
 from paper_1511_02433_amd.ccdpp import CCDPP, CCDPPError, CCDPP_EINVAL
 
@@ -101,4 +102,36 @@ def test_factors_that_are_not_finite_change_nothing(m):
     assert f"H[{(n - 1) * k + 2}] is not finite" in str(ei.value)
     for x, y in zip((W, H, R), g.factors() + (g.residual(),)):
         assert np.array_equal(x, y)
+    g.close()
+
+
+@pytest.mark.parametrize("entries", [1_000, 30_000])
+@pytest.mark.parametrize("outer", [0, 1])
+def test_held_out_arrays_are_read_before_the_call_returns(entries, outer):
+    # Pinned caller memory is copied by the DMA engine, behind the stream's work: the call
+    # waits for it, also where no iteration runs, and where the first pass fails.
+    import torch
+
+    m, n, k = 700, 300, 3
+    row, col, val, H0 = synth.small_random(m, n, 9_000, k, seed=8)
+    g = CCDPP(m, n, k, 0.1, row, col, val)
+    side = torch.cuda.Stream()
+    g.set_stream(side.cuda_stream)
+    rng = np.random.default_rng(entries)
+    pinned = [torch.from_numpy(x).pin_memory() for x in (rng.integers(0, m, entries).astype(np.int32),
+                                                         rng.integers(0, n, entries).astype(np.int32),
+                                                         rng.standard_normal(entries).astype(np.float32))]
+    test = tuple(x.numpy() for x in pinned)
+    print(f"case: {entries} entries, {outer} iterations", flush=True)
+    for fails in (False, True):
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(50_000_000)
+        if fails and outer:
+            C.ccdpp_debug_inject(1, 0)
+            with pytest.raises(CCDPPError):
+                g.run_until(outer, 1, -1.0, test)
+        else:
+            g.run_until(outer, 1, -1.0, test)
+        assert side.query()
+    C.ccdpp_debug_inject(1, -1)
     g.close()
