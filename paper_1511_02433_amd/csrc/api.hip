@@ -304,9 +304,10 @@ void relabel(const std::vector<int32_t>& count, std::vector<int32_t>& new2old,
 // takes; *all receives that sum over all rows, positive when tiling the whole copy pays.
 // Measured for whole user-major copies, one first and two plain passes, hot against tiled:
 // 100M ratings over 500,007 x 400,001 (13.6 per segment) 1033 against 773 us, 40M over
-// 300,007 x 150,001 (19.7) 366 against 267, 20M (11.9) 207 against 183, where the sum is
-// positive; 6M (5.7) 75 against 103, 10M over 300,007 x 60,001 (14.2) 86 against
-// 103, where it is negative.
+// 300,007 x 150,001 (19.7) 366 against 267, where the sum is positive; 6M (5.7) 75 against 103,
+// 10M over 300,007 x 60,001 (14.2) 86 against 103, where it is negative.  20M over 300,007 x
+// 150,001 (11.9) lies on the line, 207 against 183: with flatter popularities it is tiled, with
+// the steeper ones of this measurement it stays hot.
 int64_t choose_split(const std::vector<int32_t>& segs, const std::vector<int32_t>& cold,
                      int64_t seg_cost, int64_t* all) {
     const int64_t rows = (int64_t)segs.size();

@@ -358,14 +358,8 @@ struct DMask {
 typedef uint32_t u32x3a __attribute__((ext_vector_type(3), aligned(4)));
 // The 12-byte index record of a lane in a delta-coded window, aligned to 4 bytes
 // only: loaded through its own type, since deducing load_res's parameter type would
-// drop that alignment.
-template <int CA>
-__device__ __forceinline__ u32x3a load_rec12(const u32x3a* p) {
-    if constexpr (CA == kCacheAll)
-        return *p;
-    else
-        return __builtin_nontemporal_load(p);
-}
+// drop that alignment.  (Copies with cached accesses have no such windows.)
+__device__ __forceinline__ u32x3a load_rec12(const u32x3a* p) { return __builtin_nontemporal_load(p); }
 
 // Data loads of the window block at b (a multiple of kWin): lane l's values from
 // the two halves of the block (val_slot order), its indices in entry order (or,
@@ -401,7 +395,7 @@ __device__ __forceinline__ void load_data(const PassArgs<V>& a, int32_t b, bool 
             // 12 bytes per lane: the window's indices take its first 768 bytes.
             const u32x3a* rp = reinterpret_cast<const u32x3a*>(static_cast<const uint32_t*>(a.idx) +
                                                               b / 2 + 3 * (int)(lo / kE));
-            const u32x3a r = load_rec12<CA>(rp);
+            const u32x3a r = load_rec12(rp);
             w.c0.x = r.x;
             w.c0.y = r.y;
             w.c0.z = r.z;
@@ -758,9 +752,10 @@ __device__ __forceinline__ void pass_main(const PassArgs<V>& a) {
     const int lane = (int)(threadIdx.x & 63u);
 
     // P == 1, float: the rows cut between this workgroup's waves (at most 15), one per
-    // lane of wave 0, finished at the end from the waves' LDS partials.  (The double
-    // kernels are short of registers for it: their layouts leave every cut row to the
-    // combine kernel.)
+    // lane of wave 0, finished at the end from the waves' LDS partials.  (Double layouts leave
+    // every cut row to the combine kernel.  Only their fused hot kernel is short of
+    // registers for the finish: it spills 37 and would spill 44; the fused staged
+    // ones with one tile take 118 of 128 and would take 122.)
     constexpr bool CUT = MODE != kModeFlush && P1 && sizeof(V) == 4;
     const WgHead head = a.wg_head[wg];
     const int4 first = a.wg_first[wg * kWaves + wave];

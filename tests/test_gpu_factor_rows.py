@@ -25,10 +25,10 @@ LAYOUTS = {
 
 
 @pytest.mark.parametrize("k", [1, 3, 4, 5, 16, 17, 32, 33, 64, 67, 130])
+@pytest.mark.parametrize("layout", sorted(LAYOUTS))
 @pytest.mark.parametrize("precision", [0, 1])
-def test_factors_residual_and_rmse(k, precision):
+def test_factors_residual_and_rmse(k, layout, precision):
     m, n = 193, 130
-    layout = sorted(LAYOUTS)[k % 4]
     row, col, val, _ = synth.small_random(m, n, 6_000, k, seed=500 + k)
     rng = np.random.default_rng(900 + k)
     dt = np.float64 if precision else np.float32
