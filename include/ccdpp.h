@@ -29,6 +29,13 @@
  *  - The handle owns all device memory (on the device that was current at
  *    ccdpp_create) and is not thread-safe.  Every call on a handle makes
  *    that device current while it runs and restores the caller's afterwards.
+ *  - Until it is destroyed a handle keeps, besides its residual copies, maps
+ *    and factors, up to max(16 MiB, (m + n) k (v + 8) bytes) of device memory
+ *    for the temporaries of its calls (v: 4 bytes per value, 8 with
+ *    precision 1), and, once its copies of 4 MiB or more add up to 64 MiB,
+ *    48 MiB of pinned host memory to stage such copies.  ccdpp_create needs some 60
+ *    bytes per entry more while it runs (and 20 per (tile, row) pair of a
+ *    tiled copy).
  *  - Calls return CCDPP_OK (0) or a negative status.  Out-parameters are left
  *    untouched on error.  After a device error the handle answers every
  *    later call with CCDPP_ESTATE until it is destroyed.  A failed device
@@ -306,7 +313,8 @@ int ccdpp_profile_read(ccdpp_t *h, int32_t kind, int32_t layout, int64_t *launch
  *   [5] user-major copy gather mode (1 global memory, 2 LDS-staged, 3 hot),
  *   [6] its number of tiles P, [7] tile width T (hot: the hot width), [8] persistent workgroups per
  *   pass, [9] row segments, [10..14] the same five for the item-major copy,
- *   [15] device bytes held, [16] bytes per value (4: float, 8: double),
+ *   [15] device bytes held (the allocations whole: blocks in use, what is free
+ *   between them and the temporaries kept), [16] bytes per value (4: float, 8: double),
  *   [17] user-major rows that the workgroups of a pass finish themselves (cut
  *   between the waves of one workgroup), [18] rows the combine kernel finishes
  *   after each pass, [19..20] the same two for the item-major copy,

@@ -1200,6 +1200,7 @@ int create_device(ccdpp* h, const int32_t* row, const int32_t* col, const float*
     HIPCK(h, talloc(h, t_val, &d_val, N));
     HIPCK(h, talloc(h, t_cr, &d_cnt_r, m));
     HIPCK(h, talloc(h, t_cc, &d_cnt_c, n));
+    if ((size_t)N * 4 >= Stager::kStageMin) h->stage.expect((size_t)N * 12);
     HIPCK(h, h->stage.to_device(d_row, row, (size_t)N * 4, h->device, s));
     HIPCK(h, h->stage.to_device(d_col, col, (size_t)N * 4, h->device, s));
     HIPCK(h, h->stage.to_device(d_val, val, (size_t)N * 4, h->device, s));

@@ -63,6 +63,14 @@ bool Stager::ready() {
     return true;
 }
 
+bool Stager::staged(size_t bytes) {
+    if (bytes < kStageMin) return false;
+    const size_t known = std::min(bytes, expected_);
+    expected_ -= known;
+    seen_ += bytes - known;
+    return seen_ >= kPinFrom && ready();
+}
+
 hipError_t Stager::idle(Slot& sl) {
     if (!sl.busy) return hipSuccess;
     sl.busy = false;
@@ -117,7 +125,7 @@ hipError_t Stager::run(size_t bytes, int device, hipStream_t s, F&& f) {
 hipError_t Stager::to_device(void* dst, const void* src, size_t bytes, int device, hipStream_t s) {
     if (bytes == 0) return hipSuccess;
     if (bytes < kStageMin) return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
-    if (!ready()) {  // no pinned memory: the source may go when this returns
+    if (!staged(bytes)) {  // the source may go when this returns
         hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
         return e == hipSuccess ? hipStreamSynchronize(s) : e;
     }
@@ -140,7 +148,7 @@ hipError_t Stager::to_device(void* dst, const void* src, size_t bytes, int devic
 
 hipError_t Stager::to_host(void* dst, const void* src, size_t bytes, int device, hipStream_t s) {
     if (bytes == 0) return hipSuccess;
-    if (bytes < kStageMin || !ready()) {
+    if (!staged(bytes)) {
         hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
         return e == hipSuccess ? hipStreamSynchronize(s) : e;
     }
