@@ -527,16 +527,17 @@ int build_layout(ccdpp* h, int side, Layout& L, int64_t rows, int64_t cols, cons
         HIPCK(h, talloc(h, tplain, &d_plain, pairs));
         HIPCK(h, scan_segments(d_cnt, pairs, d_segid, d_pad, d_plain, s, take_into(h, ttmp)));
         std::vector<int64_t> tile_pad((size_t)P + 1, 0), tile_base((size_t)P + 1, 0);
-        int32_t last_len = 0;
-        HIPCK(h, hipMemcpy2DAsync(tile_seg.data(), 4, d_segid, (size_t)rows * 4, 4, (size_t)P,
-                                  hipMemcpyDeviceToHost, s));
-        HIPCK(h, hipMemcpy2DAsync(tile_pad.data(), 8, d_pad, (size_t)rows * 8, 8, (size_t)P,
-                                  hipMemcpyDeviceToHost, s));
-        HIPCK(h, hipMemcpyAsync(&tile_pad[P], d_pad + pairs - 1, 8, hipMemcpyDeviceToHost, s));
-        HIPCK(h, hipMemcpyAsync(&last_len, d_cnt + pairs - 1, 4, hipMemcpyDeviceToHost, s));
-        HIPCK(h, hipStreamSynchronize(s));
+        {
+            int64_t* d_heads;  // each tile's first pair in both scans, and the padded total
+            Tmp th;
+            std::vector<int64_t> heads(2 * (size_t)P + 1);
+            HIPCK(h, talloc(h, th, &d_heads, 2 * P + 1));
+            HIPCK(h, launch_tile_heads(d_cnt, d_segid, d_pad, rows, (int32_t)P, d_heads, s));
+            HIPCK(h, h->stage.to_host(heads.data(), d_heads, heads.size() * 8, h->device, s));
+            std::copy(heads.begin(), heads.begin() + P + 1, tile_pad.begin());
+            std::copy(heads.begin() + P + 1, heads.end(), tile_seg.begin());
+        }
         tile_seg[P] = (int32_t)S;
-        tile_pad[P] += (last_len + kE - 1) / kE * kE;
         for (int64_t p = 0; p < P; ++p)
             tile_base[p + 1] = (tile_base[p] + tile_pad[p + 1] - tile_pad[p] + kAlign - 1) / kAlign * kAlign;
         NP = tile_base[P];

@@ -806,6 +806,20 @@ __global__ void k_row_stats(const int32_t* __restrict__ cnt, int64_t rows, int32
     stats[2 * rows + r] = all;
 }
 
+// heads[p] = pad at tile p's first pair (heads[P]: past the last pair), heads[P + 1 + p] = segid
+// there.
+__global__ void k_tile_heads(const int32_t* __restrict__ cnt, const int32_t* __restrict__ segid,
+                             const int64_t* __restrict__ pad, int64_t rows, int32_t P,
+                             int64_t* __restrict__ heads) {
+    const int64_t p = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (p < P) {
+        heads[p] = pad[p * rows];
+        heads[P + 1 + p] = segid[p * rows];
+    } else if (p == P) {
+        heads[P] = pad[P * rows - 1] + ((int64_t)cnt[P * rows - 1] + kE - 1) / kE * kE;
+    }
+}
+
 // (blockIdx.y: the tile)
 __global__ void k_seg_emit(const int32_t* __restrict__ cnt, const int32_t* __restrict__ segid,
                            const int64_t* __restrict__ pad, const int32_t* __restrict__ plain,
@@ -868,6 +882,92 @@ __global__ void k_row_lists(const int32_t* __restrict__ cnt, const int32_t* __re
     }
 }
 
+// The same with a wave per row, a lane per tile: for rows too few to fill the chip and tiles
+// enough for the lanes (row_waves).  (100 rows, 62,500 tiles: 15, 17 and 18 ms with a thread per
+// row.)
+__device__ __forceinline__ int32_t wave_total(int32_t x) {
+    for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d);
+    return x;
+}
+__global__ void k_row_stats_wave(const int32_t* __restrict__ cnt, int64_t rows, int32_t P, int32_t cold_tile,
+                                 int32_t* __restrict__ stats) {
+    const int64_t r = (int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6);
+    const int lane = (int)(threadIdx.x & 63u);
+    if (r >= rows) return;  // (whole waves)
+    int32_t segs = 0, cold = 0, all = 0;
+    for (int64_t p = lane; p < P; p += 64) {
+        const int32_t c = cnt[p * rows + r];
+        segs += c > 0;
+        all += c;
+        if (p >= cold_tile) cold += c;
+    }
+    segs = wave_total(segs);
+    cold = wave_total(cold);
+    all = wave_total(all);
+    if (lane == 0) {
+        stats[r] = segs;
+        stats[rows + r] = cold;
+        stats[2 * rows + r] = all;
+    }
+}
+
+__global__ void k_row_counts_wave(const int32_t* __restrict__ cnt, const int32_t* __restrict__ segid,
+                                  int64_t rows, int32_t P, const int32_t* __restrict__ cut_of,
+                                  const int32_t* __restrict__ cut_off, int32_t* __restrict__ nsegs,
+                                  int32_t* __restrict__ nslots) {
+    const int64_t r = (int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6);
+    const int lane = (int)(threadIdx.x & 63u);
+    if (r > rows) return;
+    int32_t segs = 0, slots = 0;
+    for (int64_t p = lane; r < rows && p < P; p += 64) {
+        const int64_t i = p * rows + r;
+        if (cnt[i] == 0) continue;
+        const int32_t c = cut_of[segid[i]];
+        ++segs;
+        slots += c < 0 ? 1 : cut_off[c + 1] - cut_off[c];
+    }
+    segs = wave_total(segs);
+    slots = wave_total(slots);
+    if (lane == 0) {
+        nsegs[r] = segs;
+        nslots[r] = slots;
+    }
+}
+
+__global__ void k_row_lists_wave(const int32_t* __restrict__ cnt, const int32_t* __restrict__ segid,
+                                 int64_t rows, int32_t P, const int32_t* __restrict__ cut_of,
+                                 const int32_t* __restrict__ cut_off, const int32_t* __restrict__ cut_slot,
+                                 const int32_t* __restrict__ seg_ptr, const int32_t* __restrict__ slot_ptr,
+                                 int32_t* __restrict__ segs, int32_t* __restrict__ slots) {
+    const int64_t r = (int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6);
+    const int lane = (int)(threadIdx.x & 63u);
+    if (r >= rows) return;
+    int32_t a = seg_ptr[r], b = slot_ptr[r];
+    for (int64_t p0 = 0; p0 < P; p0 += 64) {
+        const int64_t i = (p0 + lane) * rows + r;
+        const bool held = p0 + lane < P && cnt[i] != 0;
+        const int32_t sg = held ? segid[i] : 0, c = held ? cut_of[sg] : -1;
+        const int32_t n = !held ? 0 : c < 0 ? 1 : cut_off[c + 1] - cut_off[c];
+        const uint64_t mask = __ballot(held);
+        int32_t upto = n;  // slots of the lanes up to this one
+        for (int d = 1; d < 64; d <<= 1) {
+            const int32_t x = __shfl_up(upto, d);
+            if (lane >= d) upto += x;
+        }
+        if (held) {
+            segs[a + __popcll(mask & ((1ull << lane) - 1))] = sg;
+            const int32_t at = b + upto - n;
+            if (c < 0) {
+                slots[at] = sg;
+            } else {
+                for (int32_t k = 0; k < n; ++k) slots[at + k] = cut_slot[cut_off[c] + k];
+            }
+        }
+        a += __popcll(mask);
+        b += __shfl(upto, 63);
+    }
+}
+
 struct NonEmpty {
     __host__ __device__ int32_t operator()(int32_t c) const { return c > 0; }
 };
@@ -914,9 +1014,20 @@ hipError_t build_init() {
     return hipSuccess;
 }
 
+// Whether a row's pairs take a wave (a thread per row would leave compute units idle).
+static bool row_waves(int64_t rows, int32_t P) { return rows < 16384 && P >= 64; }
 hipError_t launch_row_stats(const int32_t* cnt, int64_t rows, int32_t P, int32_t cold_tile,
                             int32_t* stats, hipStream_t s) {
-    hipLaunchKernelGGL(k_row_stats, grid_for(rows), dim3(kT), 0, s, cnt, rows, P, cold_tile, stats);
+    if (row_waves(rows, P))
+        hipLaunchKernelGGL(k_row_stats_wave, grid_for(rows * 64), dim3(kT), 0, s, cnt, rows, P, cold_tile, stats);
+    else
+        hipLaunchKernelGGL(k_row_stats, grid_for(rows), dim3(kT), 0, s, cnt, rows, P, cold_tile, stats);
+    return hipGetLastError();
+}
+hipError_t launch_tile_heads(const int32_t* cnt, const int32_t* segid, const int64_t* pad, int64_t rows,
+                             int32_t P, int64_t* heads, hipStream_t s) {
+    hipLaunchKernelGGL(k_tile_heads, grid_for((int64_t)P + 1, 1 << 24), dim3(kT), 0, s, cnt, segid, pad, rows,
+                       P, heads);
     return hipGetLastError();
 }
 hipError_t launch_seg_emit(const int32_t* cnt, const int32_t* segid, const int64_t* pad,
@@ -942,16 +1053,24 @@ hipError_t launch_mark_cuts(const int32_t* cut_seg, int64_t n, int32_t* cut_of, 
 hipError_t launch_row_counts(const int32_t* cnt, const int32_t* segid, int64_t rows, int32_t P,
                              const int32_t* cut_of, const int32_t* cut_off, int32_t* nsegs,
                              int32_t* nslots, hipStream_t s) {
-    hipLaunchKernelGGL(k_row_counts, grid_for(rows + 1), dim3(kT), 0, s, cnt, segid, rows, P, cut_of,
-                       cut_off, nsegs, nslots);
+    if (row_waves(rows, P))
+        hipLaunchKernelGGL(k_row_counts_wave, grid_for((rows + 1) * 64), dim3(kT), 0, s, cnt, segid, rows, P,
+                           cut_of, cut_off, nsegs, nslots);
+    else
+        hipLaunchKernelGGL(k_row_counts, grid_for(rows + 1), dim3(kT), 0, s, cnt, segid, rows, P, cut_of,
+                           cut_off, nsegs, nslots);
     return hipGetLastError();
 }
 hipError_t launch_row_lists(const int32_t* cnt, const int32_t* segid, int64_t rows, int32_t P,
                             const int32_t* cut_of, const int32_t* cut_off, const int32_t* cut_slot,
                             const int32_t* seg_ptr, const int32_t* slot_ptr, int32_t* segs,
                             int32_t* slots, hipStream_t s) {
-    hipLaunchKernelGGL(k_row_lists, grid_for(rows), dim3(kT), 0, s, cnt, segid, rows, P, cut_of, cut_off,
-                       cut_slot, seg_ptr, slot_ptr, segs, slots);
+    if (row_waves(rows, P))
+        hipLaunchKernelGGL(k_row_lists_wave, grid_for(rows * 64), dim3(kT), 0, s, cnt, segid, rows, P, cut_of,
+                           cut_off, cut_slot, seg_ptr, slot_ptr, segs, slots);
+    else
+        hipLaunchKernelGGL(k_row_lists, grid_for(rows), dim3(kT), 0, s, cnt, segid, rows, P, cut_of, cut_off,
+                           cut_slot, seg_ptr, slot_ptr, segs, slots);
     return hipGetLastError();
 }
 hipError_t scan_segments(const int32_t* cnt, int64_t n, int32_t* segid, int64_t* pad, int32_t* plain,

@@ -539,6 +539,8 @@ hipError_t launch_check_finite(const S* v, int64_t n, unsigned long long* bad, h
 // (both with a 0 at [rows], for scan_counts) and the lists of them.
 hipError_t launch_row_stats(const int32_t* cnt, int64_t rows, int32_t P, int32_t cold_tile,
                             int32_t* stats, hipStream_t s);
+hipError_t launch_tile_heads(const int32_t* cnt, const int32_t* segid, const int64_t* pad, int64_t rows,
+                             int32_t P, int64_t* heads, hipStream_t s);
 hipError_t launch_seg_emit(const int32_t* cnt, const int32_t* segid, const int64_t* pad,
                            const int32_t* plain, int64_t rows, int32_t P, const int64_t* tile_pad,
                            const int64_t* tile_base, int32_t* seg_row, int64_t* seg_start,

@@ -187,3 +187,33 @@ def test_long_rows_keep_the_finish_in_the_pass(name):
         assert colscaled_max_rel_err(x, y) <= 1e-3
     g.close()
     o.close()
+
+
+@pytest.mark.parametrize("m,tiles", [(90, 63), (90, 64), (90, 65), (1, 130), (700, 200), (16_383, 70), (16_384, 70)])
+def test_many_tiles(m, tiles):
+    # A row's tiles are walked by a wave from 64 tiles on, below 16,384 rows: partials of many
+    # segments, of segments cut between workgroups, and of rows without entries.
+    k, lam, n = 2, 0.3, tiles * 64
+    rng = np.random.default_rng(m + tiles)
+    key = np.unique(np.concatenate([rng.integers(0, m * n, 120_000),
+                                    (m // 2) * n + rng.integers(0, n, 3_000)]))
+    row, col = (key // n).astype(np.int32), (key % n).astype(np.int32)
+    if m > 1:
+        keep = row != m - 1  # the last row is empty
+        row, col = row[keep], col[keep]
+    val = rng.standard_normal(row.size).astype(np.float32)
+    H0 = (rng.standard_normal((n, k)) * 0.1).astype(np.float32)
+    print(f"case: {m} rows, {tiles} tiles", flush=True)
+    for kw in (dict(tile_width=(64, 0)), dict(tile_width=(64, 0), workgroups=37, precision=1)):
+        g = CCDPP(m, n, k, lam, row, col, val, opts=make_options(gather_mode=(2, 0), **kw))
+        info = g.info()
+        assert info["u_tiles"] == tiles
+        g.set_factors(None, H0)
+        o = Oracle(m, n, k, lam, row, col, val, H0)
+        g.run(1, 2)
+        o.run(1, 2)
+        for x, y in zip(g.factors_f64(), o.factors()):
+            assert colscaled_max_rel_err(x, y) <= (1e-9 if "precision" in kw else 1e-3)
+        assert g.check_consistency() == 0
+        g.close()
+        o.close()
