@@ -111,7 +111,8 @@ int ccdpp_create(int64_t m, int64_t n, int32_t k, double lambda, int64_t nnz,
  *   workgroups  : persistent workgroups per pass (0: two per compute unit,
  *                 one for copies of fewer than about 33.5M entries, four for
  *                 copies of more than about 252M, padding included, and at
- *                 most one per 512 entries)
+ *                 most one per 512 entries; copies of up to 2.1M entries take
+ *                 fewer where every share can then start on a row)
  *   seg_weight  : work of one row segment, in entries, when the entries are
  *                 shared out among workgroups and waves (0: the default, 4;
  *                 -1: shares by entries alone)
